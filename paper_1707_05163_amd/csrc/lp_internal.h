@@ -118,22 +118,51 @@ struct RecordParams {
     double *rtemp, *rage;
 };
 
-// GEMM of the surrogate network: C[M x N] = sum_k A(i, k) B(k, j) on bf16 operands
-// with FP32 accumulation, A(i, k) = A[i*sai + k*sak], B(k, j) = B[k*sbk + j*sbj].
-enum : int { kEpiHidden = 0, kEpiOut = 1, kEpiBackData = 2, kEpiAccum = 3 };
-struct GemmArgs {
-    const uint16_t *A, *B;
-    int64_t M, N, K, kchunk;   // M % 32 == 0, N % 32 == 0 (% 128 if N >= 128), K % 16 == 0
-    int64_t sai, sak, sbk, sbj;
-    const float *bias;         // hidden / output: per column
-    float *Z;                  // hidden: FP32 pre-activation out (may be null)
-    uint16_t *H;               // hidden: bf16 GELU(z) out; back-data: bf16 dz out
-    int64_t ldc;               // row stride of Z, H, Zin, dZ
-    float *Y;                  // output: FP32 out; accumulate: FP32 += C
-    int64_t ldy;
-    int32_t nvalid;            // output: columns actually stored
-    const float *Zin;          // back-data: pre-activation of the layer below
-    float *dZ;                 // back-data: FP32 dz out
+// The surrogate network's layers: inputs and outputs, and the outputs padded to whole
+// matrix-core blocks (the last layer's columns 2 .. 31 are zero).
+constexpr int kNetLayers = 5, kNetIn = 64, kNetHid = 256, kNetOut = 2, kNetOutPad = 32;
+constexpr int kNetWeights = kNetIn * kNetHid + 3 * kNetHid * kNetHid + kNetHid * kNetOutPad;
+constexpr int kNetBiases = 4 * kNetHid + kNetOut;
+constexpr int kNetParams = kNetIn * kNetHid + 3 * kNetHid * kNetHid + kNetHid * kNetOut + kNetBiases;
+constexpr int kTrainRows = 32;   // batch rows per block of k_train_pass
+constexpr int kTrainParts = 8;   // parts of the batch that the weight gradients are summed over
+
+// One training step on a batch of `rows` (a multiple of 128) rows.
+struct TrainArgs {
+    const uint16_t *X;               // bf16 features [rows][64]
+    const float *T;                  // targets [rows][2]
+    int64_t rows;
+    float inv_b;                     // 1 / rows
+    const uint16_t *WT[kNetLayers];  // bf16 [pad_out][fan_in]
+    const uint16_t *Wb[kNetLayers];  // bf16 [fan_in][pad_out]
+    const float *bias[kNetLayers];   // FP32 [pad_out]
+    // written by the pass, feature by feature (the weight gradients contract over rows):
+    uint16_t *XT;                    // features [64][rows]
+    uint16_t *HT[kNetLayers - 1];    // hidden activations [256][rows]
+    uint16_t *DT[kNetLayers - 1];    // gradients of the pre-activations [256][rows]
+    uint16_t *DO;                    // gradient of the outputs [2][rows]
+    float *bpart;                    // bias gradients per block [rows / 32][kNetBiases]
+    float *lpart;                    // loss per block [rows / 32]
+    float *wpart;                    // weight gradients [kTrainParts][kNetWeights]
+    int32_t parts;                   // parts in use
+};
+
+// What k_train_update does with the parameters.
+enum : int {
+    kUpCopies = 0,  // bf16 copies of the master weights
+    kUpAdam = 1,    // gradients summed, one Adam step, bf16 copies
+    kUpGrads = 2,   // gradients summed into `out`
+    kUpParams = 3   // master parameters into `out`
+};
+struct UpdateArgs {
+    float *W[kNetLayers], *b[kNetLayers];      // FP32 masters [fan_in][pad_out], [pad_out]
+    float *mW[kNetLayers], *vW[kNetLayers], *mb[kNetLayers], *vb[kNetLayers];
+    uint16_t *Wb[kNetLayers], *WT[kNetLayers];
+    const float *wpart, *bpart, *lpart;
+    int32_t parts, blocks;                     // partial sums: of the weights, of the biases
+    float lr, c1, c2;                          // Adam's step size and bias corrections
+    float *loss;                               // kUpAdam, kUpGrads: the batch loss
+    float *out;                                // packed parameters: W_0, b_0, W_1, ...
 };
 
 // Inference of the surrogate network 64 -> 256 x 4 -> 2 in one kernel: X [rows][64]
@@ -184,16 +213,11 @@ hipError_t launch_slot_values(int store, bool is3d, const void *slot, const floa
                               size_t plane, int nzl, float *U, float *V, float *W, hipStream_t s);
 hipError_t launch_lat_tables(const double *lat, int ny, double *coslat, double *sinlat,
                               hipStream_t s);
-hipError_t launch_gemm(int epi, const GemmArgs &g, hipStream_t s);
+hipError_t launch_train_pass(const TrainArgs &a, hipStream_t s);
+hipError_t launch_train_update(int mode, const UpdateArgs &u, hipStream_t s);
 hipError_t launch_mlp_fused(const MlpFusedArgs &a, hipStream_t s);
-hipError_t launch_loss_grad(const float *Y, const float *T, int64_t B, int ldy, float *dZ,
-                            uint16_t *dZq, float *loss, hipStream_t s);
-hipError_t launch_colsum(const float *dZ, int64_t B, int N, float *db, hipStream_t s);
-hipError_t launch_adam(float *W, const float *G, float *m, float *v, int K, int N, int nvalid,
-                       float lr, float b1, float b2, float eps, int t, uint16_t *Wb, uint16_t *WT,
-                       hipStream_t s);
-hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s);
-hipError_t launch_to_bf16(const float *x, int64_t n, uint16_t *y, hipStream_t s);
+// the first nvalid of n values rounded to bf16, the rest zero
+hipError_t launch_to_bf16(const float *x, int64_t nvalid, int64_t n, uint16_t *y, hipStream_t s);
 hipError_t launch_level_absmax(const float *F, size_t plane, int nzl, float *out,
                                hipStream_t s);
 

@@ -5,12 +5,10 @@
 // and activations are bfloat16, products accumulate in FP32 on the gfx950 matrix
 // cores (v_mfma_f32_32x32x16_bf16), and the optimiser keeps FP32 master weights.
 //
-// One GEMM kernel serves every product:
-//   C[M x N] = sum_k A(i, k) B(k, j),  A(i, k) = A[i*sai + k*sak], B(k, j) = B[k*sbk + j*sbj]
-// Each wave owns a 32-row band and NB 32-column blocks of C; a block is 4 waves
-// (128 rows).  A k-step of 16 feeds one 32x32x16 MFMA per column block.  Operand
-// fragments are loaded straight from global memory (weights and activation tiles
-// stay in L2); with a unit k-stride a lane's eight bf16 values are one 16-byte load.
+// A training step is three kernels: k_train_pass (forward, loss and the gradients of
+// every pre-activation, 32 rows a block), k_train_wgrad (the weight gradients, partial
+// sums over eight parts of the batch) and k_train_update (their sum, Adam and the
+// bfloat16 copies).  Inference is one kernel, k_mlp_fused.
 #include "lp_internal.h"
 
 namespace lp {
@@ -22,15 +20,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr float kC0 = 0.7978845608028654f;  // sqrt(2/pi)
 constexpr float kC1 = 0.044715f;
 
-__device__ inline float gelu(float x)
-{
-    return 0.5f * x * (1.f + tanhf(kC0 * (x + kC1 * x * x * x)));
-}
-
-__device__ inline float gelu_grad(float x)
+// GELU(x) and its derivative
+__device__ inline void gelu_and_grad(float x, float &g, float &gg)
 {
     const float t = tanhf(kC0 * (x + kC1 * x * x * x));
-    return 0.5f * (1.f + t) + 0.5f * x * (1.f - t * t) * kC0 * (1.f + 3.f * kC1 * x * x);
+    g = 0.5f * x * (1.f + t);
+    gg = 0.5f * (1.f + t) + 0.5f * x * (1.f - t * t) * kC0 * (1.f + 3.f * kC1 * x * x);
 }
 
 __device__ inline uint16_t bf16_bits(float f)
@@ -42,150 +37,12 @@ __device__ inline uint16_t bf16_bits(float f)
     return (uint16_t)(b >> 16);
 }
 
-__device__ inline float bf16_float(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-// eight consecutive-k values of A(i, .) or B(., j) as an MFMA operand
-__device__ inline bf16x8 frag(const uint16_t *p, int64_t kstride)
-{
-    if (kstride == 1)
-        return *reinterpret_cast<const bf16x8 *>(p);
-    bf16x8 v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        v[e] = __builtin_bit_cast(__bf16, p[e * kstride]);
-    return v;
-}
-
-}  // namespace
-
-namespace {
-
-template <int EPI, int NB>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
-{
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t row0 = (int64_t)blockIdx.x * 128 + wave * 32;
-    if (row0 >= g.M)  // a 32-row band past the end (M is a multiple of 32)
-        return;
-    const int64_t col0 = (int64_t)blockIdx.y * (32 * NB);
-    const int64_t k_lo = (int64_t)blockIdx.z * g.kchunk;
-    const int64_t k_hi = k_lo + g.kchunk < g.K ? k_lo + g.kchunk : g.K;
-    f32x16 acc[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-        acc[b] = f32x16{0.f};
-    const int r = lane & 31, kh = (lane >> 5) * 8;
-    const uint16_t *Ar = g.A + (row0 + r) * g.sai;
-    for (int64_t k0 = k_lo; k0 < k_hi; k0 += 16) {
-        const bf16x8 a = frag(Ar + (k0 + kh) * g.sak, g.sak);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const bf16x8 bb = frag(g.B + (k0 + kh) * g.sbk + (col0 + b * 32 + r) * g.sbj, g.sbk);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bb, acc[b], 0, 0, 0);
-        }
-    }
-    // accumulator layout: value v of lane l is C[8 (v/4) + 4 (l/32) + v%4][l%32]
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int64_t j = col0 + b * 32 + r;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t i = row0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            const float c = acc[b][v];
-            if constexpr (EPI == kEpiHidden) {
-                const float z = c + g.bias[j];
-                if (g.Z)
-                    g.Z[i * g.ldc + j] = z;
-                g.H[i * g.ldc + j] = bf16_bits(gelu(z));
-            } else if constexpr (EPI == kEpiOut) {
-                if (j < g.nvalid)
-                    g.Y[i * g.ldy + j] = c + g.bias[j];
-            } else if constexpr (EPI == kEpiBackData) {
-                const float dz = c * gelu_grad(g.Zin[i * g.ldc + j]);
-                g.dZ[i * g.ldc + j] = dz;
-                g.H[i * g.ldc + j] = bf16_bits(dz);
-            } else {
-                atomicAdd(&g.Y[i * g.ldy + j], c);
-            }
-        }
-    }
-}
-
-// dY = (Y - T) / B on the two outputs, zero on the padding columns; also bf16 copy
-__global__ void k_loss_grad(const float *Y, const float *T, int64_t B, int ldy, float inv_b,
-                            float *dZ, uint16_t *dZq, float *loss)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= B * ldy)
-        return;
-    const int64_t row = i / ldy;
-    const int col = (int)(i % ldy);
-    float d = 0.f;
-    if (col < 2) {
-        const float e = Y[row * ldy + col] - T[row * 2 + col];
-        d = e * inv_b;
-        atomicAdd(loss, 0.5f * e * e * inv_b);
-    }
-    dZ[i] = d;
-    dZq[i] = bf16_bits(d);
-}
-
-// column sums of dZ [B x N] (bias gradients)
-__global__ void k_colsum(const float *dZ, int64_t B, int N, float *db)
-{
-    const int j = blockIdx.x;
-    float s = 0.f;
-    for (int64_t i = threadIdx.x; i < B; i += blockDim.x)
-        s += dZ[i * N + j];
-    for (int off = 32; off > 0; off >>= 1)
-        s += __shfl_xor(s, off, 64);
-    __shared__ float ws[4];
-    if ((threadIdx.x & 63) == 0)
-        ws[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        db[j] = ws[0] + ws[1] + ws[2] + ws[3];
-}
-
-// Adam on an FP32 master tensor [K x N]; also writes the bf16 copies W [K x N] and
-// W^T [N x K].  Columns >= nvalid (output padding) stay zero.
-__global__ void k_adam(float *W, const float *G, float *m, float *v, int K, int N, int nvalid,
-                       float lr, float b1, float b2, float eps, float c1, float c2, uint16_t *Wb,
-                       uint16_t *WT)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= (int64_t)K * N)
-        return;
-    const int k = (int)(i / N), j = (int)(i % N);
-    float w = W[i];
-    if (j < nvalid && G) {
-        const float g = G[i];
-        const float mm = b1 * m[i] + (1.f - b1) * g;
-        const float vv = b2 * v[i] + (1.f - b2) * g * g;
-        m[i] = mm;
-        v[i] = vv;
-        w -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-        W[i] = w;
-    }
-    const uint16_t h = bf16_bits(j < nvalid ? w : 0.f);
-    if (Wb)
-        Wb[i] = h;
-    if (WT)
-        WT[(int64_t)j * K + k] = h;
-}
-
-__global__ void k_fill_f32(float *p, float v, int64_t n)
+// the first nvalid of n values rounded, the rest zero
+__global__ void k_to_bf16(const float *x, int64_t nvalid, int64_t n, uint16_t *y)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-__global__ void k_to_bf16(const float *x, int64_t n, uint16_t *y)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = bf16_bits(x[i]);
+        y[i] = i < nvalid ? bf16_bits(x[i]) : (uint16_t)0;
 }
 
 // ---------------------------------------------------------------- fused inference
@@ -423,6 +280,404 @@ __global__ __launch_bounds__(kFusedThreads) void k_mlp_fused(MlpFusedArgs a)
     }
 }
 
+// ---------------------------------------------------------------- training
+// Forward, loss and backward to every pre-activation for 32 rows of the batch, in one
+// kernel: the layers one after the other inside a block, so the activations never leave
+// it (layer by layer through memory a step was about 35 launches of 4 to 40 us).  Eight
+// waves; wave w owns output features 32 w .. 32 w + 31 of every layer, computed
+// transposed as in k_mlp_fused: weights (16 fragments straight from L2, each used once
+// by the block) are the matrix core's A operand, the layer's inputs its B operand, read
+// from LDS where the waves leave them bf16 [row][feature].  A wave keeps the derivative
+// of its features' GELU in registers from the forward pass for the backward one.  The
+// products take k in increasing order into one accumulator per output from zero, the
+// bias is added after them, and values round to bf16 where they are handed on, as the
+// layers' definition says, so a step's gradients do not depend on the batch's split.
+// 32 rows a block because the matrix instruction is 32 wide and a batch of 4096 then
+// fills half the CUs; what bounds a block is reading the weights (1.1 MB at 64 B per
+// clock, about 8 us).
+constexpr int kActStride = kNetHid + 8;  // bf16 per activation row in LDS (no conflicts)
+
+// Two rows' bf16 values of two adjacent features, exchanged between neighbouring lanes
+// (rows r and r ^ 1): lane r even gets feature v of rows r, r + 1, lane r odd feature
+// v + 1 of rows r - 1, r.
+__device__ inline uint32_t pair_rows(uint32_t p, int r)
+{
+    const uint32_t q = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xB1, 0xF, 0xF, true);
+    return (r & 1) ? (q >> 16) | (p & 0xFFFF0000u) : (p & 0xFFFFu) | (q << 16);
+}
+
+// One wave's 32 features of 32 rows as bf16: into the LDS rows at act, and feature by
+// feature to dst [256][rows].
+__device__ inline void put_features(const float g[16], uint16_t *act, uint16_t *dst, int64_t rows,
+                                    int64_t row0, int f0, int r, int h)
+{
+    uint32_t P[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        P[j] = pack_bf16(g[2 * j], g[2 * j + 1]);
+    // one lane offset for every store; the rest of the address is the wave's
+    const uint32_t at = (uint32_t)(4 * h + (r & 1)) * (uint32_t)rows + (uint32_t)(r & ~1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        *reinterpret_cast<uint2 *>(act + r * kActStride + f0 + 8 * q + 4 * h) =
+            uint2{P[2 * q], P[2 * q + 1]};
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            *reinterpret_cast<uint32_t *>(dst + (int64_t)(f0 + 8 * q + 2 * j) * rows + row0 + at) =
+                pair_rows(P[2 * q + j], r);
+    }
+}
+
+// The sums over the block's 32 rows of one wave's 32 features, to out[f0 ..]: halves of
+// the 16 values trade between lanes until each lane holds one value of 16 rows.
+__device__ inline void put_row_sums(const float g[16], float *out, int f0, int r, int h)
+{
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        v[i] = g[i];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int n = 8 >> s, hi = (r >> s) & 1;
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+            const float keep = hi ? v[i + n] : v[i], give = hi ? v[i] : v[i + n];
+            v[i] = keep + __shfl_xor(give, 1 << s, 64);
+        }
+    }
+    const float t = v[0] + __shfl_xor(v[0], 16, 64);
+    const int i = 8 * (r & 1) + 4 * ((r >> 1) & 1) + 2 * ((r >> 2) & 1) + ((r >> 3) & 1);
+    if (r < 16)
+        out[f0 + 8 * (i >> 2) + 4 * h + (i & 3)] = t;
+}
+
+template <int LO, int HI>
+__device__ inline void load_frags(bf16x8 (&w)[16], const uint16_t *p)
+{
+#pragma unroll
+    for (int i = LO; i < HI; ++i)
+        w[i] = *reinterpret_cast<const bf16x8 *>(p + 16 * i);
+}
+
+// Products of the wave's fragments with the LDS rows (256 inputs).
+__device__ inline f32x16 act_product(const bf16x8 (&w)[16], const uint16_t *act, int r, int h)
+{
+    f32x16 acc = {};
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            w[i], *reinterpret_cast<const bf16x8 *>(act + r * kActStride + 16 * i + 8 * h), acc, 0,
+            0, 0);
+    return acc;
+}
+
+__global__ __launch_bounds__(512) void k_train_pass(TrainArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t act[kTrainRows * kActStride];
+    __shared__ float4 grad[4][4][512];  // GELU derivatives [layer][value / 4][thread]
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int f0 = 32 * wave;
+    const int64_t row0 = (int64_t)blockIdx.x * kTrainRows, row = row0 + r, rows = a.rows;
+    bf16x8 w[16], x[4];
+    load_frags<0, 4>(w, a.WT[0] + (f0 + r) * kNetIn + 8 * h);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        x[i] = *reinterpret_cast<const bf16x8 *>(a.X + row * kNetIn + 16 * i + 8 * h);
+    {  // the input features, transposed: wave w takes features 8 w .. 8 w + 7
+        const int f = 8 * wave + 4 * h;
+        const uint2 q = *reinterpret_cast<const uint2 *>(a.X + row * kNetIn + f);
+        const uint32_t p0 = pair_rows(q.x, r), p1 = pair_rows(q.y, r);
+        *reinterpret_cast<uint32_t *>(a.XT + (f + (r & 1)) * rows + row0 + (r & ~1)) = p0;
+        *reinterpret_cast<uint32_t *>(a.XT + (f + 2 + (r & 1)) * rows + row0 + (r & ~1)) = p1;
+    }
+    float g[16];
+    f32x16 acc = {};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[i], x[i], acc, 0, 0, 0);
+    // The layers share one piece of code (unrolled, a block spent its time fetching 36 KB
+    // of instructions, each used once).  The next layer's weights (after the last hidden
+    // layer the output layer's 32 rows, two of them outputs, for every wave) are on their
+    // way across the GELU.
+#pragma unroll 1
+    for (int l = 0; l < 4; ++l) {
+        float4 bq[4];  // (read before the weights: reads return in order)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            bq[q] = *reinterpret_cast<const float4 *>(a.bias[l] + f0 + 4 * h + 8 * q);
+        __builtin_amdgcn_sched_barrier(0);
+        load_frags<0, 16>(w, l < 3 ? a.WT[l + 1] + (f0 + r) * kNetHid + 8 * h
+                                   : a.WT[4] + r * kNetHid + 8 * h);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 b = bq[q];
+            float4 d;
+            gelu_and_grad(acc[4 * q + 0] + b.x, g[4 * q + 0], d.x);
+            gelu_and_grad(acc[4 * q + 1] + b.y, g[4 * q + 1], d.y);
+            gelu_and_grad(acc[4 * q + 2] + b.z, g[4 * q + 2], d.z);
+            gelu_and_grad(acc[4 * q + 3] + b.w, g[4 * q + 3], d.w);
+            grad[l][q][threadIdx.x] = d;
+        }
+        if (l)
+            __syncthreads();  // every wave has read the layer before
+        put_features(g, act, a.HT[l], rows, row0, f0, r, h);
+        __syncthreads();
+        acc = act_product(w, act, r, h);
+    }
+    // outputs and their gradient: every wave computes them, so none waits for another
+    float d0 = 0.f, d1 = 0.f, loss = 0.f;
+    if (h == 0) {  // outputs 0 and 1 of row r are values 0 and 1 of the lower half-wave
+        const float2 t = *reinterpret_cast<const float2 *>(a.T + 2 * row);
+        const float e0 = (acc[0] + a.bias[4][0]) - t.x, e1 = (acc[1] + a.bias[4][1]) - t.y;
+        d0 = e0 * a.inv_b;
+        d1 = e1 * a.inv_b;
+        loss = 0.5f * e0 * e0 * a.inv_b + 0.5f * e1 * e1 * a.inv_b;
+    }
+    const uint32_t dq = pack_bf16(d0, d1);  // zero in the upper half-wave, as its k's are
+    if (wave == 0) {
+        float s0 = d0, s1 = d1;
+        for (int off = 16; off > 0; off >>= 1) {
+            loss += __shfl_xor(loss, off, 64);
+            s0 += __shfl_xor(s0, off, 64);
+            s1 += __shfl_xor(s1, off, 64);
+        }
+        if (lane == 0) {
+            a.lpart[blockIdx.x] = loss;
+            a.bpart[(int64_t)blockIdx.x * kNetBiases + 4 * kNetHid] = s0;
+            a.bpart[(int64_t)blockIdx.x * kNetBiases + 4 * kNetHid + 1] = s1;
+        }
+        if (h == 0) {
+            a.DO[row] = (uint16_t)(dq & 0xFFFFu);
+            a.DO[rows + row] = (uint16_t)(dq >> 16);
+        }
+    }
+    // backward: the gradient of layer l's pre-activations from layer l + 1's; the outputs'
+    // 30 padding columns are zero, so their product takes the first 16 of 32 k's
+    const bf16x8 wo = *reinterpret_cast<const bf16x8 *>(a.Wb[4] + (f0 + r) * kNetOutPad + 8 * h);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+        wo, __builtin_bit_cast(bf16x8, u32x4_t{dq, 0u, 0u, 0u}), f32x16{}, 0, 0, 0);
+#pragma unroll 1
+    for (int l = 3; l >= 0; --l) {
+        if (l)
+            load_frags<0, 16>(w, a.Wb[l] + (f0 + r) * kNetHid + 8 * h);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 d = grad[l][q][threadIdx.x];
+            g[4 * q + 0] = acc[4 * q + 0] * d.x;
+            g[4 * q + 1] = acc[4 * q + 1] * d.y;
+            g[4 * q + 2] = acc[4 * q + 2] * d.z;
+            g[4 * q + 3] = acc[4 * q + 3] * d.w;
+        }
+        __syncthreads();  // every wave has read the layer before
+        put_features(g, act, a.DT[l], rows, row0, f0, r, h);
+        put_row_sums(g, a.bpart + (int64_t)blockIdx.x * kNetBiases + l * kNetHid, f0, r, h);
+        if (l == 0)
+            break;
+        __syncthreads();
+        acc = act_product(w, act, r, h);
+    }
+}
+
+// Weight gradients: dW_l[k][n] = sum over rows of H_l-1[row][k] dZ_l[row][n], a 64 x 64
+// tile of one layer (64 x 32 of the output layer) and one part of the batch per block,
+// 32 x 32 per wave.  Both operands come feature by feature; 128 rows of the tile's 64 + 64
+// features at a time go through LDS, each feature's rows read by 16 neighbouring lanes
+// (read straight into the fragments, a load touched 32 cache lines and their lookup was
+// the bound: 21.8 us a step of 4096 rows).  The parts are summed by k_train_update in
+// order, so a step's gradients are the same from run to run (atomic adds were not).
+constexpr int kWgradTiles = 4 + 3 * 16 + 4, kWgradRows = 128;
+constexpr int kWgradStride = kWgradRows + 8;  // bf16 per LDS row (no conflicts)
+
+__global__ __launch_bounds__(256) void k_train_wgrad(TrainArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[128 * kWgradStride];
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int t = blockIdx.x, l, off = 0, N = kNetHid, ti, tj;
+    if (t < 4) {
+        l = 0, ti = 0, tj = t;
+    } else if (t < 52) {
+        t -= 4;
+        l = 1 + (t >> 4), ti = (t >> 2) & 3, tj = t & 3;
+        off = kNetIn * kNetHid + (l - 1) * kNetHid * kNetHid;
+    } else {
+        l = 4, ti = t - 52, tj = 0, N = kNetOutPad;
+        off = kNetWeights - kNetHid * kNetOutPad;
+    }
+    const int64_t rows = a.rows, per = (rows / 128 + a.parts - 1) / a.parts * 128;
+    const int64_t lo = (int64_t)blockIdx.y * per, hi = lo + per < rows ? lo + per : rows;
+    // thread t loads 16 bytes of features t/16 + 16 i: of the inputs (i < 4) and of the
+    // gradients (i >= 4; the outputs' gradient has two features, its padding is zero)
+    const int f = threadIdx.x >> 4, c = 8 * (threadIdx.x & 15);
+    const uint16_t *A = (l == 0 ? a.XT : a.HT[l - 1]) + (int64_t)(64 * ti + f) * rows + c;
+    const uint16_t *B = (l < 4 ? a.DT[l] : a.DO) + (int64_t)(64 * tj + f) * rows + c;
+    u32x4_t p[8];
+    auto load = [&](int64_t k) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = *reinterpret_cast<const u32x4_t *>(A + (int64_t)(16 * i) * rows + k);
+            p[4 + i] = u32x4_t{};
+            if (l < 4 || f + 16 * i < kNetOut)
+                p[4 + i] = *reinterpret_cast<const u32x4_t *>(B + (int64_t)(16 * i) * rows + k);
+        }
+    };
+    const int i0 = 32 * (wave & 1), j0 = 32 * (wave >> 1);
+    f32x16 acc = {};
+    if (lo < hi)
+        load(lo);
+    for (int64_t k = lo; k < hi; k += kWgradRows) {
+        if (k > lo)
+            __syncthreads();  // every wave has read the rows before
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            *reinterpret_cast<u32x4_t *>(tile + (16 * i + f) * kWgradStride + c) = p[i];
+        __syncthreads();
+        if (k + kWgradRows < hi)
+            load(k + kWgradRows);
+#pragma unroll
+        for (int i = 0; i < kWgradRows / 16; ++i)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                *reinterpret_cast<const bf16x8 *>(tile + (i0 + r) * kWgradStride + 16 * i + 8 * h),
+                *reinterpret_cast<const bf16x8 *>(tile + (64 + j0 + r) * kWgradStride + 16 * i +
+                                                  8 * h),
+                acc, 0, 0, 0);
+    }
+    if (64 * tj + j0 >= N)
+        return;
+    float *out = a.wpart + (int64_t)blockIdx.y * kNetWeights + off;
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        out[(64 * ti + i0 + 8 * (v >> 2) + 4 * h + (v & 3)) * N + 64 * tj + j0 + r] = acc[v];
+}
+
+__device__ inline float adam_step(float w, float g, float &m, float &v, const UpdateArgs &u)
+{
+    constexpr float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float mm = b1 * m + (1.f - b1) * g;
+    const float vv = b2 * v + (1.f - b2) * g * g;
+    m = mm;
+    v = vv;
+    return w - u.lr * (mm / u.c1) / (sqrtf(vv / u.c2) + eps);
+}
+
+// The parameters, a 32 x 32 tile of one layer's weights per block and after those 64
+// biases per block: their gradients summed over the partial sums in order and, by MODE,
+// applied (Adam, with the bf16 copies W and W^T; the transpose goes through LDS so that
+// both are written in runs) or written out packed.  Padding columns stay zero.
+constexpr int kUpdateTiles = 16 + 3 * 64 + 8, kUpdateBias = (kNetBiases + 63) / 64;
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_train_update(UpdateArgs u)
+{
+    constexpr bool kGrad = MODE == kUpAdam || MODE == kUpGrads;
+    __shared__ float part[4][64];
+    __shared__ uint16_t tr[32][34];
+    int t = blockIdx.x;
+    if (t >= kUpdateTiles) {  // biases: 64 a block, four threads to each sum
+        const int e = (t - kUpdateTiles) * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
+        float s = 0.f;
+        if (kGrad) {
+            if (e < kNetBiases)
+                for (int k = q; k < u.blocks; k += 4)
+                    s += u.bpart[(int64_t)k * kNetBiases + e];
+            part[q][threadIdx.x & 63] = s;
+            __syncthreads();
+        }
+        if (q == 0 && e < kNetBiases) {
+            const int l = e >> 8, j = e & 255;
+            const int at = l < 4 ? kNetIn * kNetHid + l * (kNetHid * kNetHid + kNetHid) + j
+                                 : kNetParams - kNetOut + j;
+            if (kGrad)
+                s = (part[0][threadIdx.x] + part[1][threadIdx.x]) +
+                    (part[2][threadIdx.x] + part[3][threadIdx.x]);
+            if (MODE == kUpAdam)
+                u.b[l][j] = adam_step(u.b[l][j], s, u.mb[l][j], u.vb[l][j], u);
+            else if (MODE == kUpGrads)
+                u.out[at] = s;
+            else if (MODE == kUpParams)
+                u.out[at] = u.b[l][j];
+        }
+        if (kGrad && blockIdx.x == gridDim.x - 1 && q == 1 && u.loss) {
+            float s1 = 0.f;
+            for (int k = threadIdx.x & 63; k < u.blocks; k += 64)
+                s1 += u.lpart[k];
+            for (int o = 32; o > 0; o >>= 1)
+                s1 += __shfl_xor(s1, o, 64);
+            if ((threadIdx.x & 63) == 0)
+                *u.loss = s1;
+        }
+        return;
+    }
+    int l, ti, tj, off, pk;
+    if (t < 16) {
+        l = 0, ti = t >> 3, tj = t & 7, off = 0, pk = 0;
+    } else if (t < 208) {
+        t -= 16;
+        l = 1 + (t >> 6), ti = (t >> 3) & 7, tj = t & 7;
+        off = kNetIn * kNetHid + (l - 1) * kNetHid * kNetHid;
+        pk = off + l * kNetHid;
+    } else {
+        l = 4, ti = t - 208, tj = 0, off = kNetWeights - kNetHid * kNetOutPad;
+        pk = off + 4 * kNetHid;
+    }
+    const int K = l == 0 ? kNetIn : kNetHid, N = l < 4 ? kNetHid : kNetOutPad;
+    const int nvalid = l < 4 ? kNetHid : kNetOut;
+    const int c = threadIdx.x & 31, j = 32 * tj + c, r0 = threadIdx.x >> 5;
+    const bool live = kGrad && j < nvalid;
+    // every read of the thread's four weights first (absent parts read the last one)
+    float w[4], mm[4], vv[4], q[4][kTrainParts];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const int i = (32 * ti + r0 + 8 * n) * N + j;
+        w[n] = MODE == kUpGrads ? 0.f : u.W[l][i];
+        if (live) {
+#pragma unroll
+            for (int p = 0; p < kTrainParts; ++p)
+                q[n][p] = u.wpart[(int64_t)(p < u.parts ? p : u.parts - 1) * kNetWeights + off + i];
+            if (MODE == kUpAdam) {
+                mm[n] = u.mW[l][i];
+                vv[n] = u.vW[l][i];
+            }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const int k = 32 * ti + r0 + 8 * n, i = k * N + j;
+        if (live) {
+            float g = 0.f;
+#pragma unroll
+            for (int p = 0; p < kTrainParts; ++p)
+                g += p < u.parts ? q[n][p] : 0.f;
+            if (MODE == kUpAdam) {
+                w[n] = adam_step(w[n], g, mm[n], vv[n], u);
+                u.W[l][i] = w[n];
+                u.mW[l][i] = mm[n];
+                u.vW[l][i] = vv[n];
+            } else {
+                w[n] = g;
+            }
+        }
+        if (MODE == kUpGrads || MODE == kUpParams) {
+            if (j < nvalid)
+                u.out[pk + k * nvalid + j] = w[n];
+        } else {
+            const uint16_t b = bf16_bits(j < nvalid ? w[n] : 0.f);
+            u.Wb[l][i] = b;
+            tr[c][r0 + 8 * n] = b;
+        }
+    }
+    if (MODE == kUpGrads || MODE == kUpParams)
+        return;
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const int rr = r0 + 8 * n;
+        u.WT[l][(32 * tj + rr) * K + 32 * ti + c] = tr[rr][c];
+    }
+}
+
 }  // namespace
 
 hipError_t launch_mlp_fused(const MlpFusedArgs &a, hipStream_t s)
@@ -442,76 +697,33 @@ hipError_t launch_mlp_fused(const MlpFusedArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_gemm(int epi, const GemmArgs &g, hipStream_t s)
+hipError_t launch_train_pass(const TrainArgs &a, hipStream_t s)
 {
-    if (g.M % 32 || g.K % 16 || g.kchunk % 16 || g.kchunk <= 0)
+    if (a.rows <= 0 || a.rows % 128 || a.parts < 1 || a.parts > kTrainParts)
         return hipErrorInvalidValue;
-    const int nb = g.N >= 128 ? 4 : 1;
-    if (g.N % (32 * nb))
-        return hipErrorInvalidValue;
-    const dim3 grid((uint32_t)((g.M + 127) / 128), (uint32_t)(g.N / (32 * nb)),
-                    (uint32_t)((g.K + g.kchunk - 1) / g.kchunk));
-#define LP_G(E, NBV) hipLaunchKernelGGL((k_gemm<E, NBV>), grid, dim3(256), 0, s, g)
-    if (nb == 4) {
-        switch (epi) {
-        case kEpiHidden: LP_G(kEpiHidden, 4); break;
-        case kEpiOut: LP_G(kEpiOut, 4); break;
-        case kEpiBackData: LP_G(kEpiBackData, 4); break;
-        case kEpiAccum: LP_G(kEpiAccum, 4); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        switch (epi) {
-        case kEpiHidden: LP_G(kEpiHidden, 1); break;
-        case kEpiOut: LP_G(kEpiOut, 1); break;
-        case kEpiBackData: LP_G(kEpiBackData, 1); break;
-        case kEpiAccum: LP_G(kEpiAccum, 1); break;
-        default: return hipErrorInvalidValue;
-        }
+    hipLaunchKernelGGL(k_train_pass, dim3((uint32_t)(a.rows / kTrainRows)), dim3(512), 0, s, a);
+    hipLaunchKernelGGL(k_train_wgrad, dim3(kWgradTiles, (uint32_t)a.parts), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_update(int mode, const UpdateArgs &u, hipStream_t s)
+{
+    const dim3 grid(kUpdateTiles + kUpdateBias), blk(256);
+    switch (mode) {
+    case kUpCopies: hipLaunchKernelGGL(k_train_update<kUpCopies>, grid, blk, 0, s, u); break;
+    case kUpAdam: hipLaunchKernelGGL(k_train_update<kUpAdam>, grid, blk, 0, s, u); break;
+    case kUpGrads: hipLaunchKernelGGL(k_train_update<kUpGrads>, grid, blk, 0, s, u); break;
+    case kUpParams: hipLaunchKernelGGL(k_train_update<kUpParams>, grid, blk, 0, s, u); break;
+    default: return hipErrorInvalidValue;
     }
-#undef LP_G
     return hipGetLastError();
 }
 
-hipError_t launch_loss_grad(const float *Y, const float *T, int64_t B, int ldy, float *dZ,
-                            uint16_t *dZq, float *loss, hipStream_t s)
-{
-    const int64_t n = B * ldy;
-    hipLaunchKernelGGL(k_loss_grad, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, Y, T, B,
-                       ldy, 1.f / (float)B, dZ, dZq, loss);
-    return hipGetLastError();
-}
-
-hipError_t launch_colsum(const float *dZ, int64_t B, int N, float *db, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_colsum, dim3(N), dim3(256), 0, s, dZ, B, N, db);
-    return hipGetLastError();
-}
-
-hipError_t launch_adam(float *W, const float *G, float *m, float *v, int K, int N, int nvalid,
-                       float lr, float b1, float b2, float eps, int t, uint16_t *Wb, uint16_t *WT,
-                       hipStream_t s)
-{
-    const int64_t n = (int64_t)K * N;
-    const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
-    hipLaunchKernelGGL(k_adam, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, W, G, m, v, K,
-                       N, nvalid, lr, b1, b2, eps, c1, c2, Wb, WT);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s)
-{
-    int64_t b = (n + 255) / 256;
-    hipLaunchKernelGGL(k_fill_f32, dim3((uint32_t)(b > 4096 ? 4096 : (b ? b : 1))), dim3(256), 0,
-                       s, p, v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_to_bf16(const float *x, int64_t n, uint16_t *y, hipStream_t s)
+hipError_t launch_to_bf16(const float *x, int64_t nvalid, int64_t n, uint16_t *y, hipStream_t s)
 {
     int64_t b = (n + 255) / 256;
     hipLaunchKernelGGL(k_to_bf16, dim3((uint32_t)(b > 4096 ? 4096 : (b ? b : 1))), dim3(256), 0,
-                       s, x, n, y);
+                       s, x, nvalid, n, y);
     return hipGetLastError();
 }
 

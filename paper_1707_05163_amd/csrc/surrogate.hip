@@ -21,12 +21,12 @@
 #include "lp_internal.h"
 #include "lp_objects.h"
 
-using lp::GemmArgs;
 using lp::TimeEntry;
 
 namespace {
 
-constexpr int kIn = 64, kHid = 256, kOut = 2, kOutPad = 32, kLayers = 5;
+constexpr int kIn = lp::kNetIn, kHid = lp::kNetHid, kOut = lp::kNetOut,
+              kOutPad = lp::kNetOutPad, kLayers = lp::kNetLayers;
 constexpr double kOutScale = 7200.0;  // metres: 1 m/s over 2 h
 const int kFanIn[kLayers] = {kIn, kHid, kHid, kHid, kHid};
 const int kFanOut[kLayers] = {kHid, kHid, kHid, kHid, kOut};
@@ -504,14 +504,18 @@ __global__ void k_map_ids(const uint32_t *pid, const uint32_t *n_in, const uint3
 struct lp_model {
     float *W[kLayers] = {}, *b[kLayers] = {};  // FP32 master [fan_in x pad_out], [pad_out]
     float *mW[kLayers] = {}, *vW[kLayers] = {}, *mb[kLayers] = {}, *vb[kLayers] = {};
-    float *gW[kLayers] = {}, *gb[kLayers] = {};
     uint16_t *Wb[kLayers] = {}, *WT[kLayers] = {};  // bf16 [fan_in x pad], [pad x fan_in]
-    int adam_t = 0;
-    // work buffers for `cap` rows
-    int64_t cap = 0;
-    uint16_t *X = nullptr, *H[kLayers - 1] = {}, *dzq[2] = {}, *pad = nullptr;
-    float *Z[kLayers - 1] = {}, *Y = nullptr, *T = nullptr, *dz = nullptr, *dz2 = nullptr;
+    float *out = nullptr;                           // packed parameters or gradients
     float *loss = nullptr;
+    int adam_t = 0;
+    // work buffers for `cap` rows: features, host rows before rounding, outputs, targets
+    int64_t cap = 0, cap_host = 0;
+    uint16_t *X = nullptr;
+    float *Xf = nullptr, *Y = nullptr, *T = nullptr;
+    // for training steps of `cap_train` rows (see lp::TrainArgs)
+    int64_t cap_train = 0;
+    uint16_t *XT = nullptr, *HT[kLayers - 1] = {}, *DT[kLayers - 1] = {}, *DO = nullptr;
+    float *bpart = nullptr, *lpart = nullptr, *wpart = nullptr;
 };
 
 namespace {
@@ -526,36 +530,39 @@ int model_alloc(lp_model *m)
         SCHECK(dmalloc(&m->vW[l], n));
         SCHECK(dmalloc(&m->mb[l], nb));
         SCHECK(dmalloc(&m->vb[l], nb));
-        SCHECK(dmalloc(&m->gW[l], n));
-        SCHECK(dmalloc(&m->gb[l], nb));
         SCHECK(dmalloc(&m->Wb[l], n));
         SCHECK(dmalloc(&m->WT[l], n));
         SCHECK(hipMemset(m->mW[l], 0, n * 4));
         SCHECK(hipMemset(m->vW[l], 0, n * 4));
         SCHECK(hipMemset(m->mb[l], 0, nb * 4));
         SCHECK(hipMemset(m->vb[l], 0, nb * 4));
-        SCHECK(hipMemset(m->gW[l], 0, n * 4));
-        SCHECK(hipMemset(m->gb[l], 0, nb * 4));
     }
+    SCHECK(dmalloc(&m->out, (size_t)lp::kNetParams));
     SCHECK(dmalloc(&m->loss, 1));
     return LP_OK;
+}
+
+void model_free_train(lp_model *m)
+{
+    dfree(m->XT);
+    dfree(m->DO);
+    dfree(m->bpart);
+    dfree(m->lpart);
+    dfree(m->wpart);
+    for (int l = 0; l < kLayers - 1; ++l) {
+        dfree(m->HT[l]);
+        dfree(m->DT[l]);
+    }
+    m->cap_train = 0;
 }
 
 void model_free_work(lp_model *m)
 {
     dfree(m->X);
-    dfree(m->pad);
+    dfree(m->Xf);
     dfree(m->Y);
     dfree(m->T);
-    dfree(m->dz);
-    dfree(m->dz2);
-    dfree(m->dzq[0]);
-    dfree(m->dzq[1]);
-    for (int l = 0; l < kLayers - 1; ++l) {
-        dfree(m->H[l]);
-        dfree(m->Z[l]);
-    }
-    m->cap = 0;
+    m->cap = m->cap_host = 0;
 }
 
 int model_work(lp_model *m, int64_t rows)
@@ -564,168 +571,116 @@ int model_work(lp_model *m, int64_t rows)
         return LP_OK;
     model_free_work(m);
     SCHECK(dmalloc(&m->X, (size_t)rows * kIn));
-    for (int l = 0; l < kLayers - 1; ++l) {
-        SCHECK(dmalloc(&m->H[l], (size_t)rows * kHid));
-        SCHECK(dmalloc(&m->Z[l], (size_t)rows * kHid));
-    }
-    SCHECK(dmalloc(&m->pad, (size_t)rows * kOutPad));
-    SCHECK(dmalloc(&m->dzq[0], (size_t)rows * kHid));
-    SCHECK(dmalloc(&m->dzq[1], (size_t)rows * kHid));
     SCHECK(dmalloc(&m->Y, (size_t)rows * kOut));
     SCHECK(dmalloc(&m->T, (size_t)rows * kOut));
-    SCHECK(dmalloc(&m->dz, (size_t)rows * kHid));
-    SCHECK(dmalloc(&m->dz2, (size_t)rows * kOut));
     m->cap = rows;
     return LP_OK;
+}
+
+int model_train_work(lp_model *m, int64_t rows)
+{
+    if (rows <= m->cap_train)
+        return LP_OK;
+    model_free_train(m);
+    const size_t blocks = (size_t)(rows / lp::kTrainRows);
+    SCHECK(dmalloc(&m->XT, (size_t)rows * kIn));
+    for (int l = 0; l < kLayers - 1; ++l) {
+        SCHECK(dmalloc(&m->HT[l], (size_t)rows * kHid));
+        SCHECK(dmalloc(&m->DT[l], (size_t)rows * kHid));
+    }
+    SCHECK(dmalloc(&m->DO, (size_t)rows * kOut));
+    SCHECK(dmalloc(&m->bpart, blocks * lp::kNetBiases));
+    SCHECK(dmalloc(&m->lpart, blocks));
+    SCHECK(dmalloc(&m->wpart, (size_t)lp::kTrainParts * lp::kNetWeights));
+    m->cap_train = rows;
+    return LP_OK;
+}
+
+lp::UpdateArgs update_args(lp_model *m)
+{
+    lp::UpdateArgs u{};
+    for (int l = 0; l < kLayers; ++l) {
+        u.W[l] = m->W[l];
+        u.b[l] = m->b[l];
+        u.mW[l] = m->mW[l];
+        u.vW[l] = m->vW[l];
+        u.mb[l] = m->mb[l];
+        u.vb[l] = m->vb[l];
+        u.Wb[l] = m->Wb[l];
+        u.WT[l] = m->WT[l];
+    }
+    u.out = m->out;
+    u.loss = m->loss;
+    return u;
 }
 
 // bf16 copies of the master weights
 int refresh_bf16(lp_model *m, hipStream_t s)
 {
-    for (int l = 0; l < kLayers; ++l)
-        SCHECK(lp::launch_adam(m->W[l], nullptr, nullptr, nullptr, kFanIn[l], kPadOut[l],
-                               kFanOut[l], 0.f, 0.9f, 0.999f, 1e-8f, 1, m->Wb[l], m->WT[l], s));
+    SCHECK(lp::launch_train_update(lp::kUpCopies, update_args(m), s));
     return LP_OK;
 }
 
-// forward over `rows` (multiple of 128) rows of m->X; keeps pre-activations if train.
-// Inference runs the fused kernel (activations never leave the chip); training runs
-// the layer-by-layer GEMMs, which store what the backward pass needs.
-int forward(lp_model *m, int64_t rows, bool train, hipStream_t s)
+// inference over `rows` rows of m->X into m->Y
+int forward(lp_model *m, int64_t rows, hipStream_t s)
 {
-    if (!train) {
-        lp::MlpFusedArgs a{};
-        a.X = m->X;
-        a.rows = rows;
-        for (int l = 0; l < kLayers; ++l) {
-            a.WT[l] = m->WT[l];
-            a.bias[l] = m->b[l];
-        }
-        a.Y = m->Y;
-        SCHECK(lp::launch_mlp_fused(a, s));
-        return LP_OK;
-    }
-    const uint16_t *in = m->X;
+    lp::MlpFusedArgs a{};
+    a.X = m->X;
+    a.rows = rows;
     for (int l = 0; l < kLayers; ++l) {
-        GemmArgs g{};
-        g.A = in;
-        g.B = m->WT[l];
-        g.M = rows;
-        g.N = kPadOut[l];
-        g.K = kFanIn[l];
-        g.kchunk = g.K;
-        g.sai = kFanIn[l];
-        g.sak = 1;
-        g.sbk = 1;
-        g.sbj = kFanIn[l];
-        g.bias = m->b[l];
-        g.ldc = kPadOut[l];
-        if (l < kLayers - 1) {
-            g.Z = train ? m->Z[l] : nullptr;
-            g.H = m->H[l];
-            SCHECK(lp::launch_gemm(lp::kEpiHidden, g, s));
-            in = m->H[l];
-        } else {
-            g.Y = m->Y;
-            g.ldy = kOut;
-            g.nvalid = kOut;
-            SCHECK(lp::launch_gemm(lp::kEpiOut, g, s));
-        }
+        a.WT[l] = m->WT[l];
+        a.bias[l] = m->b[l];
     }
+    a.Y = m->Y;
+    SCHECK(lp::launch_mlp_fused(a, s));
     return LP_OK;
 }
 
-__global__ void k_pad_out(const float *dz2, int64_t rows, uint16_t *pad)
+// Gradients of L = (1/2B) sum (y - t)^2 for the batch of `rows` rows in m->X / m->T: as
+// one Adam step (kUpAdam) or packed into m->out (kUpGrads).  The weight gradients are
+// summed over up to kTrainParts parts of the batch, each at least 512 rows where the
+// batch has them: eight parts give k_train_wgrad 448 blocks, and more of them only add
+// partial sums to write and read (0.9 MB each).
+int train_pass(lp_model *m, int64_t rows, int mode, float lr, float *loss, hipStream_t s)
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= rows * kOutPad)
-        return;
-    const int64_t r = i / kOutPad;
-    const int c = (int)(i % kOutPad);
-    pad[i] = c < kOut ? to_bf16(dz2[r * kOut + c]) : (uint16_t)0;
-}
-
-int64_t split_of(int64_t rows)
-{
-    // split the batch dimension of the weight gradients over more blocks
-    int64_t c = rows;
-    while (c > 512 && c % 2 == 0 && (c / 2) % 16 == 0)
-        c /= 2;
-    return c;
-}
-
-// gradients of L = (1/2B) sum (y - t)^2 for the batch in m->X / m->T (after forward)
-int backward(lp_model *m, int64_t rows, hipStream_t s)
-{
-    SCHECK(lp::launch_fill_f32(m->loss, 0.f, 1, s));
-    uint16_t *scratch = m->dzq[0];  // the loss kernel's bf16 output is not used
-    SCHECK(lp::launch_loss_grad(m->Y, m->T, rows, kOut, m->dz2, scratch, m->loss, s));
-    hipLaunchKernelGGL(k_pad_out, dim3((uint32_t)((rows * kOutPad + 255) / 256)), dim3(256), 0,
-                       s, m->dz2, rows, m->pad);
-    SCHECK(hipGetLastError());
-    int cur = 0;
-    for (int l = kLayers - 1; l >= 0; --l) {
-        const int K = kFanIn[l], N = kPadOut[l];
-        const bool out = l == kLayers - 1;
-        const uint16_t *dzq = out ? m->pad : m->dzq[cur];
-        const uint16_t *hin = l == 0 ? m->X : m->H[l - 1];
-        // gW[l] [K x N] = H_in^T dzq
-        SCHECK(lp::launch_fill_f32(m->gW[l], 0.f, (int64_t)K * N, s));
-        GemmArgs gw{};
-        gw.A = hin;
-        gw.B = dzq;
-        gw.M = K;
-        gw.N = N;
-        gw.K = rows;
-        gw.kchunk = split_of(rows);
-        gw.sai = 1;
-        gw.sak = K;
-        gw.sbk = N;
-        gw.sbj = 1;
-        gw.Y = m->gW[l];
-        gw.ldy = N;
-        SCHECK(lp::launch_gemm(lp::kEpiAccum, gw, s));
-        if (out) {
-            SCHECK(lp::launch_colsum(m->dz2, rows, kOut, m->gb[l], s));
-            SCHECK(lp::launch_fill_f32(m->gb[l] + kOut, 0.f, N - kOut, s));
-        } else {
-            SCHECK(lp::launch_colsum(m->dz, rows, N, m->gb[l], s));
-        }
-        if (l > 0) {
-            // dH = dzq W_l^T, then dz = dH * gelu'(z_{l-1}) -> m->dz, bf16 -> other buffer
-            const int nxt = out ? 0 : 1 - cur;
-            GemmArgs g{};
-            g.A = dzq;
-            g.B = m->Wb[l];
-            g.M = rows;
-            g.N = K;
-            g.K = N;
-            g.kchunk = N;
-            g.sai = N;
-            g.sak = 1;
-            g.sbk = 1;
-            g.sbj = N;
-            g.Zin = m->Z[l - 1];
-            g.ldc = K;
-            g.dZ = m->dz;
-            g.H = m->dzq[nxt];
-            SCHECK(lp::launch_gemm(lp::kEpiBackData, g, s));
-            cur = nxt;
-        }
-    }
-    return LP_OK;
-}
-
-int adam(lp_model *m, float lr, hipStream_t s)
-{
-    m->adam_t++;
+    int rc = model_train_work(m, rows);
+    if (rc)
+        return rc;
+    lp::TrainArgs a{};
+    a.X = m->X;
+    a.T = m->T;
+    a.rows = rows;
+    a.inv_b = 1.f / (float)rows;
     for (int l = 0; l < kLayers; ++l) {
-        SCHECK(lp::launch_adam(m->W[l], m->gW[l], m->mW[l], m->vW[l], kFanIn[l], kPadOut[l],
-                               kFanOut[l], lr, 0.9f, 0.999f, 1e-8f, m->adam_t, m->Wb[l], m->WT[l],
-                               s));
-        SCHECK(lp::launch_adam(m->b[l], m->gb[l], m->mb[l], m->vb[l], 1, kPadOut[l], kFanOut[l],
-                               lr, 0.9f, 0.999f, 1e-8f, m->adam_t, nullptr, nullptr, s));
+        a.WT[l] = m->WT[l];
+        a.Wb[l] = m->Wb[l];
+        a.bias[l] = m->b[l];
     }
+    a.XT = m->XT;
+    for (int l = 0; l < kLayers - 1; ++l) {
+        a.HT[l] = m->HT[l];
+        a.DT[l] = m->DT[l];
+    }
+    a.DO = m->DO;
+    a.bpart = m->bpart;
+    a.lpart = m->lpart;
+    a.wpart = m->wpart;
+    a.parts = (int32_t)std::min<int64_t>(lp::kTrainParts, std::max<int64_t>(1, rows / 512));
+    SCHECK(lp::launch_train_pass(a, s));
+    lp::UpdateArgs u = update_args(m);
+    u.wpart = m->wpart;
+    u.bpart = m->bpart;
+    u.lpart = m->lpart;
+    u.parts = a.parts;
+    u.blocks = (int32_t)(rows / lp::kTrainRows);
+    u.loss = loss;
+    if (mode == lp::kUpAdam) {
+        m->adam_t++;
+        u.lr = lr;
+        u.c1 = 1.f - powf(0.9f, (float)m->adam_t);
+        u.c2 = 1.f - powf(0.999f, (float)m->adam_t);
+    }
+    SCHECK(lp::launch_train_update(mode, u, s));
     return LP_OK;
 }
 
@@ -733,18 +688,16 @@ int adam(lp_model *m, float lr, hipStream_t s)
 int upload_batch(lp_model *m, int64_t B, int64_t rows, const float *X, const float *T,
                  hipStream_t s)
 {
-    float *tmp = nullptr;
-    SCHECK(dmalloc(&tmp, (size_t)rows * kIn));
-    hipError_t e = hipMemset(tmp, 0, (size_t)rows * kIn * 4);
-    if (e == hipSuccess) e = hipMemcpy(tmp, X, (size_t)B * kIn * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = lp::launch_to_bf16(tmp, rows * kIn, m->X, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess && T) {
-        e = hipMemset(m->T, 0, (size_t)rows * kOut * 4);
-        if (e == hipSuccess) e = hipMemcpy(m->T, T, (size_t)B * kOut * 4, hipMemcpyHostToDevice);
+    if (B > m->cap_host) {
+        dfree(m->Xf);
+        m->cap_host = 0;
+        SCHECK(dmalloc(&m->Xf, (size_t)B * kIn));
+        m->cap_host = B;
     }
-    dfree(tmp);
-    SCHECK(e);
+    SCHECK(hipMemcpyAsync(m->Xf, X, (size_t)B * kIn * 4, hipMemcpyHostToDevice, s));
+    if (T)
+        SCHECK(hipMemcpyAsync(m->T, T, (size_t)B * kOut * 4, hipMemcpyHostToDevice, s));
+    SCHECK(lp::launch_to_bf16(m->Xf, B * kIn, rows * kIn, m->X, s));
     return LP_OK;
 }
 
@@ -773,13 +726,13 @@ extern "C" void surrogate_destroy(lp_model *m)
         dfree(m->vW[l]);
         dfree(m->mb[l]);
         dfree(m->vb[l]);
-        dfree(m->gW[l]);
-        dfree(m->gb[l]);
         dfree(m->Wb[l]);
         dfree(m->WT[l]);
     }
+    dfree(m->out);
     dfree(m->loss);
     model_free_work(m);
+    model_free_train(m);
     delete m;
 }
 
@@ -807,23 +760,6 @@ extern "C" int surrogate_set_params(lp_model *m, const float *params)
     return LP_OK;
 }
 
-static int copy_out(lp_model *m, float *const *W, float *const *b, float *out)
-{
-    (void)m;
-    float *p = out;
-    for (int l = 0; l < kLayers; ++l) {
-        std::vector<float> w((size_t)kFanIn[l] * kPadOut[l]), bb((size_t)kPadOut[l]);
-        SCHECK(hipMemcpy(w.data(), W[l], w.size() * 4, hipMemcpyDeviceToHost));
-        SCHECK(hipMemcpy(bb.data(), b[l], bb.size() * 4, hipMemcpyDeviceToHost));
-        for (int k = 0; k < kFanIn[l]; ++k)
-            for (int j = 0; j < kFanOut[l]; ++j)
-                *p++ = w[(size_t)k * kPadOut[l] + j];
-        for (int j = 0; j < kFanOut[l]; ++j)
-            *p++ = bb[j];
-    }
-    return LP_OK;
-}
-
 extern "C" int surrogate_get_params(lp_model *m, float *params)
 {
     if (!m || !params) {
@@ -831,7 +767,9 @@ extern "C" int surrogate_get_params(lp_model *m, float *params)
         return LP_EINVAL;
     }
     SCHECK(hipDeviceSynchronize());
-    return copy_out(m, m->W, m->b, params);
+    SCHECK(lp::launch_train_update(lp::kUpParams, update_args(m), nullptr));
+    SCHECK(hipMemcpy(params, m->out, (size_t)lp::kNetParams * 4, hipMemcpyDeviceToHost));
+    return LP_OK;
 }
 
 extern "C" int surrogate_create(uint32_t seed, lp_model **out)
@@ -876,7 +814,7 @@ extern "C" int surrogate_forward(lp_model *m, int64_t B, const float *X, float *
     const int64_t rows = round128(B);
     int rc;
     if ((rc = model_work(m, rows)) || (rc = upload_batch(m, B, rows, X, nullptr, nullptr)) ||
-        (rc = forward(m, rows, false, nullptr)))
+        (rc = forward(m, rows, nullptr)))
         return rc;
     SCHECK(hipDeviceSynchronize());
     SCHECK(hipMemcpy(Y, m->Y, (size_t)B * kOut * 4, hipMemcpyDeviceToHost));
@@ -892,12 +830,13 @@ extern "C" int surrogate_gradients(lp_model *m, int64_t B, const float *X, const
     }
     int rc;
     if ((rc = model_work(m, B)) || (rc = upload_batch(m, B, B, X, T, nullptr)) ||
-        (rc = forward(m, B, true, nullptr)) || (rc = backward(m, B, nullptr)))
+        (rc = train_pass(m, B, lp::kUpGrads, 0.f, m->loss, nullptr)))
         return rc;
     SCHECK(hipDeviceSynchronize());
     if (loss)
         SCHECK(hipMemcpy(loss, m->loss, 4, hipMemcpyDeviceToHost));
-    return copy_out(m, m->gW, m->gb, grads);
+    SCHECK(hipMemcpy(grads, m->out, (size_t)lp::kNetParams * 4, hipMemcpyDeviceToHost));
+    return LP_OK;
 }
 
 extern "C" int surrogate_train_step(lp_model *m, int64_t B, const float *X, const float *T,
@@ -909,8 +848,7 @@ extern "C" int surrogate_train_step(lp_model *m, int64_t B, const float *X, cons
     }
     int rc;
     if ((rc = model_work(m, B)) || (rc = upload_batch(m, B, B, X, T, nullptr)) ||
-        (rc = forward(m, B, true, nullptr)) || (rc = backward(m, B, nullptr)) ||
-        (rc = adam(m, (float)lr, nullptr)))
+        (rc = train_pass(m, B, lp::kUpAdam, (float)lr, m->loss, nullptr)))
         return rc;
     SCHECK(hipDeviceSynchronize());
     if (loss)
@@ -1153,10 +1091,8 @@ extern "C" int surrogate_train(lp_fieldset *fs, lp_model *m, const lp_surrogate_
         SCHECK(hipGetLastError());
         const double frac = (double)it / (double)cfg->iterations;
         const double lr = cfg->lr * (0.05 + 0.95 * 0.5 * (1.0 + std::cos(M_PI * frac)));
-        if ((rc = forward(m, B, true, stream)) || (rc = backward(m, B, stream)) ||
-            (rc = adam(m, (float)lr, stream)))
+        if ((rc = train_pass(m, B, lp::kUpAdam, (float)lr, loss_hist + it, stream)))
             return rc;
-        SCHECK(hipMemcpyAsync(loss_hist + it, m->loss, 4, hipMemcpyDeviceToDevice, stream));
     }
     st->train_ms = tt.stop_ms(stream);
     std::vector<float> lh((size_t)cfg->iterations);
@@ -1431,7 +1367,7 @@ extern "C" int pset_execute_surrogate(lp_pset *ps, lp_model *m, double runtime, 
         hipLaunchKernelGGL(k_features, dim3((uint32_t)((rows + kFeatBlock - 1) / kFeatBlock)),
                            dim3(kFeatBlock), 0, stream, fa);
         SCHECK(hipGetLastError());
-        if ((rc = forward(m, rows, false, stream)))
+        if ((rc = forward(m, rows, stream)))
             break;
         SCHECK(hipEventRecord(E.e[2], stream));
         // coarse RK4: two steps over the segment from the same state
