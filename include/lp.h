@@ -201,7 +201,7 @@ typedef struct {
      * the tracer at its position and the step's start time.  While a sinking
      * particle is at its dwelling depth the advection is horizontal only.  Any of
      * these needs LP_KERNEL_RK4 or LP_KERNEL_EULER.  With stencil_cache = 1 they run
-     * in the cached 3D kernel for FP32/FP64 fields without a Brownian term, else in
+     * in the cached kernels for FP32/FP64 fields without a Brownian term, else in
      * the gather kernel (same results up to rounding). */
     double sink_speed;    /* m/s, >= 0 (0 = off) */
     double dwell_depth;   /* m */

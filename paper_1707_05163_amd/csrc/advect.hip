@@ -191,6 +191,7 @@ __device__ inline void load_node(const char *slot, size_t node, const float *sc,
 struct Cell {
     int i, j, k;
     double xi, eta, zeta;
+    double y0;  // lower latitude face
 };
 
 // The cell of a point (as locate on each axis), the axes searched together so that their
@@ -216,6 +217,7 @@ __device__ inline bool locate_point(const GridDev &g, double x, double y, double
     c.xi = FRAC ? (x - fx.lo) * fx.rw : 0.0;
     c.eta = FRAC ? (y - fy.lo) * fy.rw : 0.0;
     c.zeta = FRAC && IS3D ? (z - fz.lo) * fz.rw : 0.0;
+    c.y0 = fy.lo;
     return true;
 }
 
@@ -280,16 +282,69 @@ __device__ inline void spatial(const AdvectParams &P, int sidx, const Cell &c,
     }
 }
 
-// A sample's velocity in coordinate units per second (degrees on the sphere).
+// cos of a latitude in a cell whose lower face has cosine cl and sine sl: cos(l0 + dl) =
+// cos l0 cos dl - sin l0 sin dl with dl = lat - l0 and cos dl, sin dl by their Taylor
+// series, cut after 2, 3 or 4 terms so that the truncation stays below a quarter ulp for
+// the grid's tallest cell (0.3, 1.5 or 5 degrees).
+__device__ inline double cos_series(double cl, double sl, double y0, double y, int terms)
+{
+    const double dl = (y - y0) * kDegToRad, d2 = dl * dl;
+    double cd, sd;
+    if (terms <= 2) {
+        cd = fma(d2, fma(d2, 1.0 / 24.0, -0.5), 1.0);
+        sd = dl * fma(d2, fma(d2, 1.0 / 120.0, -1.0 / 6.0), 1.0);
+    } else if (terms == 3) {
+        cd = fma(d2, fma(d2, fma(d2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);
+        sd = dl * fma(d2, fma(d2, fma(d2, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0), 1.0);
+    } else {
+        cd = fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 40320.0, -1.0 / 720.0), 1.0 / 24.0), -0.5),
+                 1.0);
+        sd = dl * fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 362880.0, -1.0 / 5040.0), 1.0 / 120.0),
+                              -1.0 / 6.0), 1.0);
+    }
+    return cl * cd - sl * sd;
+}
+
+// 1 / d to within an ulp or two: hardware reciprocal refined by two Newton steps
+__device__ inline double recip(double d)
+{
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return r;
+}
+
+// The latitude row that a gather's metric starts from: its lower face, and the tables'
+// cosine and sine there (read with the stencil; zero without tables).
+struct LatRow {
+    double y0, cl, sl;
+};
+
+__device__ inline LatRow lat_row(const GridDev &g, int j, double y0)
+{
+    return {y0, *(g.coslat ? g.coslat + j : &kAbsentTable), *(g.coslat ? g.sinlat + j : &kAbsentTable)};
+}
+
+// A sample's velocity in coordinate units per second (degrees on the sphere), and the
+// metric M cos(lat) that it divided by (1 on a flat mesh).  With FP64 values the cosine
+// comes from the cell's latitude tables, as in the cached kernels: the library cosine and
+// the two divisions were more than half of a gather's instructions (adaptive RKF45 on
+// the 0.25 degree field, 1M particles: 1.63 ms a launch).  Grids without tables (cells
+// taller than 5 degrees) take the library cosine.
 template <int ST>
-__device__ inline bool sample_finish(const AdvectParams &P, double y,
-                                     const typename Real<ST>::T v[3], double k[3])
+__device__ inline bool sample_finish(const AdvectParams &P, double y, const LatRow &lr,
+                                     const typename Real<ST>::T v[3], double k[3], double &m)
 {
     using R = typename Real<ST>::T;
+    m = 1.0;
     if (P.g.spherical) {
         if constexpr (sizeof(R) == 8) {
-            k[0] = v[0] / (kMetresPerDegree * cos(y * kDegToRad));
-            k[1] = v[1] / kMetresPerDegree;
+            if (P.g.coslat)
+                m = kMetresPerDegree * cos_series(lr.cl, lr.sl, lr.y0, y, P.g.cos_terms);
+            else
+                m = kMetresPerDegree * cos(y * kDegToRad);
+            k[0] = v[0] * recip(m);
+            k[1] = v[1] * (1.0 / kMetresPerDegree);
         } else {
             const float cl = cosf((float)(y * kDegToRad));
             k[0] = (double)(v[0] / ((float)kMetresPerDegree * cl));
@@ -340,7 +395,7 @@ __device__ inline void bilinear_from(const typename Real<ST>::T f[4][3], double 
 // The arithmetic is the same as locate_point followed by spatial.
 template <int ST, bool STEADY>
 __device__ inline bool gather2(const AdvectParams &P, const TimeEntry &te, double x, double y,
-                               typename Real<ST>::T a[3], typename Real<ST>::T b[3])
+                               typename Real<ST>::T a[3], typename Real<ST>::T b[3], LatRow &lr)
 {
     using R = typename Real<ST>::T;
     const GridDev &g = P.g;
@@ -353,9 +408,11 @@ __device__ inline bool gather2(const AdvectParams &P, const TimeEntry &te, doubl
     corners2<ST>(P, te.sa, fx.g, fy.g, fa);
     if constexpr (!STEADY)
         corners2<ST>(P, te.sb, fx.g, fy.g, fb);
+    lr = lat_row(g, fy.g, fy.lo);
     find_finish<true>(g.ax, x, fx);
     find_finish<true>(g.ay, y, fy);
     if (fx.g != fx.g0 || fy.g != fy.g0) {
+        lr = lat_row(g, fy.g, fy.lo);
         corners2<ST>(P, te.sa, fx.g, fy.g, fa);
         if constexpr (!STEADY)
             corners2<ST>(P, te.sb, fx.g, fy.g, fb);
@@ -377,13 +434,14 @@ __device__ inline bool gather2(const AdvectParams &P, const TimeEntry &te, doubl
 // holds cost as much as it saves, and the other storage forms of the RKF45 lane spill.
 template <int ST, bool IS3D, bool STEADY, bool SPEC = false>
 __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double x, double y,
-                              double z, double k[3])
+                              double z, double k[3], double &m)
 {
     using R = typename Real<ST>::T;
     R v[3];
+    LatRow lr;
     if constexpr (SPEC && !IS3D) {
         R a[3], b[3];
-        if (!gather2<ST, STEADY>(P, te, x, y, a, b))
+        if (!gather2<ST, STEADY>(P, te, x, y, a, b, lr))
             return false;
         if constexpr (STEADY) {
 #pragma unroll
@@ -395,11 +453,12 @@ __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double
             for (int q = 0; q < 3; ++q)
                 v[q] = ((R)1 - tau) * a[q] + tau * b[q];
         }
-        return sample_finish<ST>(P, y, v, k);
+        return sample_finish<ST>(P, y, lr, v, k, m);
     }
     Cell c;
     if (!locate_point<IS3D, true>(P.g, x, y, z, c))
         return false;
+    lr = lat_row(P.g, c.j, c.y0);
     if (P.nearest) {
         c.xi = c.xi < 0.5 ? 0.0 : 1.0;
         c.eta = c.eta < 0.5 ? 0.0 : 1.0;
@@ -416,7 +475,7 @@ __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double
         for (int q = 0; q < 3; ++q)
             v[q] = ((R)1 - tau) * a[q] + tau * b[q];
     }
-    return sample_finish<ST>(P, y, v, k);
+    return sample_finish<ST>(P, y, lr, v, k, m);
 }
 
 // Philox4x32-10 (Salmon et al., SC'11): ten Philox-4x32 rounds, key bumped by the
@@ -447,15 +506,6 @@ __device__ inline double unit53(uint32_t a, uint32_t b)
 {
     const uint64_t m = (((uint64_t)a << 32) | (uint64_t)b) >> 11;
     return (double)m * 0x1p-53 + 0x1p-54;
-}
-
-// 1 / d to within an ulp or two: hardware reciprocal refined by two Newton steps
-__device__ inline double recip(double d)
-{
-    double r = __builtin_amdgcn_rcp(d);
-    r = fma(fma(-d, r, 1.0), r, r);
-    r = fma(fma(-d, r, 1.0), r, r);
-    return r;
 }
 
 // sin and cos of 2 pi u for u in [0, 1].  The argument is a fraction of a turn, so the
@@ -600,7 +650,8 @@ __device__ inline uint8_t rk4_step(const AdvectParams &P, int s, uint32_t id, do
     // stages run on (a sample only reads the cell it located); the step then fails
     double k1[3] = {0.0, 0.0, 0.0}, k2[3] = {0.0, 0.0, 0.0}, k3[3] = {0.0, 0.0, 0.0},
            k4[3] = {0.0, 0.0, 0.0};
-    bool ok = sample<ST, IS3D, STEADY>(P, e0, x, y, z, k1);
+    double m;
+    bool ok = sample<ST, IS3D, STEADY>(P, e0, x, y, z, k1, m);
     double xs, ys, zs = z;
     if (P.scheme) {  // Euler forward
         xs = x + k1[0] * dt;
@@ -609,11 +660,11 @@ __device__ inline uint8_t rk4_step(const AdvectParams &P, int s, uint32_t id, do
             zs = z + k1[2] * dt;
     } else {
         ok = sample<ST, IS3D, STEADY>(P, e1, x + k1[0] * hd, y + k1[1] * hd, z + k1[2] * hd,
-                                      k2) & ok;
+                                      k2, m) & ok;
         ok = sample<ST, IS3D, STEADY>(P, e1, x + k2[0] * hd, y + k2[1] * hd, z + k2[2] * hd,
-                                      k3) & ok;
+                                      k3, m) & ok;
         ok = sample<ST, IS3D, STEADY>(P, e2, x + k3[0] * dt, y + k3[1] * dt, z + k3[2] * dt,
-                                      k4) & ok;
+                                      k4, m) & ok;
         xs = x + ((((k1[0] + 2.0 * k2[0]) + 2.0 * k3[0]) + k4[0]) * dt) / 6.0;
         ys = y + ((((k1[1] + 2.0 * k2[1]) + 2.0 * k3[1]) + k4[1]) * dt) / 6.0;
         if constexpr (IS3D)
@@ -676,8 +727,9 @@ __device__ inline bool sample_tracer(const AdvectParams &P, const TimeEntry &te,
 // The worked example's kernels ahead of the advection of step s (sinking, age,
 // tracer sample); returns a status to stop with, or 0.  The sinking update is
 // rounded as written (no contraction) so that reaching the dwelling depth is the
-// same decision as in a plain FP64 evaluation.
-template <bool IS3D, bool STEADY>
+// same decision as in a plain FP64 evaluation.  The cached kernels sample from their
+// cell after the first stage instead (tracer_in_cell), without SAMPLE here.
+template <bool IS3D, bool STEADY, bool SAMPLE = true>
 __device__ inline uint8_t behave_pre(const AdvectParams &P, int s, double x, double y,
                                      double &z, double &temp, double &age, bool &horizontal)
 {
@@ -692,7 +744,7 @@ __device__ inline uint8_t behave_pre(const AdvectParams &P, int s, double x, dou
         if (age >= P.maxage)
             return (uint8_t)(ST_AGED | ST_DELETED);
     }
-    if (P.sample) {
+    if (SAMPLE && P.sample) {
         double v;
         if (!sample_tracer<IS3D, STEADY>(P, P.tab[2 * s], x, y, z, v))
             return (uint8_t)(ST_OOB | (P.policy == 0 ? ST_DELETED : 0));
@@ -866,7 +918,7 @@ struct Fehlberg {
 template <int ST, bool IS3D, bool STEADY>
 __device__ inline bool rkf45_attempt(const AdvectParams &P, double t, double h,
                                      const double p[3], double p4[3], double ev[3],
-                                     LaneTime &lt)
+                                     LaneTime &lt, double &m0)
 {
     double k[6][3] = {};
     bool ok = true;  // as in the RK4 step: a failed stage leaves a zero slope
@@ -882,7 +934,10 @@ __device__ inline bool rkf45_attempt(const AdvectParams &P, double t, double h,
             q[d] = p[d] + h * s;
         }
         const TimeEntry te = bracket_lane(P, t + Fehlberg::c[i] * h, lt);
-        ok = sample<ST, IS3D, STEADY, ST == kF32>(P, te, q[0], q[1], q[2], k[i]) & ok;
+        double m = 1.0;
+        ok = sample<ST, IS3D, STEADY, ST == kF32>(P, te, q[0], q[1], q[2], k[i], m) & ok;
+        if (i == 0)
+            m0 = m;  // the metric at the step's start, for the error's length
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -969,15 +1024,18 @@ struct GatherLane {
         const double rem = sg > 0.0 ? P.t_end - s.t : s.t - P.t_end;
         const bool cut = h >= rem;
         const double hs = sg * (cut ? rem : h);
-        double p4[3], ev[3];
-        if (!rkf45_attempt<ST, IS3D, STEADY>(P, s.t, hs, p, p4, ev, lt)) {
+        double p4[3], ev[3], m0 = 1.0;
+        if (!rkf45_attempt<ST, IS3D, STEADY>(P, s.t, hs, p, p4, ev, lt, m0)) {
             ++acc;
             s.st = (uint8_t)(ST_OOB | extra);
             return true;
         }
         double ex = ev[0], ey = ev[1];
         if (P.g.spherical) {
-            ex = ex * (kMetresPerDegree * cos(p[1] * kDegToRad));
+            if constexpr (sizeof(typename Real<ST>::T) == 8)
+                ex = ex * m0;
+            else  // (the FP32 gathers' metric is FP32)
+                ex = ex * (kMetresPerDegree * cos(p[1] * kDegToRad));
             ey = ey * kMetresPerDegree;
         }
         const double err = sqrt((ex * ex + ey * ey) + ev[2] * ev[2]);
@@ -1030,6 +1088,7 @@ struct Cell2 {
                             // 16 - NL .. 15 (see cache_slot_ptr)
     uint32_t gs;            // elements from one of the lane's groups to the next
     R lr[NL < 16 ? 16 - NL : 1];  // registers: coefficients 0 .. 15 - NL
+    uint32_t node;          // the cell's lowest node (read by the tracer sample only)
     bool land;
     static constexpr int G = 16 / (int)sizeof(R);  // coefficients per 16-byte group
     __device__ R &lds(int j) { return lc[(j / G) * gs + j % G]; }
@@ -1050,6 +1109,7 @@ struct Cell2 {
         y0 = uy = rx = ry = cl = sl = 0.0;
         for (int i = 0; i < (NL < 16 ? 16 - NL : 1); ++i)
             lr[i] = (R)0;
+        node = 0;
         land = false;
         invalidate();
     }
@@ -1132,6 +1192,7 @@ __device__ inline bool reload2(const AdvectParams &P, Cell2<typename Real<ST>::T
     c.uy = (j == ay.n - 2) ? nextafter(ay.hi, __builtin_inf()) : yh;
     const size_t nx = (size_t)ax.n;
     const size_t n00 = (size_t)j * nx + (size_t)i;
+    c.node = (uint32_t)n00;
     const char *base = static_cast<const char *>(P.f.slots);
     const char *A = base + (size_t)sa * P.f.slot_bytes;
     const float *sca = ST == kF16S ? P.f.scales + (size_t)sa * P.f.nzl * 3 : nullptr;
@@ -1217,29 +1278,6 @@ struct BracketMoves {
     __device__ bool at(int q) const { return (bits >> q) & 1u; }
 };
 
-
-// cos of a latitude inside the cached cell: cos(l0 + dl) = cos l0 cos dl - sin l0 sin dl
-// with dl = lat - l0 and cos dl, sin dl by their Taylor series, cut after 2, 3 or 4
-// terms so that the truncation stays below a quarter ulp for the grid's tallest cell
-// (0.3, 1.5 or 5 degrees).
-__device__ inline double cos_series(double cl, double sl, double y0, double y, int terms)
-{
-    const double dl = (y - y0) * kDegToRad, d2 = dl * dl;
-    double cd, sd;
-    if (terms <= 2) {
-        cd = fma(d2, fma(d2, 1.0 / 24.0, -0.5), 1.0);
-        sd = dl * fma(d2, fma(d2, 1.0 / 120.0, -1.0 / 6.0), 1.0);
-    } else if (terms == 3) {
-        cd = fma(d2, fma(d2, fma(d2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);
-        sd = dl * fma(d2, fma(d2, fma(d2, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0), 1.0);
-    } else {
-        cd = fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 40320.0, -1.0 / 720.0), 1.0 / 24.0), -0.5),
-                 1.0);
-        sd = dl * fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 362880.0, -1.0 / 5040.0), 1.0 / 120.0),
-                              -1.0 / 6.0), 1.0);
-    }
-    return cl * cd - sl * sd;
-}
 
 template <int MET>
 constexpr bool met_series() { return MET == kSphTable || MET == kSphTable2; }
@@ -1399,9 +1437,47 @@ __device__ inline bool stage2_tc(const AdvectParams &P, Cell2<typename Real<ST>:
     return ok;
 }
 
+// Tracer at a point of a cached cell whose lowest node is `node`, at fractions (xi, eta,
+// zeta) and the time entry te: the sums of sample_tracer, without its cell search, on
+// corner pairs read with one 8-byte load each, all of them issued before any is used.
+// Searching the cell again at every step and reading the corners one by one cost a third
+// of a 3D step (the 2D samples had only the gather kernel, 9 times slower than this).
+template <bool IS3D, bool STEADY>
+__device__ inline double tracer_in_cell(const AdvectParams &P, const TimeEntry &te, size_t node,
+                                        double xi, double eta, double zeta)
+{
+    typedef float Pair __attribute__((ext_vector_type(2), aligned(4)));
+    const size_t nx = (size_t)P.g.ax.n, plane = nx * (size_t)P.g.ay.n;
+    constexpr int L = IS3D ? 2 : 1, S = STEADY ? 1 : 2;
+    Pair lo[S][L], hi[S][L];
+#pragma unroll
+    for (int q = 0; q < S; ++q)
+#pragma unroll
+        for (int k = 0; k < L; ++k) {
+            const float *F =
+                P.f.tracer + ((size_t)(q ? te.sb : te.sa) * P.f.nzl + (size_t)k) * plane + node;
+            lo[q][k] = *reinterpret_cast<const Pair *>(F);
+            hi[q][k] = *reinterpret_cast<const Pair *>(F + nx);
+        }
+    const double w00 = (1.0 - xi) * (1.0 - eta), w10 = xi * (1.0 - eta);
+    const double w11 = xi * eta, w01 = (1.0 - xi) * eta;
+    double v[S];
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+        double f[L];
+#pragma unroll
+        for (int k = 0; k < L; ++k)
+            f[k] = ((w00 * (double)lo[q][k].x + w10 * (double)lo[q][k].y) +
+                    w11 * (double)hi[q][k].y) + w01 * (double)hi[q][k].x;
+        v[q] = IS3D ? (1.0 - zeta) * f[0] + zeta * f[L - 1] : f[0];
+    }
+    return STEADY ? v[0] : (1.0 - te.tau) * v[0] + te.tau * v[S - 1];
+}
+
 // One particle (position k of the processing order) for all steps of the launch;
-// returns the number of steps it started active.
-template <int ST, bool STEADY, int MET, bool BROWN, uint32_t BS>
+// returns the number of steps it started active.  With BEHAVE the worked example's age
+// and tracer sample run in each step (there is no sinking in 2D).
+template <int ST, bool STEADY, int MET, bool BROWN, uint32_t BS, bool BEHAVE = false>
 __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, uint32_t nact)
 {
     using R = typename Real<ST>::T;
@@ -1411,6 +1487,11 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
         uint8_t st = P.status[id];
         if (st == 0) {
             double x = P.x[id], y = P.y[id];
+            double temp = 0.0, age = 0.0;
+            if constexpr (BEHAVE) {
+                temp = P.temp[id];
+                age = P.age[id];
+            }
             constexpr int NL = cache_lds_coefs<ST, BROWN>();
             Cell2<R, NL> c;
             c.clear();
@@ -1427,6 +1508,15 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                 const TimeEntry e0 = P.tab[2 * s], e1 = P.tab[2 * s + 1], e2 = P.tab[2 * s + 2];
                 const BracketMoves moves(P, s, e0, e1, e2);
                 uint8_t err = ST_OOB;
+                if constexpr (BEHAVE) {
+                    bool horizontal;
+                    double z = 0.0;
+                    if (const uint8_t b = behave_pre<false, STEADY, false>(P, s, x, y, z, temp,
+                                                                           age, horizontal)) {
+                        st = b;
+                        break;
+                    }
+                }
                 // the four stages: offsets 0, dt/2, dt/2, dt from X_n along the previous
                 // slope; weights 1, 2, 2, 1.  A stage whose point is off the grid leaves
                 // its slope as it was and the later stages run on (their loads stay in
@@ -1451,6 +1541,12 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                     if (q == 0) {
                         sx = kx;
                         sy = ky;
+                        if constexpr (BEHAVE) {
+                            if (P.sample && ok)
+                                temp = tracer_in_cell<false, STEADY>(P, e0, c.node,
+                                                                     (x - c.x0) * c.rx,
+                                                                     (y - c.y0) * c.ry, 0.0);
+                        }
                     } else if (q < 3) {
                         sx = fma(2.0, kx, sx);
                         sy = fma(2.0, ky, sy);
@@ -1504,6 +1600,10 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
             const uint32_t sid = id + (BROWN ? P.zero : 0u);
             P.x[sid] = x;
             P.y[sid] = y;
+            if constexpr (BEHAVE) {
+                P.temp[sid] = temp;
+                P.age[sid] = age;
+            }
             if (st)
                 P.status[sid] = st;
         }
@@ -1515,14 +1615,14 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
 // stage time that the lane keeps between stages take the registers of a fifth wave;
 // the LDS saved, a quarter to a half of the reads, is worth more), 3 with the Brownian
 // term.
-template <int ST, bool STEADY, int MET, bool BROWN>
+template <int ST, bool STEADY, int MET, bool BROWN, bool BEHAVE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     BROWN ? 3 : (MET == kSphLib ? 1 : 4)))) void k_advect2d(
     AdvectParams P)
 {
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
     const uint32_t k = blk * kBlock + threadIdx.x;
-    long long steps = advect_lane_2d<ST, STEADY, MET, BROWN, kBlock>(P, k, *P.n_active);
+    long long steps = advect_lane_2d<ST, STEADY, MET, BROWN, kBlock, BEHAVE>(P, k, *P.n_active);
     for (int off = 32; off > 0; off >>= 1)
         steps += __shfl_xor(steps, off, 64);
     if ((threadIdx.x & 63) == 0 && steps)
@@ -1819,8 +1919,14 @@ struct Cell3 {
     R *dl;                  // LDS slot (DL): variable v at [8 v .. 8 v + 7]
     bool land;
     __device__ R &d(int v, int q) { return DL ? dl[8 * v + q] : dr[DL ? 0 : v][q]; }
+    size_t node_reg;        // (not DL) see node()
     // (DL) the cell's depth index, kept in the slot's padding after the coefficients
     __device__ int &kidx() { return *reinterpret_cast<int *>(dl + 24); }
+    // the cell's lowest node, for the tracer sample: in the padding too, or a register
+    __device__ size_t &node()
+    {
+        return DL ? *reinterpret_cast<size_t *>(reinterpret_cast<char *>(dl + 24) + 8) : node_reg;
+    }
     // as for the 2D cell: an empty x range until the next reload
     __device__ void invalidate()
     {
@@ -1830,6 +1936,7 @@ struct Cell3 {
     __device__ void clear()
     {
         y0 = uy = z0 = uz = rx = ry = rz = cl = sl = 0.0;
+        node_reg = 0;
         land = false;
         invalidate();
     }
@@ -1900,7 +2007,8 @@ __device__ inline typename Real<ST>::T node_var(const typename NodeWord3<ST>::T 
 
 // With CARRY the cell keeps the coefficients at the stage time tau, a + tau d, in place of
 // the earlier snapshot's a (see stage3).
-template <int ST, bool STEADY, bool DL, bool CARRY = false>
+// KEEP_NODE: the cell's lowest node is kept for the tracer sample.
+template <int ST, bool STEADY, bool DL, bool CARRY, bool KEEP_NODE>
 __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T, DL> &c, int sa,
                                int sb, double x, double y, double z, double tau = 0.0)
 {
@@ -1936,6 +2044,8 @@ __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T
     const size_t nx = (size_t)ax.n, plane = nx * (size_t)ay.n;
     const size_t n000 = (size_t)k * plane + (size_t)j * nx + (size_t)i;
     const size_t off[8] = {0, 1, nx, nx + 1, plane, plane + 1, plane + nx, plane + nx + 1};
+    if constexpr (KEEP_NODE)
+        c.node() = n000;
     const char *base = static_cast<const char *>(P.f.slots);
     using W = typename NodeWord3<ST>::T;
     // Every read of the reload is issued before any of its values is used, so that the
@@ -2019,7 +2129,7 @@ __device__ inline bool in_cell3(const Cell3<R, DL> &c, const AdvectParams &P, do
 // advance, and stages at the previous stage's time (the first and third of RK4; the
 // last stage of a step and the first of the next share a time) skip it for the whole
 // wave: per step two advances of 24 products instead of four second polynomials.
-template <int ST, bool STEADY, int MET, bool DL>
+template <int ST, bool STEADY, int MET, bool DL, bool KEEP_NODE>
 __device__ inline bool stage3(const AdvectParams &P, Cell3<typename Real<ST>::T, DL> &c,
                               const TimeEntry &e, bool fresh, double x, double y, double z,
                               double k[3], double tau_prev)
@@ -2028,7 +2138,7 @@ __device__ inline bool stage3(const AdvectParams &P, Cell3<typename Real<ST>::T,
     constexpr bool CARRY = !STEADY && sizeof(R) == 8;
     const bool re = !in_cell3(c, P, x, y, z) | fresh;
     if (re) {
-        if (!reload3<ST, STEADY, DL, CARRY>(P, c, e.sa, e.sb, x, y, z, e.tau))
+        if (!reload3<ST, STEADY, DL, CARRY, KEEP_NODE>(P, c, e.sa, e.sb, x, y, z, e.tau))
             return false;
     }
     const R xi = (R)((x - c.x0) * c.rx), eta = (R)((y - c.y0) * c.ry);
@@ -2110,7 +2220,7 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                 bool horizontal = false;
                 if constexpr (BEHAVE) {
                     const uint8_t b =
-                        behave_pre<true, STEADY>(P, s, x, y, z, temp, age, horizontal);
+                        behave_pre<true, STEADY, false>(P, s, x, y, z, temp, age, horizontal);
                     if (b) {
                         st = b;
                         break;
@@ -2134,9 +2244,16 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                     // (stage 1 adds a zero slope, so its offset is immaterial; the
                     // half step comes in with the launch, as a scalar operand)
                     const double h = q == 3 ? dt : P.hdt;
-                    ok = stage3<ST, STEADY, MET, DL>(P, c, e, moves.at(q), x + k[0] * h,
-                                                     y + k[1] * h, z + k[2] * h, k, tau_prev) &
+                    ok = stage3<ST, STEADY, MET, DL, BEHAVE>(P, c, e, moves.at(q), x + k[0] * h,
+                                                             y + k[1] * h, z + k[2] * h, k,
+                                                             tau_prev) &
                          ok;
+                    if constexpr (BEHAVE) {
+                        if (q == 0 && P.sample && ok)
+                            temp = tracer_in_cell<true, STEADY>(
+                                P, e0, c.node(), (x - c.x0) * c.rx, (y - c.y0) * c.ry,
+                                (z - c.z0) * c.rz);
+                    }
                     tau_prev = e.tau;
                     const double wq = q == 0 ? 1.0 : (q == 3 ? 0.0 : 2.0);
 #pragma unroll
@@ -2330,9 +2447,9 @@ hipError_t launch3(const AdvectParams &p, bool steady, uint32_t n_launch, hipStr
     const uint32_t blocks = (n_launch + kBlock - 1) / kBlock;
     if (blocks == 0)
         return hipSuccess;
-    // the cached kernels interpolate linearly; the worked-example kernels run in the 3D
-    // cached kernel for FP32 / FP64 fields without a Brownian term, else in the gather
-    constexpr bool kBehaveCached = IS3D && (ST == kF32 || ST == kF64);
+    // the cached kernels interpolate linearly; the worked-example kernels run in them for
+    // FP32 / FP64 fields without a Brownian term, else in the gather kernel
+    constexpr bool kBehaveCached = ST == kF32 || ST == kF64;
     if (!p.cache || p.nearest || (p.behave && (!kBehaveCached || p.Kh > 0.0))) {
         const bool brown = p.Kh > 0.0;
         if (steady && brown)
@@ -2356,8 +2473,16 @@ hipError_t launch3(const AdvectParams &p, bool steady, uint32_t n_launch, hipStr
             const size_t lds =
                 (size_t)kBlock *
                 cache_slot<R, cache_lds_coefs<ST, decltype(brown)::value>()>() * sizeof(R);
+            if constexpr (kBehaveCached && !decltype(brown)::value) {
+                if (p.behave) {
+                    hipLaunchKernelGGL((k_advect2d<ST, decltype(stc)::value, decltype(met)::value,
+                                                   false, true>),
+                                       g, b, lds, s, p);
+                    return;
+                }
+            }
             hipLaunchKernelGGL((k_advect2d<ST, decltype(stc)::value, decltype(met)::value,
-                                           decltype(brown)::value>),
+                                           decltype(brown)::value, false>),
                                g, b, lds, s, p);
         });
     } else {
