@@ -1073,16 +1073,26 @@ struct GatherLane {
 // bilinear interpolant as the corner-weight form (Sect. 2.3), and (1 - tau) f_a +
 // tau f_b, taken on the coefficients or on the values, is the linear time
 // interpolation (Sect. 2.4); only rounding differs.
+//
+// A stage works in offsets from the cell's lower faces: the step's start has the offsets
+// b = X - (x0, y0), a stage point's are b + h k (one product), and with FP64 coefficients
+// the inverse cell widths are folded into the coefficients at the reload, so the offsets
+// go straight into the polynomials.  A point is in the cell when the high words of its
+// offsets are below those of the widths, two 32-bit unsigned compares: a negative offset
+// or a NaN has a larger high word, and a point within 2^-20 of the upper face counts as
+// outside, which only sends it through the exact search of the reload.  Against positions
+// in degrees, faces compared in FP64 and fractions formed by a difference and a product
+// this saved 10 of 31 vector instructions a stage.
 // NL of the 16 coefficients (the last NL) sit in the lane's LDS slot and the others
 // in registers: LDS frees registers, so more waves fit on a SIMD, at the cost of LDS
 // reads every stage; the split is chosen per kernel mode (cache_lds_coefs).
 template <class R, int NL>
 struct Cell2 {
-    double x0, ux, y0, uy;  // lower faces; exclusive upper faces (for the last cell the
-                            // next double above the last node, so the domain's closed
-                            // upper end needs no separate test)
-    double rx, ry;          // inverse cell widths
-    double cl, sl;          // cos and sin of the lower latitude face
+    double x0, y0;          // lower faces
+    uint32_t wx, wy;        // high words of the cell widths
+    double rx, ry;          // inverse cell widths (FP32 coefficients and the tracer sample)
+    double m[5];            // metric: see metric_poly; with the 3/4-term series m[0], m[1] are
+                            // M cos and M sin of the lower latitude face
     // U, V coefficients of the earlier snapshot [0..7] and of the later one [8..15]
     R *lc;                  // LDS: this lane's first 16-byte group of coefficients
                             // 16 - NL .. 15 (see cache_slot_ptr)
@@ -1095,18 +1105,16 @@ struct Cell2 {
     __device__ R lds(int j) const { return lc[(j / G) * gs + j % G]; }
     __device__ R &coef(int i) { return i < 16 - NL ? lr[i] : lds(i - (16 - NL)); }
     __device__ R coef(int i) const { return i < 16 - NL ? lr[i] : lds(i - (16 - NL)); }
-    // no point is in the cell until the next reload (an empty x range also keeps a
-    // NaN position out)
-    __device__ void invalidate()
-    {
-        x0 = __builtin_inf();
-        ux = -__builtin_inf();
-    }
+    // no point is in the cell until the next reload
+    __device__ void invalidate() { wx = 0; }
     // a fresh cell: every field defined (a stage whose point is off the grid still
     // evaluates the cell it has, and discards the result)
     __device__ void clear()
     {
-        y0 = uy = rx = ry = cl = sl = 0.0;
+        x0 = y0 = rx = ry = 0.0;
+        wy = 0;
+        for (double &c : m)
+            c = 0.0;
         for (int i = 0; i < (NL < 16 ? 16 - NL : 1); ++i)
             lr[i] = (R)0;
         node = 0;
@@ -1172,6 +1180,36 @@ __device__ inline R poly(const R c[4], R xi, R eta)
     return fma(eta, fma(xi, c[3], c[2]), fma(xi, c[1], c[0]));
 }
 
+// Whether the inverse widths are folded into the coefficients (FP64 ones; folded FP32
+// coefficients would round once more than the fraction that they replace).
+template <class R>
+constexpr bool folded() { return sizeof(R) == 8; }
+
+__device__ inline uint32_t high_word(double x)
+{
+    return (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32);
+}
+
+// M cos(lat) inside a cell at most 0.3 degrees tall as a polynomial in the offset t from
+// its lower face, in degrees: cos(l0 + d) = cos l0 (1 - d^2/2 + d^4/24) - sin l0 (d -
+// d^3/6) with d = t pi/180 < 5.3e-3; the truncation, d^6/720 of the cosine and d^5/120 of
+// the sine, stays below 4e-14 of the metric (1e-16 on the 0.1 degree grid).  Four products
+// a stage, against eight for the two series from the cosine and sine.
+__device__ inline void metric_poly(double mc, double ms, double m[5])
+{
+    constexpr double k = kDegToRad;
+    m[0] = mc;
+    m[1] = -k * ms;
+    m[2] = (-k * k / 2.0) * mc;
+    m[3] = (k * k * k / 6.0) * ms;
+    m[4] = (k * k * k * k / 24.0) * mc;
+}
+
+__device__ inline double metric_at(const double m[5], double t)
+{
+    return fma(fma(fma(fma(m[4], t, m[3]), t, m[2]), t, m[1]), t, m[0]);
+}
+
 template <int ST, bool STEADY, int MET, int NL>
 __device__ inline bool reload2(const AdvectParams &P, Cell2<typename Real<ST>::T, NL> &c, int sa,
                                int sb, double x, double y)
@@ -1188,8 +1226,8 @@ __device__ inline bool reload2(const AdvectParams &P, Cell2<typename Real<ST>::T
     axis_faces(ay, j, c.y0, yh);
     axis_correct(ax, x, i, c.x0, xh);
     axis_correct(ay, y, j, c.y0, yh);
-    c.ux = (i == ax.n - 2) ? nextafter(ax.hi, __builtin_inf()) : xh;
-    c.uy = (j == ay.n - 2) ? nextafter(ay.hi, __builtin_inf()) : yh;
+    c.wx = high_word(xh - c.x0);
+    c.wy = high_word(yh - c.y0);
     const size_t nx = (size_t)ax.n;
     const size_t n00 = (size_t)j * nx + (size_t)i;
     c.node = (uint32_t)n00;
@@ -1216,41 +1254,45 @@ __device__ inline bool reload2(const AdvectParams &P, Cell2<typename Real<ST>::T
     const double slat = *(P.g.coslat ? P.g.sinlat + j : &kAbsentTable);
     const uint32_t land = *(P.g.landcell ? P.g.landcell + ((size_t)j * (nx - 1) + (size_t)i)
                                          : reinterpret_cast<const uint8_t *>(&kAbsentTable));
-    if constexpr (!STEADY) {
+    // factors of the four coefficients of U and of V: the inverse widths where the stages
+    // take offsets, and 1/M in V (v_in_degrees)
+    R w[2][4];
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            R ca[4], cb[4];
-            coeffs<R>(q00[v], q10[v], q01[v], q11[v], cb);
-            coeffs<R>(p00[v], p10[v], p01[v], p11[v], ca);
+    for (int v = 0; v < 2; ++v) {
+        w[v][0] = v == 1 && v_in_degrees<R, MET>() ? (R)(1.0 / kMetresPerDegree) : (R)1;
+        w[v][1] = folded<R>() ? w[v][0] * (R)c.rx : w[v][0];
+        w[v][2] = folded<R>() ? w[v][0] * (R)c.ry : w[v][0];
+        w[v][3] = folded<R>() ? w[v][1] * (R)c.ry : w[v][0];
+    }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const R w = v == 1 && v_in_degrees<R, MET>() ? (R)(1.0 / kMetresPerDegree) : (R)1;
-                c.coef(4 * v + q) = ca[q] * w;
-                c.coef(8 + 4 * v + q) = cb[q] * w;
-            }
-        }
-    } else {
+    for (int v = 0; v < 2; ++v) {
+        R ca[4];
+        coeffs<R>(p00[v], p10[v], p01[v], p11[v], ca);
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            R ca[4];
-            coeffs<R>(p00[v], p10[v], p01[v], p11[v], ca);
+        for (int q = 0; q < 4; ++q)
+            c.coef(4 * v + q) = ca[q] * w[v][q];
+        if constexpr (!STEADY) {
+            coeffs<R>(q00[v], q10[v], q01[v], q11[v], ca);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const R w = v == 1 && v_in_degrees<R, MET>() ? (R)(1.0 / kMetresPerDegree) : (R)1;
-                c.coef(4 * v + q) = ca[q] * w;
-            }
+            for (int q = 0; q < 4; ++q)
+                c.coef(8 + 4 * v + q) = ca[q] * w[v][q];
         }
     }
-    c.cl = kMetresPerDegree * clat;
-    c.sl = kMetresPerDegree * slat;
+    if constexpr (MET == kSphTable2)
+        metric_poly(kMetresPerDegree * clat, kMetresPerDegree * slat, c.m);
+    else if constexpr (MET == kSphTable) {
+        c.m[0] = kMetresPerDegree * clat;
+        c.m[1] = kMetresPerDegree * slat;
+    }
     c.land = land != 0;
     return true;
 }
 
+// Whether a point at offsets (tx, ty) from the lower faces is in the cached cell.
 template <class R, int NL>
-__device__ inline bool in_cell(const Cell2<R, NL> &c, const AdvectParams &P, double x, double y)
+__device__ inline bool in_cell(const Cell2<R, NL> &c, double tx, double ty)
 {
-    return x >= c.x0 && x < c.ux && y >= c.y0 && y < c.uy;
+    return (high_word(tx) < c.wx) & (high_word(ty) < c.wy);
 }
 
 // Whether two time-table entries interpolate between the same two snapshots.
@@ -1282,10 +1324,7 @@ struct BracketMoves {
 template <int MET>
 constexpr bool met_series() { return MET == kSphTable || MET == kSphTable2; }
 
-// M cos(lat) inside a cell at most 0.3 degrees tall, for the slopes of the RK4 stages:
-// cos(d) = 1 - d^2/2 + d^4/24 and sin(d) = d (1 - d^2/6) across the cell (d < 5.3e-3
-// rad); the truncation, d^6/720 of the cosine and d^5/120 of the sine, stays below
-// 4e-14 of the metric (1e-16 on the 0.1 degree grid).
+// The same from the cosine and sine of the lower face (the 3D cells keep those).
 __device__ inline double mcos_short(double cl, double sl, double y0, double y)
 {
     const double dl = (y - y0) * kDegToRad, d2 = dl * dl;
@@ -1309,19 +1348,6 @@ __device__ inline double cos_series_m(double cl, double sl, double y0, double y,
     return cos_series(cl, sl, y0, y, MET == kSphTable2 ? 2 : P.g.cos_terms);
 }
 
-// Metres per degree of longitude at latitude y inside the cached cell, M cos(lat): the
-// cells keep M cos and M sin of their lower face, so the series gives the product.
-template <int MET, class R, int NL>
-__device__ inline double metres_lon(const Cell2<R, NL> &c, const AdvectParams &P, double y)
-{
-    if constexpr (MET == kSphLib)
-        return kMetresPerDegree * cos(y * kDegToRad);
-    else
-        return cos_series_m<MET>(c.cl, c.sl, c.y0, y, P);
-}
-
-
-
 // 1 / (M cos(lat)) at a stage point inside the cached cell, for the slope of an RK4
 // stage: the short series in cells of at most 0.3 degrees, else the cell's series (or
 // the library cosine), then one Newton step on the hardware reciprocal.
@@ -1338,6 +1364,39 @@ __device__ inline double stage_metric(const CellT &c, const AdvectParams &P, dou
     return recip_stage(m);
 }
 
+// The same for the 2D cells, at offset t from the lower latitude face.
+template <int MET, class R, int NL>
+__device__ inline double stage_metric(const Cell2<R, NL> &c, const AdvectParams &P, double t,
+                                      double y)
+{
+    double m;
+    if constexpr (MET == kSphLib)
+        m = kMetresPerDegree * cos(y * kDegToRad);
+    else if constexpr (MET == kSphTable2)
+        m = metric_at(c.m, t);
+    else
+        m = cos_series(c.m[0], c.m[1], 0.0, t, P.g.cos_terms);
+    return recip_stage(m);
+}
+
+// 1 / (M cos(lat)) at the end point of a step at offset t, for the metric of the Brownian
+// term: the cell's series when the end point is in the cell (the sine then takes its fifth
+// power too), else the turn form of the cosine.
+template <int MET, class R, int NL>
+__device__ inline double inv_metres_lon(const Cell2<R, NL> &c, const AdvectParams &P, double t,
+                                        double y)
+{
+    if constexpr (met_series<MET>()) {
+        if (high_word(t) < c.wy) {
+            if constexpr (MET == kSphTable)
+                return recip(cos_series(c.m[0], c.m[1], 0.0, t, P.g.cos_terms));
+            const double m3 = c.m[3] * fma(t * t, -kDegToRad * kDegToRad / 20.0, 1.0);
+            return recip(fma(fma(fma(fma(c.m[4], t, m3), t, c.m[2]), t, c.m[1]), t, c.m[0]));
+        }
+    }
+    return recip(kMetresPerDegree * cos_deg(y));
+}
+
 // 1 / (M cos(lat)) at the end point of a step, for the metric of the Brownian term: the
 // cached cell's series when the latitude is inside the cell's band (where the series
 // holds), else the turn form of the cosine.
@@ -1349,20 +1408,20 @@ __device__ inline double inv_metres_lon(const CellT &c, const AdvectParams &P, d
     return recip(kMetresPerDegree * cos_deg(y));
 }
 
-// The U and V coefficients at a stage's time, (1 - tau) earlier + tau later: exactly the
-// earlier snapshot's at tau = 0 and the later one's at tau = 1, so a time that falls on a
-// snapshot gives the same coefficients whichever of its two brackets the table names.
+// The U and V coefficients at a time, wa earlier + wb later, with weights (1 - tau, tau)
+// or twice those: exactly the earlier snapshot's at tau = 0 and the later one's at tau = 1,
+// so a time that falls on a snapshot gives the same coefficients whichever of its two
+// brackets the table names.
 template <bool STEADY, class R, int NL>
-__device__ inline void coefs_at(const Cell2<R, NL> &c, double tau_d, R tc[8])
+__device__ inline void coefs_at(const Cell2<R, NL> &c, R wa, R wb, R tc[8])
 {
-    const R tau = (R)tau_d, omt = (R)1 - tau;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        tc[i] = STEADY ? c.coef(i) : fma(tau, c.coef(8 + i), omt * c.coef(i));
+        tc[i] = STEADY ? c.coef(i) : fma(wb, c.coef(8 + i), wa * c.coef(i));
 }
 
-// U and V at (xi, eta) and a stage's time from the two snapshots' values, with the
-// same endpoint property (fewer operations when the coefficients are not kept).
+// U and V at the polynomials' arguments and a stage's time from the two snapshots' values,
+// with the same endpoint property (fewer operations when the coefficients are not kept).
 template <bool STEADY, class R, int NL>
 __device__ inline void values_at(const Cell2<R, NL> &c, double tau_d, R xi, R eta, R &u, R &v)
 {
@@ -1379,61 +1438,133 @@ __device__ inline void values_at(const Cell2<R, NL> &c, double tau_d, R xi, R et
     }
 }
 
-template <int ST, bool STEADY, int MET, int NL>
-__device__ inline bool stage2(const AdvectParams &P, Cell2<typename Real<ST>::T, NL> &c,
-                              const TimeEntry &e, bool fresh, double x, double y, double &kx,
-                              double &ky)
+// The polynomials' argument for an offset t: the offset, or the fraction t r.
+template <class R>
+__device__ inline R poly_arg(double t, double r)
 {
-    using R = typename Real<ST>::T;
-    if (!in_cell(c, P, x, y) | fresh) {
-        if (!reload2<ST, STEADY, MET, NL>(P, c, e.sa, e.sb, x, y))
-            return false;
-    }
-    const R xi = (R)((x - c.x0) * c.rx), eta = (R)((y - c.y0) * c.ry);
-    R u, v;
-    values_at<STEADY>(c, e.tau, xi, eta, u, v);
+    return folded<R>() ? (R)t : (R)(t * r);
+}
+
+// U, V at offsets (tx, ty) as slopes in coordinate units per second.
+template <int MET, class R, int NL>
+__device__ inline void slopes(const Cell2<R, NL> &c, const AdvectParams &P, R u, R v, double ty,
+                              double y, double &kx, double &ky)
+{
     if constexpr (MET != kFlat) {
-        kx = (double)u * stage_metric<MET>(c, P, y);
+        kx = (double)u * stage_metric<MET>(c, P, ty, y);
         ky = v_in_degrees<R, MET>() ? (double)v : (double)v * (1.0 / kMetresPerDegree);
     } else {
         kx = (double)u;
         ky = (double)v;
     }
+}
+
+// A stage of the adaptive lane at (x, y).
+template <int ST, bool STEADY, int MET, int NL>
+__device__ inline bool stage2(const AdvectParams &P, Cell2<typename Real<ST>::T, NL> &c,
+                              const TimeEntry &e, double x, double y, double &kx, double &ky)
+{
+    using R = typename Real<ST>::T;
+    double tx = x - c.x0, ty = y - c.y0;
+    if (!in_cell(c, tx, ty)) {
+        if (!reload2<ST, STEADY, MET, NL>(P, c, e.sa, e.sb, x, y))
+            return false;
+        tx = x - c.x0;
+        ty = y - c.y0;
+    }
+    R u, v;
+    values_at<STEADY>(c, e.tau, poly_arg<R>(tx, c.rx), poly_arg<R>(ty, c.ry), u, v);
+    slopes<MET>(c, P, u, v, ty, y, kx, ky);
     return true;
 }
 
-// A stage of the cached RK4 lane on the coefficients at the stage's time, tc = (1 - tau)
-// earlier + tau later: U in tc[0..3], V in tc[4..7].  With keep, tc stands
-// from the stage before, whose time entry was the same, unless the point leaves the
-// cached cell (or the bracket moves), so such a stage reads no LDS.  A point off the
-// grid leaves the cell as it was and returns false.
-template <int ST, bool STEADY, int MET, int NL>
-__device__ inline bool stage2_tc(const AdvectParams &P, Cell2<typename Real<ST>::T, NL> &c,
-                                 const TimeEntry &e, bool fresh, bool keep, double x, double y,
-                                 typename Real<ST>::T tc[8], double &kx, double &ky)
+// The time entries of one step as the cached RK4 lane uses them; every active lane of a
+// wave runs the same steps, so all of it is wave-uniform.  Where the step's start and
+// middle share a bracket (`mean`), the coefficients at the middle come from those at the
+// ends, their sum taken as twice the mean: with the end's kept for the next step's start
+// a step then forms coefficients once (16 products and 8 sums, against 32 products for
+// middle and end).  The end's weight is its own tau, or 1 where the table already names
+// the next bracket for a time on the snapshot; a step that straddles a snapshot forms the
+// middle's by themselves.
+struct StepTimes {
+    TimeEntry e0, e1, e2;
+    bool mean;
+    double tau_end;  // of the step's end, in the bracket of its middle
+    __device__ StepTimes(const TimeEntry &a, const TimeEntry &b, const TimeEntry &c)
+        : e0(a), e1(b), e2(c)
+    {
+        const bool same = same_bracket(e1, e2), next = e2.tau == 0.0 && e2.sa == e1.sb;
+        mean = same_bracket(e0, e1) && (same || next);
+        tau_end = same ? e2.tau : 1.0;
+    }
+};
+
+// One stage of the cached RK4 lane, Q = 0 .. 3, for the step that starts at (x, y), at
+// offsets (bx, by) from the cell's lower faces: slope (kx, ky) in, the previous stage's,
+// and out.  tc, tm, te: the coefficients (U in [0..3], V in [4..7]) at the step's start,
+// twice those at its middle, and those at its end; the middle stages' slopes come out
+// doubled (h is then half of theirs).  With coefficients in registers (NL = 0) or a steady
+// field nothing of that: tc serves every stage.  A point off the grid leaves the cell as
+// it was and returns false.
+template <int ST, bool STEADY, int MET, int NL, int Q>
+__device__ inline bool stage2_rk4(const AdvectParams &P, Cell2<typename Real<ST>::T, NL> &c,
+                                  const StepTimes &t, bool fresh, double x, double y, double h,
+                                  double &bx, double &by, typename Real<ST>::T tc[8],
+                                  typename Real<ST>::T tm[8], typename Real<ST>::T te[8],
+                                  double &kx, double &ky)
 {
     using R = typename Real<ST>::T;
+    const TimeEntry &e = Q == 0 ? t.e0 : (Q == 3 ? t.e2 : t.e1);
+    double tx = Q ? fma(kx, h, bx) : bx, ty = Q ? fma(ky, h, by) : by;
     bool ok = true;
-    const bool moved = !in_cell(c, P, x, y) | fresh;
-    if (moved)
-        ok = reload2<ST, STEADY, MET, NL>(P, c, e.sa, e.sb, x, y);
-    const R xi = (R)((x - c.x0) * c.rx), eta = (R)((y - c.y0) * c.ry);
+    const bool moved = !in_cell(c, tx, ty) | fresh;
+    if (moved) {
+        const double px = Q ? fma(kx, h, x) : x, py = Q ? fma(ky, h, y) : y;
+        ok = reload2<ST, STEADY, MET, NL>(P, c, e.sa, e.sb, px, py);
+        if (ok) {  // (the offsets depend on the cell alone, not on having reloaded it)
+            bx = x - c.x0;
+            by = y - c.y0;
+            tx = Q ? fma(kx, h, bx) : bx;
+            ty = Q ? fma(ky, h, by) : by;
+        }
+    }
+    const R xi = poly_arg<R>(tx, c.rx), eta = poly_arg<R>(ty, c.ry);
     R u, v;
-    if constexpr (NL == 0) {  // coefficients in registers: nothing is kept
+    if constexpr (NL == 0) {
         values_at<STEADY>(c, e.tau, xi, eta, u, v);
-    } else {
-        if (moved | !keep)
-            coefs_at<STEADY>(c, e.tau, tc);
+    } else if constexpr (STEADY) {
+        if (moved)
+            coefs_at<STEADY>(c, (R)1, (R)0, tc);
         u = poly<R>(tc + 0, xi, eta);
         v = poly<R>(tc + 4, xi, eta);
-    }
-    if constexpr (MET != kFlat) {
-        kx = (double)u * stage_metric<MET>(c, P, y);
-        ky = v_in_degrees<R, MET>() ? (double)v : (double)v * (1.0 / kMetresPerDegree);
+    } else if constexpr (Q == 0) {
+        // (Euler's only stage follows another time; RK4's has the previous step's end)
+        if (moved | (P.scheme != 0))
+            coefs_at<false>(c, (R)1 - (R)e.tau, (R)e.tau, tc);
+        u = poly<R>(tc + 0, xi, eta);
+        v = poly<R>(tc + 4, xi, eta);
+    } else if constexpr (Q < 3) {
+        const R tau = (R)e.tau, te1 = (R)t.tau_end;
+        if (Q == 1 || moved) {
+            if (t.mean)
+                coefs_at<false>(c, (R)1 - te1, te1, te);
+            if (moved | !t.mean) {
+                coefs_at<false>(c, (R)2 * ((R)1 - tau), (R)2 * tau, tm);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    tm[i] = tc[i] + te[i];
+            }
+        }
+        u = poly<R>(tm + 0, xi, eta);
+        v = poly<R>(tm + 4, xi, eta);
     } else {
-        kx = (double)u;
-        ky = (double)v;
+        if (moved | !t.mean)
+            coefs_at<false>(c, (R)1 - (R)e.tau, (R)e.tau, te);
+        u = poly<R>(te + 0, xi, eta);
+        v = poly<R>(te + 4, xi, eta);
     }
+    slopes<MET>(c, P, u, v, ty, Q ? fma(ky, h, y) : y, kx, ky);
     return ok;
 }
 
@@ -1501,12 +1632,15 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                 // immediate of the LDS read
                 c.gs = BS ? BS * (16 / (uint32_t)sizeof(R)) : cache_group_stride<R>();
             }
-            R tc[8] = {};  // coefficients at the last stage's time
+            // the middle stages' slopes are doubled where their coefficients are
+            constexpr bool TWICE = NL > 0 && !STEADY;
+            R tc[8] = {}, tm[8] = {}, te[8] = {};  // see stage2_rk4
             const double dt = P.dt, dt6 = P.dt6;
+            double bx = 0.0, by = 0.0;
             for (int s = 0; s < P.nsteps; ++s) {
                 ++steps;
-                const TimeEntry e0 = P.tab[2 * s], e1 = P.tab[2 * s + 1], e2 = P.tab[2 * s + 2];
-                const BracketMoves moves(P, s, e0, e1, e2);
+                const StepTimes t(P.tab[2 * s], P.tab[2 * s + 1], P.tab[2 * s + 2]);
+                const BracketMoves moves(P, s, t.e0, t.e1, t.e2);
                 uint8_t err = ST_OOB;
                 if constexpr (BEHAVE) {
                     bool horizontal;
@@ -1521,60 +1655,59 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                 // slope; weights 1, 2, 2, 1.  A stage whose point is off the grid leaves
                 // its slope as it was and the later stages run on (their loads stay in
                 // bounds: a reload only reads the cell it located); the step then fails.
-                double kx = 0.0, ky = 0.0, sx = 0.0, sy = 0.0;
-                bool ok = true;
+                double kx = 0.0, ky = 0.0, sx, sy;
+                bx = x - c.x0;
+                by = y - c.y0;
+                bool ok = stage2_rk4<ST, STEADY, MET, NL, 0>(P, c, t, moves.at(0), x, y, 0.0, bx,
+                                                             by, tc, tm, te, kx, ky);
+                sx = kx;
+                sy = ky;
+                if constexpr (BEHAVE) {
+                    if (P.sample && ok)
+                        temp = tracer_in_cell<false, STEADY>(P, t.e0, c.node, bx * c.rx,
+                                                             by * c.ry, 0.0);
+                }
+                if (!P.scheme) {  // (Euler forward has one stage)
+                    ok = stage2_rk4<ST, STEADY, MET, NL, 1>(P, c, t, moves.at(1), x, y, P.hdt, bx,
+                                                            by, tc, tm, te, kx, ky) & ok;
+                    sx = TWICE ? sx + kx : fma(2.0, kx, sx);
+                    sy = TWICE ? sy + ky : fma(2.0, ky, sy);
+                    ok = stage2_rk4<ST, STEADY, MET, NL, 2>(P, c, t, moves.at(2), x, y,
+                                                            TWICE ? P.qdt : P.hdt, bx, by, tc, tm,
+                                                            te, kx, ky) & ok;
+                    sx = TWICE ? sx + kx : fma(2.0, kx, sx);
+                    sy = TWICE ? sy + ky : fma(2.0, ky, sy);
+                    ok = stage2_rk4<ST, STEADY, MET, NL, 3>(P, c, t, moves.at(3), x, y,
+                                                            TWICE ? P.hdt : dt, bx, by, tc, tm,
+                                                            te, kx, ky) & ok;
+                    if constexpr (TWICE) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (q > 0 && P.scheme)  // Euler forward: one stage
-                        break;
-                    // stage constants (folded by the unrolling): time entry and
-                    // offset along the previous slope; the slopes are summed with
-                    // weights 1, 2, 2 here and stage 4's is added after the loop
-                    const TimeEntry e = q == 0 ? e0 : (q == 3 ? e2 : e1);
-                    const double h = q == 3 ? dt : P.hdt;  // (a scalar operand)
-                    const double px = q == 0 ? x : x + kx * h, py = q == 0 ? y : y + ky * h;
-                    // stage 3 has stage 2's time entry; RK4's stage 1 has the previous
-                    // step's stage 4's (its bracket cannot have moved since)
-                    const bool keep = NL > 0 && (q == 2 || (q == 0 && !P.scheme));
-                    ok = stage2_tc<ST, STEADY, MET, NL>(P, c, e, moves.at(q), keep, px, py, tc,
-                                                        kx, ky) & ok;
-                    if (q == 0) {
-                        sx = kx;
-                        sy = ky;
-                        if constexpr (BEHAVE) {
-                            if (P.sample && ok)
-                                temp = tracer_in_cell<false, STEADY>(P, e0, c.node,
-                                                                     (x - c.x0) * c.rx,
-                                                                     (y - c.y0) * c.ry, 0.0);
-                        }
-                    } else if (q < 3) {
-                        sx = fma(2.0, kx, sx);
-                        sy = fma(2.0, ky, sy);
+                        for (int i = 0; i < 8; ++i)
+                            tc[i] = te[i];
                     }
                 }
                 if (!ok)
                     goto fail;
                 {
-                    double xs, ys;
-                    if (P.scheme) {  // Euler forward
-                        xs = x + kx * dt;
-                        ys = y + ky * dt;
-                    } else {
-                        xs = x + (sx + kx) * dt6;
-                        ys = y + (sy + ky) * dt6;
-                    }
+                    // the end point, and its offsets in the last stage's cell
+                    const double g = P.scheme ? dt : dt6;
+                    const double dx = P.scheme ? kx : sx + kx, dy = P.scheme ? ky : sy + ky;
+                    double xs = fma(dx, g, x), ys = fma(dy, g, y);
+                    double tx = fma(dx, g, bx), ty = fma(dy, g, by);
                     if (BROWN && P.Kh > 0.0) {
-                        double dx, dy;
-                        brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, dx, dy);
+                        double wx, wy;
+                        brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, wx, wy);
                         if constexpr (MET != kFlat) {
-                            dx = dx * inv_metres_lon<MET>(c, P, ys);
-                            dy = dy / kMetresPerDegree;
+                            wx = wx * inv_metres_lon<MET>(c, P, ty, ys);
+                            wy = wy / kMetresPerDegree;
                         }
-                        xs = xs + dx;
-                        ys = ys + dy;
+                        xs = xs + wx;
+                        ys = ys + wy;
+                        tx = xs - c.x0;  // (of the rounded end point: both sides of a face agree)
+                        ty = ys - c.y0;
                     }
                     bool land;
-                    if (in_cell(c, P, xs, ys)) {
+                    if (in_cell(c, tx, ty)) {
                         land = c.land;
                     } else {
                         const uint8_t e = point_status<false>(P.g, xs, ys, 0.0);
@@ -1705,8 +1838,7 @@ struct CachedLane2 {
                 csb = ent.sb;
             }
             double kx = 0.0, ky = 0.0;
-            ok = stage2<ST, STEADY, MET, 16>(P, c, ent, false, x + hs * ax, y + hs * ay, kx,
-                                             ky) & ok;
+            ok = stage2<ST, STEADY, MET, 16>(P, c, ent, x + hs * ax, y + hs * ay, kx, ky) & ok;
             s4x = s4x + kRkfB4[q] * kx;
             s4y = s4y + kRkfB4[q] * ky;
             sex = sex + kRkfE[q] * kx;
@@ -1735,7 +1867,7 @@ struct CachedLane2 {
             return false;
         const double xs = x + hs * s4x, ys = y + hs * s4y;
         bool land;
-        if (in_cell(c, P, xs, ys)) {
+        if (in_cell(c, xs - c.x0, ys - c.y0)) {
             land = c.land;
         } else {
             const uint8_t e = point_status<false>(P.g, xs, ys, 0.0);
