@@ -40,6 +40,14 @@ __device__ inline uint32_t xcd_block(uint32_t b, uint32_t nb)
     return x * q + (x < r ? x : r) + local;
 }
 
+// The processing-order position of this thread, or one past every list where the thread
+// takes no particle: a wave carries P.lanes particles (see wave_lanes).
+__device__ inline uint32_t order_position(const AdvectParams &P, uint32_t blk)
+{
+    const uint32_t lane = threadIdx.x & 63u, wave = blk * (kBlock / 64) + (threadIdx.x >> 6);
+    return lane < P.lanes ? wave * P.lanes + lane : 0xFFFFFFFFu;
+}
+
 // What a reload reads in place of an absent per-cell table (no land mask, or no latitude
 // tables on a flat mesh): a zero in device memory, so that the read needs no branch and
 // goes out with the reload's other reads instead of after them.
@@ -760,7 +768,7 @@ template <int ST, bool IS3D, bool STEADY, bool BROWN>
 __global__ __launch_bounds__(kBlock) void k_advect(AdvectParams P)
 {
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const uint32_t k = blk * kBlock + threadIdx.x;
+    const uint32_t k = order_position(P, blk);
     const uint32_t nact = *P.n_active;
     long long steps = 0;
     if (k < nact) {
@@ -1639,7 +1647,9 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
             double bx = 0.0, by = 0.0;
             for (int s = 0; s < P.nsteps; ++s) {
                 ++steps;
-                const StepTimes t(P.tab[2 * s], P.tab[2 * s + 1], P.tab[2 * s + 2]);
+                // (a steady field needs no times: every entry names the one snapshot)
+                const StepTimes t(P.tab[STEADY ? 0 : 2 * s], P.tab[STEADY ? 0 : 2 * s + 1],
+                                  P.tab[STEADY ? 0 : 2 * s + 2]);
                 const BracketMoves moves(P, s, t.e0, t.e1, t.e2);
                 uint8_t err = ST_OOB;
                 if constexpr (BEHAVE) {
@@ -1754,7 +1764,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     AdvectParams P)
 {
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const uint32_t k = blk * kBlock + threadIdx.x;
+    const uint32_t k = order_position(P, blk);
     long long steps = advect_lane_2d<ST, STEADY, MET, BROWN, kBlock, BEHAVE>(P, k, *P.n_active);
     for (int off = 32; off > 0; off >>= 1)
         steps += __shfl_xor(steps, off, 64);
@@ -2324,7 +2334,7 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
 {
     using R = typename Real<ST>::T;
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const uint32_t kk = blk * kBlock + threadIdx.x;
+    const uint32_t kk = order_position(P, blk);
     const uint32_t nact = *P.n_active;
     long long steps = 0;
     if (kk < nact) {
@@ -2573,10 +2583,22 @@ hipError_t dispatch_cached(const AdvectParams &p, bool steady, F &&f)
     return hipGetLastError();
 }
 
+// Particles per wave: 64, or 32 while that leaves at most one wave per SIMD (1024 on the
+// chip).  With so few waves a step lasts as long as the wave's own chain of instructions
+// and reload waits, and half the lanes halve how often a wave has to wait for the reload
+// of one of them.  Measured with 32 and 64 lanes: 10k particles on 1 km cells 70 and 87 us
+// per 60 steps, 30k on 0.5 degrees 694 and 711 us per 576 steps, in 3D 610 and 647 us per
+// 288 steps; at 60k particles 830 and 725 us.  Fewer than 32 lose: 16 lanes 820 us at 30k,
+// and a CU whose waves have 8 active lanes or less issues at a third of the rate.
+uint32_t wave_lanes(uint32_t n) { return n <= 32u * 1024u ? 32u : 64u; }
+
 template <int ST, bool IS3D>
-hipError_t launch3(const AdvectParams &p, bool steady, uint32_t n_launch, hipStream_t s)
+hipError_t launch3(const AdvectParams &params, bool steady, uint32_t n_launch, hipStream_t s)
 {
-    const uint32_t blocks = (n_launch + kBlock - 1) / kBlock;
+    AdvectParams p = params;
+    p.lanes = wave_lanes(n_launch);
+    const uint32_t per_block = kBlock / 64 * p.lanes;
+    const uint32_t blocks = (n_launch + per_block - 1) / per_block;
     if (blocks == 0)
         return hipSuccess;
     // the cached kernels interpolate linearly; the worked-example kernels run in them for
