@@ -1213,6 +1213,19 @@ __device__ inline void metric_poly(double mc, double ms, double m[5])
     m[4] = (k * k * k * k / 24.0) * mc;
 }
 
+// What a cell keeps of its lower face's M cos and M sin: the polynomial, or with the
+// 3/4-term series the two themselves.
+template <int MET>
+__device__ inline void metric_of_face(double mc, double ms, double m[5])
+{
+    if constexpr (MET == kSphTable2) {
+        metric_poly(mc, ms, m);
+    } else if constexpr (MET == kSphTable) {
+        m[0] = mc;
+        m[1] = ms;
+    }
+}
+
 __device__ inline double metric_at(const double m[5], double t)
 {
     return fma(fma(fma(fma(m[4], t, m[3]), t, m[2]), t, m[1]), t, m[0]);
@@ -1286,12 +1299,7 @@ __device__ inline bool reload2(const AdvectParams &P, Cell2<typename Real<ST>::T
                 c.coef(8 + 4 * v + q) = ca[q] * w[v][q];
         }
     }
-    if constexpr (MET == kSphTable2)
-        metric_poly(kMetresPerDegree * clat, kMetresPerDegree * slat, c.m);
-    else if constexpr (MET == kSphTable) {
-        c.m[0] = kMetresPerDegree * clat;
-        c.m[1] = kMetresPerDegree * slat;
-    }
+    metric_of_face<MET>(kMetresPerDegree * clat, kMetresPerDegree * slat, c.m);
     c.land = land != 0;
     return true;
 }
@@ -1332,15 +1340,6 @@ struct BracketMoves {
 template <int MET>
 constexpr bool met_series() { return MET == kSphTable || MET == kSphTable2; }
 
-// The same from the cosine and sine of the lower face (the 3D cells keep those).
-__device__ inline double mcos_short(double cl, double sl, double y0, double y)
-{
-    const double dl = (y - y0) * kDegToRad, d2 = dl * dl;
-    const double cd = fma(d2, fma(d2, 1.0 / 24.0, -0.5), 1.0);
-    const double sd = dl * fma(d2, -1.0 / 6.0, 1.0);
-    return fma(cl, cd, -sl * sd);
-}
-
 // 1/d for the slopes of the RK4 stages: the hardware reciprocal (about 25 bits) and one
 // Newton step, within 11 ulp (1.2e-15 relative).
 __device__ inline double recip_stage(double d)
@@ -1349,33 +1348,12 @@ __device__ inline double recip_stage(double d)
     return fma(fma(-d, r, 1.0), r, r);
 }
 
-template <int MET>
-__device__ inline double cos_series_m(double cl, double sl, double y0, double y,
-                                      const AdvectParams &P)
-{
-    return cos_series(cl, sl, y0, y, MET == kSphTable2 ? 2 : P.g.cos_terms);
-}
-
-// 1 / (M cos(lat)) at a stage point inside the cached cell, for the slope of an RK4
-// stage: the short series in cells of at most 0.3 degrees, else the cell's series (or
-// the library cosine), then one Newton step on the hardware reciprocal.
+// 1 / (M cos(lat)) at a stage point inside the cached cell, at offset t from its lower
+// latitude face, for the slope of an RK4 stage: the polynomial in cells of at most 0.3
+// degrees, else the cell's series (or the library cosine), then one Newton step on the
+// hardware reciprocal.
 template <int MET, class CellT>
-__device__ inline double stage_metric(const CellT &c, const AdvectParams &P, double y)
-{
-    double m;
-    if constexpr (MET == kSphLib)
-        m = kMetresPerDegree * cos(y * kDegToRad);
-    else if constexpr (MET == kSphTable2)
-        m = mcos_short(c.cl, c.sl, c.y0, y);
-    else
-        m = cos_series_m<MET>(c.cl, c.sl, c.y0, y, P);
-    return recip_stage(m);
-}
-
-// The same for the 2D cells, at offset t from the lower latitude face.
-template <int MET, class R, int NL>
-__device__ inline double stage_metric(const Cell2<R, NL> &c, const AdvectParams &P, double t,
-                                      double y)
+__device__ inline double stage_metric(const CellT &c, const AdvectParams &P, double t, double y)
 {
     double m;
     if constexpr (MET == kSphLib)
@@ -1390,9 +1368,8 @@ __device__ inline double stage_metric(const Cell2<R, NL> &c, const AdvectParams 
 // 1 / (M cos(lat)) at the end point of a step at offset t, for the metric of the Brownian
 // term: the cell's series when the end point is in the cell (the sine then takes its fifth
 // power too), else the turn form of the cosine.
-template <int MET, class R, int NL>
-__device__ inline double inv_metres_lon(const Cell2<R, NL> &c, const AdvectParams &P, double t,
-                                        double y)
+template <int MET, class CellT>
+__device__ inline double inv_metres_lon(const CellT &c, const AdvectParams &P, double t, double y)
 {
     if constexpr (met_series<MET>()) {
         if (high_word(t) < c.wy) {
@@ -1402,17 +1379,6 @@ __device__ inline double inv_metres_lon(const Cell2<R, NL> &c, const AdvectParam
             return recip(fma(fma(fma(fma(c.m[4], t, m3), t, c.m[2]), t, c.m[1]), t, c.m[0]));
         }
     }
-    return recip(kMetresPerDegree * cos_deg(y));
-}
-
-// 1 / (M cos(lat)) at the end point of a step, for the metric of the Brownian term: the
-// cached cell's series when the latitude is inside the cell's band (where the series
-// holds), else the turn form of the cosine.
-template <int MET, class CellT>
-__device__ inline double inv_metres_lon(const CellT &c, const AdvectParams &P, double y)
-{
-    if (met_series<MET>() && y >= c.y0 && y < c.uy)
-        return recip(cos_series_m<MET>(c.cl, c.sl, c.y0, y, P));
     return recip(kMetresPerDegree * cos_deg(y));
 }
 
@@ -2053,9 +2019,10 @@ __attribute__((amdgpu_waves_per_eu(BROWN || MET == kSphLib ? 3 : 4))) void k_adv
 // DL the 24 difference coefficients sit in the lane's LDS slot instead of registers.
 template <class R, bool DL>
 struct Cell3 {
-    double x0, ux, y0, uy, z0, uz;
-    double rx, ry, rz;
-    double cl, sl;
+    double x0, y0, z0;      // lower faces
+    uint32_t wx, wy, wz;    // high words of the cell widths (in_cell3)
+    double rx, ry, rz;      // inverse cell widths
+    double m[5];            // metric, as in Cell2
     R a[3][8];
     R dr[DL ? 1 : 3][8];    // registers (not DL)
     R *dl;                  // LDS slot (DL): variable v at [8 v .. 8 v + 7]
@@ -2069,15 +2036,14 @@ struct Cell3 {
     {
         return DL ? *reinterpret_cast<size_t *>(reinterpret_cast<char *>(dl + 24) + 8) : node_reg;
     }
-    // as for the 2D cell: an empty x range until the next reload
-    __device__ void invalidate()
-    {
-        x0 = __builtin_inf();
-        ux = -__builtin_inf();
-    }
+    // as for the 2D cell: no point is inside until the next reload
+    __device__ void invalidate() { wx = 0; }
     __device__ void clear()
     {
-        y0 = uy = z0 = uz = rx = ry = rz = cl = sl = 0.0;
+        x0 = y0 = z0 = rx = ry = rz = 0.0;
+        wy = wz = 0;
+        for (double &c : m)
+            c = 0.0;
         node_reg = 0;
         land = false;
         invalidate();
@@ -2150,7 +2116,7 @@ __device__ inline typename Real<ST>::T node_var(const typename NodeWord3<ST>::T 
 // With CARRY the cell keeps the coefficients at the stage time tau, a + tau d, in place of
 // the earlier snapshot's a (see stage3).
 // KEEP_NODE: the cell's lowest node is kept for the tracer sample.
-template <int ST, bool STEADY, bool DL, bool CARRY, bool KEEP_NODE>
+template <int ST, bool STEADY, int MET, bool DL, bool CARRY, bool KEEP_NODE>
 __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T, DL> &c, int sa,
                                int sb, double x, double y, double z, double tau = 0.0)
 {
@@ -2162,7 +2128,7 @@ __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T
     // changes are horizontal), which spares the depth axis's bin-table guess and face
     // reads, the longest chain of the search on a non-uniform axis.  The level sits in
     // the LDS slot, so only the LDS-cached forms keep it.
-    const bool keep_k = DL && z >= c.z0 && z < c.uz;
+    const bool keep_k = DL && high_word(z - c.z0) < c.wz;
     int i = axis_guess(ax, x), j = axis_guess(ay, y), k = 0;
     double xh, yh, zh = 0.0;
     if (keep_k)
@@ -2177,12 +2143,12 @@ __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T
     axis_correct(ay, y, j, c.y0, yh);
     if (!keep_k) {
         axis_correct(az, z, k, c.z0, zh);
-        c.uz = (k == az.n - 2) ? nextafter(az.hi, __builtin_inf()) : zh;
+        c.wz = high_word(zh - c.z0);
     }
     if constexpr (DL)
         c.kidx() = k;
-    c.ux = (i == ax.n - 2) ? nextafter(ax.hi, __builtin_inf()) : xh;
-    c.uy = (j == ay.n - 2) ? nextafter(ay.hi, __builtin_inf()) : yh;
+    c.wx = high_word(xh - c.x0);
+    c.wy = high_word(yh - c.y0);
     const size_t nx = (size_t)ax.n, plane = nx * (size_t)ay.n;
     const size_t n000 = (size_t)k * plane + (size_t)j * nx + (size_t)i;
     const size_t off[8] = {0, 1, nx, nx + 1, plane, plane + 1, plane + nx, plane + nx + 1};
@@ -2249,17 +2215,18 @@ __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T
             }
         }
     }
-    c.cl = kMetresPerDegree * clat;
-    c.sl = kMetresPerDegree * slat;
+    metric_of_face<MET>(kMetresPerDegree * clat, kMetresPerDegree * slat, c.m);
     c.land = land != 0;
     return true;
 }
 
+// Whether a point at offsets t from the lower faces is in the cached cell (see Cell2: 12
+// FP64 instructions of a stage, three differences and six compares among them, for three
+// products and three 32-bit compares).
 template <class R, bool DL>
-__device__ inline bool in_cell3(const Cell3<R, DL> &c, const AdvectParams &P, double x, double y,
-                                double z)
+__device__ inline bool in_cell3(const Cell3<R, DL> &c, double tx, double ty, double tz)
 {
-    return x >= c.x0 && x < c.ux && y >= c.y0 && y < c.uy && z >= c.z0 && z < c.uz;
+    return (high_word(tx) < c.wx) & (high_word(ty) < c.wy) & (high_word(tz) < c.wz);
 }
 
 // With FP64 coefficients the cell carries the coefficients at the last stage's time,
@@ -2271,20 +2238,30 @@ __device__ inline bool in_cell3(const Cell3<R, DL> &c, const AdvectParams &P, do
 // advance, and stages at the previous stage's time (the first and third of RK4; the
 // last stage of a step and the first of the next share a time) skip it for the whole
 // wave: per step two advances of 24 products instead of four second polynomials.
+// (x, y, z) is the step's start, b its offsets from the cell's lower faces, k the previous
+// stage's slope in (zero at the first stage) and this stage's out, h the offset along it.
 template <int ST, bool STEADY, int MET, bool DL, bool KEEP_NODE>
 __device__ inline bool stage3(const AdvectParams &P, Cell3<typename Real<ST>::T, DL> &c,
                               const TimeEntry &e, bool fresh, double x, double y, double z,
-                              double k[3], double tau_prev)
+                              double h, double b[3], double k[3], double tau_prev)
 {
     using R = typename Real<ST>::T;
     constexpr bool CARRY = !STEADY && sizeof(R) == 8;
-    const bool re = !in_cell3(c, P, x, y, z) | fresh;
+    double tx = fma(k[0], h, b[0]), ty = fma(k[1], h, b[1]), tz = fma(k[2], h, b[2]);
+    const bool re = !in_cell3(c, tx, ty, tz) | fresh;
     if (re) {
-        if (!reload3<ST, STEADY, DL, CARRY, KEEP_NODE>(P, c, e.sa, e.sb, x, y, z, e.tau))
+        if (!reload3<ST, STEADY, MET, DL, CARRY, KEEP_NODE>(P, c, e.sa, e.sb, fma(k[0], h, x),
+                                                            fma(k[1], h, y), fma(k[2], h, z),
+                                                            e.tau))
             return false;
+        b[0] = x - c.x0;
+        b[1] = y - c.y0;
+        b[2] = z - c.z0;
+        tx = fma(k[0], h, b[0]);
+        ty = fma(k[1], h, b[1]);
+        tz = fma(k[2], h, b[2]);
     }
-    const R xi = (R)((x - c.x0) * c.rx), eta = (R)((y - c.y0) * c.ry);
-    const R zeta = (R)((z - c.z0) * c.rz);
+    const R xi = (R)(tx * c.rx), eta = (R)(ty * c.ry), zeta = (R)(tz * c.rz);
     R v[3];
     if constexpr (CARRY) {
         const double dtau = e.tau - tau_prev;
@@ -2313,7 +2290,8 @@ __device__ inline bool stage3(const AdvectParams &P, Cell3<typename Real<ST>::T,
         }
     }
     if constexpr (MET != kFlat) {
-        k[0] = (double)v[0] * stage_metric<MET>(c, P, y);
+        k[0] = (double)v[0] *
+               stage_metric<MET>(c, P, ty, MET == kSphLib ? fma(k[1], h, y) : 0.0);
         k[1] = (double)v[1] * (1.0 / kMetresPerDegree);
     } else {
         k[0] = (double)v[0];
@@ -2369,6 +2347,7 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                     }
                 }
                 double k[3] = {0.0, 0.0, 0.0}, sm[3] = {0.0, 0.0, 0.0};
+                double b[3] = {x - c.x0, y - c.y0, z - c.z0};
                 const int nst = P.scheme ? 1 : 4;
                 bool ok = true;  // as in 2D: a failed stage leaves its slope, the step fails
                 // The four stages side by side: with FP32 coefficients (+11% on the BF16
@@ -2386,15 +2365,13 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                     // (stage 1 adds a zero slope, so its offset is immaterial; the
                     // half step comes in with the launch, as a scalar operand)
                     const double h = q == 3 ? dt : P.hdt;
-                    ok = stage3<ST, STEADY, MET, DL, BEHAVE>(P, c, e, moves.at(q), x + k[0] * h,
-                                                             y + k[1] * h, z + k[2] * h, k,
-                                                             tau_prev) &
+                    ok = stage3<ST, STEADY, MET, DL, BEHAVE>(P, c, e, moves.at(q), x, y, z, h, b,
+                                                             k, tau_prev) &
                          ok;
                     if constexpr (BEHAVE) {
                         if (q == 0 && P.sample && ok)
                             temp = tracer_in_cell<true, STEADY>(
-                                P, e0, c.node(), (x - c.x0) * c.rx, (y - c.y0) * c.ry,
-                                (z - c.z0) * c.rz);
+                                P, e0, c.node(), b[0] * c.rx, b[1] * c.ry, b[2] * c.rz);
                     }
                     tau_prev = e.tau;
                     const double wq = q == 0 ? 1.0 : (q == 3 ? 0.0 : 2.0);
@@ -2405,30 +2382,31 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                 if (!ok)
                     goto fail;
                 {
-                    double xs, ys, zs;
-                    if (P.scheme) {  // Euler forward
-                        xs = x + k[0] * dt;
-                        ys = y + k[1] * dt;
-                        zs = z + k[2] * dt;
-                    } else {
-                        xs = x + (sm[0] + k[0]) * dt6;
-                        ys = y + (sm[1] + k[1]) * dt6;
-                        zs = z + (sm[2] + k[2]) * dt6;
-                    }
-                    if (BEHAVE && horizontal)  // a dwelling particle keeps its depth
+                    // the end point, and its offsets in the last stage's cell
+                    const double g = P.scheme ? dt : dt6;
+                    const double dx = P.scheme ? k[0] : sm[0] + k[0];
+                    const double dy = P.scheme ? k[1] : sm[1] + k[1];
+                    const double dz = P.scheme ? k[2] : sm[2] + k[2];
+                    double xs = fma(dx, g, x), ys = fma(dy, g, y), zs = fma(dz, g, z);
+                    double tx = fma(dx, g, b[0]), ty = fma(dy, g, b[1]), tz = fma(dz, g, b[2]);
+                    if (BEHAVE && horizontal) {  // a dwelling particle keeps its depth
                         zs = z;
+                        tz = b[2];
+                    }
                     if (BROWN && P.Kh > 0.0) {
-                        double dx, dy;
-                        brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, dx, dy);
+                        double wx, wy;
+                        brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, wx, wy);
                         if constexpr (MET != kFlat) {
-                            dx = dx * inv_metres_lon<MET>(c, P, ys);
-                            dy = dy / kMetresPerDegree;
+                            wx = wx * inv_metres_lon<MET>(c, P, ty, ys);
+                            wy = wy / kMetresPerDegree;
                         }
-                        xs = xs + dx;
-                        ys = ys + dy;
+                        xs = xs + wx;
+                        ys = ys + wy;
+                        tx = xs - c.x0;  // (of the rounded end point: both sides of a face agree)
+                        ty = ys - c.y0;
                     }
                     bool land;
-                    if (in_cell3(c, P, xs, ys, zs)) {
+                    if (in_cell3(c, tx, ty, tz)) {
                         land = c.land;
                     } else {
                         const uint8_t e = point_status<true>(P.g, xs, ys, zs);
