@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "_lp_hip.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["advect.hip", "support.hip", "capi.hip", "mlp.hip", "surrogate.hip"]
+SOURCES = ["advect.hip", "support.hip", "capi.hip", "mlp.hip", "surrogate.hip", "results.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

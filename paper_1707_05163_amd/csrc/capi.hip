@@ -57,6 +57,11 @@ int dalloc(T **p, size_t count)
     if (count == 0)
         return LP_OK;
     hipError_t e = hipMalloc((void **)p, count * sizeof(T));
+    if (e == hipErrorOutOfMemory) {  // without the blocks kept for later, it may fit
+        (void)hipGetLastError();
+        lp_pool_purge();
+        e = hipMalloc((void **)p, count * sizeof(T));
+    }
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -73,6 +78,44 @@ void dfree(T *&p)
         (void)hipFree((void *)p);
     p = nullptr;
 }
+
+// The same from the blocks kept between objects (lp_pool_alloc), device or pinned.  A
+// block is freed only when nothing queued uses it any more.
+template <class T>
+int palloc(T **p, size_t count, bool host = false)
+{
+    *p = nullptr;
+    if (count == 0)
+        return LP_OK;
+    hipError_t e;
+    *p = (T *)lp_pool_alloc(count * sizeof(T), host, &e);
+    if (!*p)
+        return fail(LP_ENOMEM, "%s allocation of %zu bytes failed: %s",
+                    host ? "pinned" : "device", count * sizeof(T), hipGetErrorString(e));
+    return LP_OK;
+}
+
+template <class T>
+void pfree(T *&p)
+{
+    lp_pool_free((void *)p);
+    p = nullptr;
+}
+
+// Makes a set's device current for a call that launches on it.
+struct DeviceGuard {
+    int old = -1;
+    explicit DeviceGuard(int dev)
+    {
+        if (hipGetDevice(&old) != hipSuccess || old == dev || hipSetDevice(dev) != hipSuccess)
+            old = -1;
+    }
+    ~DeviceGuard()
+    {
+        if (old >= 0)
+            (void)hipSetDevice(old);
+    }
+};
 
 struct HostAxis {
     std::vector<double> c, rw;
@@ -256,6 +299,8 @@ extern "C" int fieldset_create(const lp_grid_desc *g, lp_fieldset **out)
     fs->slot_t.assign(fs->capacity, 0.0);
     fs->slot_seq.assign(fs->capacity, -1);
     fs->tracer_seq.assign(fs->capacity, -1);
+    fs->pool_user = true;
+    lp_pool_user(1);
     *out = fs;
     return LP_OK;
 }
@@ -291,6 +336,8 @@ extern "C" void fieldset_destroy(lp_fieldset *fs)
         if (e) (void)hipEventDestroy(e);
     if (fs->up)
         (void)hipStreamDestroy(fs->up);
+    if (fs->pool_user)
+        lp_pool_user(-1);
     delete fs;
 }
 
@@ -524,7 +571,47 @@ std::vector<Resident> resident(const lp_fieldset *fs)
 
 // Bracket of time t among the resident snapshots: linear weight tau between
 // slot sa (earlier) and sb (later).
-int bracket(const lp_fieldset *fs, const std::vector<Resident> &r, double t, TimeEntry &e)
+// fmod(a, P) for P > 0, bit for bit: where |a / P| < 2^51 the remainder a - n P with n =
+// trunc(a / P), corrected by at most one, is exact in one fused multiply-add.  (The
+// library's fmod divides bit by bit: 50 to 100 ns for each of a run's stage times.)
+double exact_fmod(double a, double P)
+{
+    double n = std::trunc(a / P);
+    if (!(std::fabs(n) < 0x1p51))
+        return std::fmod(a, P);
+    double r = std::fma(-n, P, a);
+    if (a >= 0.0) {
+        if (r < 0.0)
+            r = std::fma(-(n - 1.0), P, a);
+        else if (r >= P)
+            r = std::fma(-(n + 1.0), P, a);
+    } else {
+        if (r > 0.0)
+            r = std::fma(-(n + 1.0), P, a);
+        else if (r <= -P)
+            r = std::fma(-(n - 1.0), P, a);
+        if (r == 0.0)
+            r = -0.0;  // the sign of the dividend
+    }
+    return r;
+}
+
+// The largest k < m with r[k].t <= t (0 if none), looked for at `hint` and after it first:
+// a run's stage times follow each other.
+int last_at_or_before(const std::vector<Resident> &r, int m, double t, int &hint)
+{
+    for (int k = hint; k < m && k < hint + 2; ++k)
+        if (r[k].t <= t && (k + 1 >= m || r[k + 1].t > t))
+            return hint = k;
+    int s = 0;
+    for (int k = 0; k < m; ++k)
+        if (r[k].t <= t)
+            s = k;
+    return hint = s;
+}
+
+int bracket(const lp_fieldset *fs, const std::vector<Resident> &r, double t, TimeEntry &e,
+            int &hint)
 {
     const int m = (int)r.size();
     if (m == 0)
@@ -536,14 +623,11 @@ int bracket(const lp_fieldset *fs, const std::vector<Resident> &r, double t, Tim
     }
     if (fs->period > 0.0) {
         const double T0 = r[0].t;
-        double q = std::fmod(t - T0, fs->period);
+        double q = exact_fmod(t - T0, fs->period);
         if (q < 0.0)
             q += fs->period;
         const double tp = T0 + q;
-        int s = 0;
-        for (int k = 0; k < m; ++k)
-            if (r[k].t <= tp)
-                s = k;
+        const int s = last_at_or_before(r, m, tp, hint);
         const double tn = (s + 1 < m) ? r[s + 1].t : T0 + fs->period;
         e.sa = r[s].slot;
         e.sb = (s + 1 < m) ? r[s + 1].slot : r[0].slot;
@@ -553,10 +637,7 @@ int bracket(const lp_fieldset *fs, const std::vector<Resident> &r, double t, Tim
     if (!(t >= r[0].t && t <= r[m - 1].t) || m < 2)
         return fail(LP_ETIME, "time %.17g is not covered by the resident snapshots [%.17g, %.17g]",
                     t, r[0].t, r[m - 1].t);
-    int s = 0;
-    for (int k = 0; k + 1 < m; ++k)
-        if (r[k].t <= t)
-            s = k;
+    const int s = last_at_or_before(r, m - 1, t, hint);
     e.sa = r[s].slot;
     e.sb = r[s + 1].slot;
     e.tau = (t - r[s].t) / (r[s + 1].t - r[s].t);
@@ -637,37 +718,37 @@ extern "C" void pset_destroy(lp_pset *ps)
 {
     if (!ps)
         return;
+    const DeviceGuard dev(ps->device);
     (void)hipDeviceSynchronize();
-    dfree(ps->dx);
-    dfree(ps->dy);
-    dfree(ps->dz);
-    dfree(ps->dst);
-    dfree(ps->dorder[0]);
-    dfree(ps->dorder[1]);
-    dfree(ps->dcount);
-    dfree(ps->dkeys);
-    dfree(ps->dhist);
-    dfree(ps->dblk);
-    dfree(ps->dpsteps);
-    dfree(ps->dexp);
-    dfree(ps->dtemp);
-    dfree(ps->dage);
-    dfree(ps->rtemp);
-    dfree(ps->rage);
-    dfree(ps->dqueues);
-    dfree(ps->dres);
-    dfree(ps->rx);
-    dfree(ps->ry);
-    dfree(ps->rz);
-    dfree(ps->rst);
-    dfree(ps->rci);
-    dfree(ps->rcj);
-    dfree(ps->rck);
-    dfree(ps->dtab);
-    if (ps->htab)
-        (void)hipHostFree(ps->htab);
-    if (ps->hcount)
-        (void)hipHostFree(ps->hcount);
+    pfree(ps->dx);
+    pfree(ps->dy);
+    pfree(ps->dz);
+    pfree(ps->dst);
+    pfree(ps->dorder[0]);
+    pfree(ps->dorder[1]);
+    pfree(ps->dcount);
+    pfree(ps->dkeys);
+    pfree(ps->dhist);
+    pfree(ps->dblk);
+    pfree(ps->dpsteps);
+    pfree(ps->dexp);
+    pfree(ps->dtemp);
+    pfree(ps->dage);
+    pfree(ps->rtemp);
+    pfree(ps->rage);
+    pfree(ps->dqueues);
+    pfree(ps->dres);
+    pfree(ps->rx);
+    pfree(ps->ry);
+    pfree(ps->rz);
+    pfree(ps->rst);
+    pfree(ps->rci);
+    pfree(ps->rcj);
+    pfree(ps->rck);
+    pfree(ps->dtab);
+    pfree(ps->dstat);
+    pfree(ps->htab);
+    pfree(ps->hcount);
     if (ps->tab_ev)
         (void)hipEventDestroy(ps->tab_ev);
     if (ps->count_ev)
@@ -698,24 +779,25 @@ static int pset_create_common(lp_fieldset *fs, int64_t n, const double *lon, con
         return code;
     };
     ps->fs = fs;
+    ps->device = fs->device;
     ps->n = n;
     ps->t0 = t0;
     ps->step = step0;
     int rc;
     const size_t N = (size_t)n;
-    if ((rc = dalloc(&ps->dx, N)) || (rc = dalloc(&ps->dy, N)) ||
-        (fs->is3d && (rc = dalloc(&ps->dz, N))) || (rc = dalloc(&ps->dst, N)) ||
-        (rc = dalloc(&ps->dorder[0], N)) || (rc = dalloc(&ps->dorder[1], N)) ||
-        (rc = dalloc(&ps->dcount, 2)) || (rc = dalloc(&ps->dpsteps, 2 * lp::kCountWords)) ||
-        (rc = dalloc(&ps->dexp, N)) || (rc = dalloc(&ps->dqueues, 8)) ||
-        (rc = dalloc(&ps->dtemp, N)) || (rc = dalloc(&ps->dage, N)))
+    if ((rc = palloc(&ps->dx, N)) || (rc = palloc(&ps->dy, N)) ||
+        (fs->is3d && (rc = palloc(&ps->dz, N))) || (rc = palloc(&ps->dst, N)) ||
+        (rc = palloc(&ps->dorder[0], N)) || (rc = palloc(&ps->dorder[1], N)) ||
+        (rc = palloc(&ps->dcount, 2)) || (rc = palloc(&ps->dpsteps, 2 * lp::kCountWords)) ||
+        (rc = palloc(&ps->dexp, N)) || (rc = palloc(&ps->dqueues, 8)) ||
+        (rc = palloc(&ps->dtemp, N)) || (rc = palloc(&ps->dage, N)))
         return bail(rc);
     ps->nbins = lp::sort_bins(fs->g);
-    if ((rc = dalloc(&ps->dkeys, N)) || (rc = dalloc(&ps->dhist, ps->nbins)) ||
-        (rc = dalloc(&ps->dblk, lp::sort_blocksums(ps->nbins))))
+    if ((rc = palloc(&ps->dkeys, N)) || (rc = palloc(&ps->dhist, ps->nbins)) ||
+        (rc = palloc(&ps->dblk, lp::sort_blocksums(ps->nbins))))
         return bail(rc);
-    if (hipHostMalloc((void **)&ps->hcount, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess)
-        return bail(fail(LP_ENOMEM, "pinned allocation failed"));
+    if ((rc = palloc(&ps->dstat, 6)) || (rc = palloc(&ps->hcount, 1, true)))
+        return bail(rc);
     if (hipEventCreateWithFlags(&ps->tab_ev, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ps->count_ev, hipEventDisableTiming) != hipSuccess)
         return bail(fail(LP_EDEVICE, "event creation failed"));
@@ -770,9 +852,9 @@ int grow_records(lp_pset *ps, int64_t need)
     uint8_t *rst;
     int32_t *ci, *cj, *ck = nullptr;
     int rc;
-    if ((rc = dalloc(&rx, tot)) || (rc = dalloc(&ry, tot)) || (is3d && (rc = dalloc(&rz, tot))) ||
-        (rc = dalloc(&rst, tot)) || (rc = dalloc(&ci, tot)) || (rc = dalloc(&cj, tot)) ||
-        (is3d && (rc = dalloc(&ck, tot))))
+    if ((rc = palloc(&rx, tot)) || (rc = palloc(&ry, tot)) || (is3d && (rc = palloc(&rz, tot))) ||
+        (rc = palloc(&rst, tot)) || (rc = palloc(&ci, tot)) || (rc = palloc(&cj, tot)) ||
+        (is3d && (rc = palloc(&ck, tot))))
         return rc;
     if (old) {
         HIPCHECK(hipMemcpy(rx, ps->rx, old * 8, hipMemcpyDeviceToDevice));
@@ -785,17 +867,19 @@ int grow_records(lp_pset *ps, int64_t need)
         if (is3d)
             HIPCHECK(hipMemcpy(ck, ps->rck, old * 4, hipMemcpyDeviceToDevice));
     }
-    dfree(ps->rx);
-    dfree(ps->ry);
-    dfree(ps->rz);
-    dfree(ps->rst);
-    dfree(ps->rci);
-    dfree(ps->rcj);
-    dfree(ps->rck);
+    if (ps->rx)  // queued records may still write the old arrays
+        HIPCHECK(hipDeviceSynchronize());
+    pfree(ps->rx);
+    pfree(ps->ry);
+    pfree(ps->rz);
+    pfree(ps->rst);
+    pfree(ps->rci);
+    pfree(ps->rcj);
+    pfree(ps->rck);
     if (ps->behave_records) {
         double *rt = nullptr, *ra = nullptr;
-        if ((rc = dalloc(&rt, tot)) || (rc = dalloc(&ra, tot))) {
-            dfree(rt);
+        if ((rc = palloc(&rt, tot)) || (rc = palloc(&ra, tot))) {
+            pfree(rt);
             return rc;
         }
         if (old && ps->rtemp) {
@@ -805,8 +889,8 @@ int grow_records(lp_pset *ps, int64_t need)
             HIPCHECK(hipMemset(rt, 0xFF, old * 8));
             HIPCHECK(hipMemset(ra, 0, old * 8));
         }
-        dfree(ps->rtemp);
-        dfree(ps->rage);
+        pfree(ps->rtemp);
+        pfree(ps->rage);
         ps->rtemp = rt;
         ps->rage = ra;
     }
@@ -958,16 +1042,19 @@ int exec_prepare(lp_pset *ps, double runtime, double dt, double outputdt, const 
         const double ta = t0 + (double)ps->step * dt, tb = t0 + (double)(ps->step + nsteps) * dt;
         TimeEntry e;
         int rc;
-        if ((rc = bracket(fs, res, ta, e)) || (rc = bracket(fs, res, tb, e)))
+        int hint = 0;
+        if ((rc = bracket(fs, res, ta, e, hint)) || (rc = bracket(fs, res, tb, e, hint)))
             return rc;
         const double tm = std::max(std::fabs(ta), std::fabs(tb));
         if (tm + std::ldexp(adt, o->rkf_min_exp) * 0.25 == tm)
             return fail(LP_EINVAL, "the RKF45 floor step |dt| 2^%d is too small for times "
                                    "near %g", o->rkf_min_exp, tm);
         if (res.size() > ps->res_cap) {
-            dfree(ps->dres);
+            if (ps->dres)
+                HIPCHECK(hipDeviceSynchronize());
+            pfree(ps->dres);
             ps->res_cap = 0;
-            if ((rc = dalloc(&ps->dres, res.size())))
+            if ((rc = palloc(&ps->dres, res.size())))
                 return rc;
             ps->res_cap = res.size();
         }
@@ -987,26 +1074,24 @@ int exec_prepare(lp_pset *ps, double runtime, double dt, double outputdt, const 
         ps->tab_pending = false;
     }
     if (ntab > 0 && ntab > ps->tab_cap) {
-        dfree(ps->dtab);
-        if (ps->htab)
-            (void)hipHostFree(ps->htab);
-        ps->htab = nullptr;
+        if (ps->dtab)  // launches of the call before may still read the table
+            HIPCHECK(hipDeviceSynchronize());
+        pfree(ps->dtab);
+        pfree(ps->htab);
         ps->tab_cap = 0;
-        int rc = dalloc(&ps->dtab, ntab);
-        if (rc)
+        int rc;
+        if ((rc = palloc(&ps->dtab, ntab)) || (rc = palloc(&ps->htab, ntab, true)))
             return rc;
-        if (hipHostMalloc((void **)&ps->htab, ntab * sizeof(TimeEntry), hipHostMallocDefault) !=
-            hipSuccess)
-            return fail(LP_ENOMEM, "pinned allocation of the time table failed");
         ps->tab_cap = ntab;
     }
     if (!rkf) {
         size_t q = 0;
+        int hint = 0;
         for (auto &sg : plan.segs) {
             for (int64_t h = 0; h <= 2 * sg.second; ++h) {
                 const int64_t nn = sg.first + h / 2;
                 const double t = (h & 1) ? t0 + ((double)nn + 0.5) * dt : t0 + (double)nn * dt;
-                int rc = bracket(fs, res, t, ps->htab[q]);
+                int rc = bracket(fs, res, t, ps->htab[q], hint);
                 if (rc)
                     return rc;
                 plan.used[ps->htab[q].sa] = plan.used[ps->htab[q].sb] = 1;
@@ -1707,27 +1792,25 @@ extern "C" int pset_status(lp_pset *ps, lp_counts *c, uint8_t *status)
 {
     if (!ps || !c)
         return fail(LP_EINVAL, "null argument");
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
-    std::vector<uint8_t> st((size_t)ps->n);
-    HIPCHECK(hipMemcpy(st.data(), ps->dst, st.size(), hipMemcpyDeviceToHost));
-    unsigned long long steps[2] = {0, 0};
-    if (int rc = read_counters(ps, steps))
-        return rc;
+    const DeviceGuard dev(ps->device);
+    const std::lock_guard<std::mutex> lock(ps->scratch_mu);
+    unsigned long long v[6];
+    HIPCHECK(lp::launch_count_status(ps->dst, (size_t)ps->n, ps->dpsteps, ps->dstat,
+                                     ps->last_stream));
+    const lp_readback seg[2] = {{v, ps->dstat, sizeof v},
+                                {status, ps->dst, status ? (size_t)ps->n : 0}};
+    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 2));
     lp_counts r{};
     r.n = ps->n;
-    for (uint8_t s : st) {
-        if (s == 0) r.active++;
-        if (s & LP_ST_OOB) r.oob++;
-        if (s & LP_ST_LAND) r.land++;
-        if (s & LP_ST_DELETED) r.deleted++;
-    }
-    r.particle_steps = (int64_t)steps[0];
-    r.rejected_steps = (int64_t)steps[1];
+    r.active = (int64_t)v[0];
+    r.oob = (int64_t)v[1];
+    r.land = (int64_t)v[2];
+    r.deleted = (int64_t)v[3];
+    r.particle_steps = (int64_t)v[4];
+    r.rejected_steps = (int64_t)v[5];
     r.step = ps->step;
     r.time = ps->t0 + (double)ps->step * (ps->dt != 0.0 ? ps->dt : 0.0);
     *c = r;
-    if (status)
-        std::memcpy(status, st.data(), st.size());
     return LP_OK;
 }
 
@@ -1735,10 +1818,11 @@ extern "C" int pset_get_behaviour(lp_pset *ps, double *temp, double *age)
 {
     if (!ps)
         return fail(LP_EINVAL, "null argument");
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
     const size_t N = (size_t)ps->n;
-    if (temp) HIPCHECK(hipMemcpy(temp, ps->dtemp, N * 8, hipMemcpyDeviceToHost));
-    if (age) HIPCHECK(hipMemcpy(age, ps->dage, N * 8, hipMemcpyDeviceToHost));
+    const lp_readback seg[2] = {{temp, ps->dtemp, temp ? N * 8 : 0},
+                                {age, ps->dage, age ? N * 8 : 0}};
+    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 2));
+    HIPCHECK(hipStreamSynchronize(ps->last_stream));
     return LP_OK;
 }
 
@@ -1748,12 +1832,12 @@ extern "C" int pset_records_behaviour(lp_pset *ps, double *temp, double *age)
         return fail(LP_EINVAL, "null argument");
     if (!ps->behave_records)
         return fail(LP_ESTATE, "no execute with a worked-example kernel has run");
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
     const size_t T = (size_t)(ps->nrec * ps->nper);
-    if (T == 0 || !ps->rtemp)
-        return LP_OK;
-    if (temp) HIPCHECK(hipMemcpy(temp, ps->rtemp, T * 8, hipMemcpyDeviceToHost));
-    if (age) HIPCHECK(hipMemcpy(age, ps->rage, T * 8, hipMemcpyDeviceToHost));
+    const bool any = T > 0 && ps->rtemp;
+    const lp_readback seg[2] = {{temp, ps->rtemp, any && temp ? T * 8 : 0},
+                                {age, ps->rage, any && age ? T * 8 : 0}};
+    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 2));
+    HIPCHECK(hipStreamSynchronize(ps->last_stream));
     return LP_OK;
 }
 
@@ -1761,8 +1845,8 @@ extern "C" int pset_get_step_exponents(lp_pset *ps, int8_t *e)
 {
     if (!ps || !e)
         return fail(LP_EINVAL, "null argument");
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
-    HIPCHECK(hipMemcpy(e, ps->dexp, (size_t)ps->n, hipMemcpyDeviceToHost));
+    const lp_readback seg = {e, ps->dexp, (size_t)ps->n};
+    HIPCHECK(lp_read_back(ps->device, ps->last_stream, &seg, 1));
     return LP_OK;
 }
 
@@ -1771,35 +1855,44 @@ extern "C" int pset_get(lp_pset *ps, double *lon, double *lat, double *depth, in
 {
     if (!ps)
         return fail(LP_EINVAL, "null argument");
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
+    const DeviceGuard dev(ps->device);
+    const std::lock_guard<std::mutex> lock(ps->scratch_mu);
     const size_t N = (size_t)ps->n;
-    if (lon) HIPCHECK(hipMemcpy(lon, ps->dx, N * 8, hipMemcpyDeviceToHost));
-    if (lat) HIPCHECK(hipMemcpy(lat, ps->dy, N * 8, hipMemcpyDeviceToHost));
-    if (depth && ps->fs->is3d) HIPCHECK(hipMemcpy(depth, ps->dz, N * 8, hipMemcpyDeviceToHost));
-    if (ci || cj || ck) {
-        int32_t *d = nullptr;
-        int rc = dalloc(&d, 3 * N);
-        if (rc)
-            return rc;
-        lp::RecordParams R{};
-        R.g = ps->fs->g;
-        R.x = ps->dx;
-        R.y = ps->dy;
-        R.z = ps->dz;
-        R.status = ps->dst;
-        R.n = ps->n;
-        R.stride = 1;
-        R.nper = ps->n;
-        R.ci = d;
-        R.cj = d + N;
-        R.ck = d + 2 * N;
-        hipError_t e = lp::launch_record(R, nullptr);
-        if (e == hipSuccess) e = hipDeviceSynchronize();
-        if (e == hipSuccess && ci) e = hipMemcpy(ci, d, N * 4, hipMemcpyDeviceToHost);
-        if (e == hipSuccess && cj) e = hipMemcpy(cj, d + N, N * 4, hipMemcpyDeviceToHost);
-        if (e == hipSuccess && ck) e = hipMemcpy(ck, d + 2 * N, N * 4, hipMemcpyDeviceToHost);
-        dfree(d);
-        HIPCHECK(e);
+    const hipStream_t s = ps->last_stream;
+    const bool z = depth && ps->fs->is3d;
+    if (!(lon || lat || z || ci || cj || ck)) {
+        HIPCHECK(hipStreamSynchronize(s));
+        return LP_OK;
+    }
+    // the cells into the sort's keys and the order list that is not in use, both scratch
+    // between executes; the depth index, the third, in a round of its own
+    lp::RecordParams R{};
+    R.g = ps->fs->g;
+    R.x = ps->dx;
+    R.y = ps->dy;
+    R.z = ps->dz;
+    R.status = ps->dst;
+    R.n = ps->n;
+    R.stride = 1;
+    R.nper = ps->n;
+    int32_t *ki = (int32_t *)ps->dkeys, *kj = (int32_t *)ps->dorder[1 - ps->cur];
+    if (ci || cj) {
+        R.ci = ci ? ki : nullptr;
+        R.cj = cj ? kj : nullptr;
+        HIPCHECK(lp::launch_record(R, s));
+    }
+    const lp_readback seg[5] = {{lon, ps->dx, lon ? N * 8 : 0},
+                                {lat, ps->dy, lat ? N * 8 : 0},
+                                {depth, ps->dz, z ? N * 8 : 0},
+                                {ci, ki, ci ? N * 4 : 0},
+                                {cj, kj, cj ? N * 4 : 0}};
+    HIPCHECK(lp_read_back(ps->device, s, seg, 5));
+    if (ck) {
+        R.ci = R.cj = nullptr;
+        R.ck = ki;
+        HIPCHECK(lp::launch_record(R, s));
+        const lp_readback k = {ck, ki, N * 4};
+        HIPCHECK(lp_read_back(ps->device, s, &k, 1));
     }
     return LP_OK;
 }
@@ -1896,17 +1989,16 @@ extern "C" int pset_records(lp_pset *ps, int64_t *nrec, int64_t *nper, double *l
     *nper = ps->nper;
     if (!(lon || lat || depth || status || ci || cj || ck))
         return LP_OK;
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
     const size_t T = (size_t)(ps->nrec * ps->nper);
-    if (T == 0)
-        return LP_OK;
-    if (lon) HIPCHECK(hipMemcpy(lon, ps->rx, T * 8, hipMemcpyDeviceToHost));
-    if (lat) HIPCHECK(hipMemcpy(lat, ps->ry, T * 8, hipMemcpyDeviceToHost));
-    if (depth && ps->rz) HIPCHECK(hipMemcpy(depth, ps->rz, T * 8, hipMemcpyDeviceToHost));
-    if (status) HIPCHECK(hipMemcpy(status, ps->rst, T, hipMemcpyDeviceToHost));
-    if (ci) HIPCHECK(hipMemcpy(ci, ps->rci, T * 4, hipMemcpyDeviceToHost));
-    if (cj) HIPCHECK(hipMemcpy(cj, ps->rcj, T * 4, hipMemcpyDeviceToHost));
-    if (ck && ps->rck) HIPCHECK(hipMemcpy(ck, ps->rck, T * 4, hipMemcpyDeviceToHost));
+    const lp_readback seg[7] = {{lon, ps->rx, lon ? T * 8 : 0},
+                                {lat, ps->ry, lat ? T * 8 : 0},
+                                {depth, ps->rz, depth && ps->rz ? T * 8 : 0},
+                                {status, ps->rst, status ? T : 0},
+                                {ci, ps->rci, ci ? T * 4 : 0},
+                                {cj, ps->rcj, cj ? T * 4 : 0},
+                                {ck, ps->rck, ck && ps->rck ? T * 4 : 0}};
+    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 7));
+    HIPCHECK(hipStreamSynchronize(ps->last_stream));
     return LP_OK;
 }
 
@@ -1971,5 +2063,6 @@ void lp_set_error(const char *msg) { g_err = msg; }
 
 int lp_time_entry(const lp_fieldset *fs, double t, lp::TimeEntry *e)
 {
-    return bracket(fs, resident(fs), t, *e);
+    int hint = 0;
+    return bracket(fs, resident(fs), t, *e, hint);
 }

@@ -182,6 +182,9 @@ hipError_t launch_advect(int store, bool is3d, const AdvectParams &p, uint32_t n
 hipError_t launch_rkf45(int store, bool is3d, const AdvectParams &p, uint32_t n_launch,
                         hipStream_t s);
 hipError_t launch_record(const RecordParams &p, hipStream_t s);
+// status counts and the sums of the step counters into out[0 .. 5]
+hipError_t launch_count_status(const uint8_t *st, size_t n, const unsigned long long *steps,
+                               unsigned long long *out, hipStream_t s);
 // batched launch: met 0 flat, 1 spherical with latitude tables, 2 spherical without,
 // 3 spherical with latitude tables and the 2-term series in every run;
 // brown: some run has a Brownian term

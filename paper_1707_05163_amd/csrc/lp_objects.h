@@ -2,6 +2,7 @@
 // (internal to the library).
 #pragma once
 
+#include <mutex>
 #include <utility>
 #include <vector>
 
@@ -47,12 +48,14 @@ struct lp_fieldset {
     std::vector<int64_t> slot_seq;  // push index held by each slot, -1 = empty
     int64_t npushed = 0;
     double first_t = 0.0, last_t = 0.0;
+    bool pool_user = false;         // counted by lp_pool_user
 
     size_t plane() const { return (size_t)nx * (size_t)ny; }
 };
 
 struct lp_pset {
     lp_fieldset *fs = nullptr;
+    int device = 0;
     int64_t n = 0;
     double *dx = nullptr, *dy = nullptr, *dz = nullptr;
     uint8_t *dst = nullptr;
@@ -66,6 +69,7 @@ struct lp_pset {
     uint32_t *dkeys = nullptr, *dhist = nullptr, *dblk = nullptr;
     uint32_t nbins = 0;
     unsigned long long *dpsteps = nullptr;  // [0] particle-steps, [1] RKF45 retries
+    unsigned long long *dstat = nullptr;    // status counts and counter sums (pset_status)
     int8_t *dexp = nullptr;                  // RKF45 step exponents
     double *dtemp = nullptr, *dage = nullptr;// worked-example tracer sample and age
     bool behave_records = false;             // records carry temp and age
@@ -89,11 +93,28 @@ struct lp_pset {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof;
     int segs_since_sort = 1 << 30;
     hipStream_t last_stream = nullptr;
+    // queries that use the set's scratch arrays (pset_get, pset_status) take turns
+    std::mutex scratch_mu;
 };
 
 
 int lp_pset_reset_device(lp_pset *ps, int64_t n, const double *x, const double *y, double t0,
                          hipStream_t stream);
 void lp_set_error(const char *msg);
+// Device (or pinned host) memory from the blocks that earlier objects freed, or new;
+// nullptr and an error if there is none.  Freed only once nothing queued uses it.
+void *lp_pool_alloc(size_t bytes, bool host, hipError_t *err);
+void lp_pool_free(void *p);
+void lp_pool_purge(void);
+// A field set comes (+1) or goes (-1): with the last one the kept blocks are given back.
+void lp_pool_user(int change);
+// Device arrays (16-byte aligned) into host arrays, in stream order after what is queued;
+// returns once they are there.
+struct lp_readback {
+    void *dst;
+    const void *src;
+    size_t bytes;
+};
+hipError_t lp_read_back(int dev, hipStream_t stream, const lp_readback *segs, int nsegs);
 // bracketing resident snapshots of time t (LP_ETIME if not covered)
 int lp_time_entry(const lp_fieldset *fs, double t, lp::TimeEntry *e);

@@ -912,13 +912,18 @@ struct SegmentEvents {
 struct DeviceBuf {
     std::vector<void *> p;
     ~DeviceBuf() {
+        (void)hipDeviceSynchronize();  // (the blocks go on to the next caller)
         for (void *q : p)
-            if (q) (void)hipFree(q);
+            lp_pool_free(q);
     }
     template <class T>
     hipError_t get(T **out, size_t n) {
-        hipError_t e = dmalloc(out, n);
-        if (e == hipSuccess)
+        *out = nullptr;
+        if (n == 0)
+            return hipSuccess;
+        hipError_t e;
+        *out = (T *)lp_pool_alloc(n * sizeof(T), false, &e);
+        if (*out)
             p.push_back((void *)*out);
         return e;
     }
