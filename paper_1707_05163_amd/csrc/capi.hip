@@ -793,7 +793,7 @@ static int pset_create_common(lp_fieldset *fs, int64_t n, const double *lon, con
         (rc = palloc(&ps->dtemp, N)) || (rc = palloc(&ps->dage, N)))
         return bail(rc);
     ps->nbins = lp::sort_bins(fs->g);
-    if ((rc = palloc(&ps->dkeys, N)) || (rc = palloc(&ps->dhist, ps->nbins)) ||
+    if ((rc = palloc(&ps->dkeys, N)) || (rc = palloc(&ps->dhist, lp::sort_hist(ps->nbins, N))) ||
         (rc = palloc(&ps->dblk, lp::sort_blocksums(ps->nbins))))
         return bail(rc);
     if ((rc = palloc(&ps->dstat, 6)) || (rc = palloc(&ps->hcount, 1, true)))

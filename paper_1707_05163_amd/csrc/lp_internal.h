@@ -205,7 +205,9 @@ hipError_t launch_sort(const GridDev &g, const double *x, const double *y, const
 // bins of the sort's key: tiles (times levels in 3D), or with `cells` the cells of the
 // tiles, kTile x kTile bins a tile (2D only; ignored in 3D)
 uint32_t sort_bins(const GridDev &g, bool cells = false);
+// words that launch_sort needs at `blocksums`, and at `hist` for lists of up to n
 size_t sort_blocksums(uint32_t nbins);
+size_t sort_hist(uint32_t nbins, size_t n);
 hipError_t launch_convert_snapshot(int store, bool is3d, const float *U, const float *V,
                                    const float *W, const double *U64, const double *V64,
                                    const double *W64, size_t plane, int nzl, void *slot,

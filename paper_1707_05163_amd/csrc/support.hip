@@ -1,8 +1,8 @@
 // support.hip -- particle bookkeeping and snapshot conversion kernels:
 //   * wavefront compaction of the active-particle list (ballot + mbcnt prefix,
 //     one atomic per wave);
-//   * a counting sort of the active particles by grid tile (and level in 3D),
-//     which also drops particles that are no longer active;
+//   * counting sorts of the active particles by grid tile (and level in 3D), in LDS
+//     where the bins fit, which also drop particles that are no longer active;
 //   * conversion of float32 / float64 snapshots into the interleaved node layout
 //     of a device slot, including bfloat16 (round to nearest even) and float16
 //     with a power-of-two scale per (level, variable).
@@ -108,29 +108,51 @@ __device__ inline void wave_runs(uint32_t key, bool valid, int &start, uint32_t 
     len = (uint32_t)(next - lane);  // meaningful on the start lane
 }
 
+// the cell to look at first for coordinate x
+__device__ inline int cell_guess(const AxisDev &a, double x)
+{
+    int g = (int)((x - a.lo) * a.ginv);
+    if (!a.uniform) {
+        g = g < kGuessBins - 1 ? g : kGuessBins - 1;
+        g = a.guess[g < 0 ? 0 : g];
+    }
+    return g < 0 ? 0 : (g > a.n - 2 ? a.n - 2 : g);
+}
+
+// the cell of x from a guess g and its two faces
+__device__ inline int cell_settle(const AxisDev &a, double x, int g, double lo, double hi)
+{
+    while (g > 0 && lo > x) {
+        --g;
+        hi = lo;
+        lo = a.c[g];
+    }
+    while (g < a.n - 2 && hi <= x) {
+        ++g;
+        hi = a.c[g + 1];
+    }
+    return g;
+}
+
 __device__ inline int cell_of(const AxisDev &a, double x)
 {
-    int g;
-    if (a.uniform) {
-        g = (int)((x - a.lo) * a.ginv);
-    } else {
-        int b = (int)((x - a.lo) * a.ginv);
-        b = b < kGuessBins - 1 ? b : kGuessBins - 1;
-        b = b < 0 ? 0 : b;
-        g = a.guess[b];
-    }
-    g = g < 0 ? 0 : (g > a.n - 2 ? a.n - 2 : g);
-    while (g > 0 && a.c[g] > x)
-        --g;
-    while (g < a.n - 2 && a.c[g + 1] <= x)
-        ++g;
-    return g;
+    const int g = cell_guess(a, x);
+    return cell_settle(a, x, g, a.c[g], a.c[g + 1]);
 }
 
 // Sort key: tile index (16 x 16 cells, row-major over tiles), times the level in
 // 3D; with `cells` (2D) the tile index times 256 plus the cell's row-major index in its
 // tile, so that a wave's particles share cells, not only a tile.  Inactive particles get
 // no key and are dropped by the sort.
+__device__ inline uint32_t sort_key(const GridDev &g, int i, int j, int kk, bool cells)
+{
+    const uint32_t ntx = (uint32_t)(g.ax.n - 2) / kTile + 1;
+    uint32_t key = (uint32_t)(j / kTile) * ntx + (uint32_t)(i / kTile);
+    if (cells)
+        key = key * (uint32_t)(kTile * kTile) + (uint32_t)((j % kTile) * kTile + i % kTile);
+    return g.az.n ? key * (uint32_t)(g.az.n - 1) + (uint32_t)kk : key;
+}
+
 __global__ __launch_bounds__(256) void k_sort_keys(GridDev g, const double *x, const double *y,
                                                    const double *z, const uint8_t *status,
                                                    const uint32_t *order, const uint32_t *n_in,
@@ -141,18 +163,9 @@ __global__ __launch_bounds__(256) void k_sort_keys(GridDev g, const double *x, c
     uint32_t key = 0xFFFFFFFFu;
     if (k < n) {
         const uint32_t id = order[k];
-        if (status[id] == 0) {
-            const int i = cell_of(g.ax, x[id]);
-            const int j = cell_of(g.ay, y[id]);
-            const uint32_t ntx = (uint32_t)(g.ax.n - 2) / kTile + 1;
-            key = (uint32_t)(j / kTile) * ntx + (uint32_t)(i / kTile);
-            if (cells)
-                key = key * (uint32_t)(kTile * kTile) + (uint32_t)((j % kTile) * kTile + i % kTile);
-            if (g.az.n) {
-                const int kk = cell_of(g.az, z[id]);
-                key = key * (uint32_t)(g.az.n - 1) + (uint32_t)kk;
-            }
-        }
+        if (status[id] == 0)
+            key = sort_key(g, cell_of(g.ax, x[id]), cell_of(g.ay, y[id]),
+                           g.az.n ? cell_of(g.az, z[id]) : 0, cells);
         keys[k] = key;
     }
     const bool valid = key != 0xFFFFFFFFu;
@@ -264,6 +277,215 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t *order_in,
     base = __shfl(base, start, 64);
     if (valid)
         order_out[base + (uint32_t)(lane - start)] = order_in[k];
+}
+
+// ---------------------------------------------------------------- sorts in LDS
+// With up to kSortBins bins (2D grids up to about 2000 x 2000 nodes) a block counts its
+// part of the list in LDS and no global atomic is taken: k_sort_hist writes one row of
+// counts per block, k_sort_columns turns each bin's column into offsets, and k_sort_apply
+// scans the totals, each block for itself, and hands out places from LDS counters.  Bound
+// by the chain of reads order -> position -> cell faces, so a thread has kSortItems of them
+// in flight, and a block only 2048 particles until there are 256 blocks (with 4096 a block
+// k_sort_hist took 13.5 us for 10k particles, not 7.2; one block for the whole list 24).
+// 13 + 5 + 8 us for 500k particles in 4050 bins, 7 + 3 + 5 us for 10k (a call of 60 steps
+// on 10k: 155 -> 144 us; 24 sets of 1k to 2M in one batch: 68 -> 63 ms).  The six launches
+// above take one global atomic per particle, 54 + 52 us on average over those 24 sets and
+// up to 1.4 ms for the largest; they stay for grids with more bins.
+constexpr uint32_t kSortBins = 15360, kSortThreads = 1024;
+constexpr int kSortItems = 2;
+constexpr uint32_t kSortStep = kSortItems * kSortThreads;
+constexpr uint32_t kSortGroups = 16;  // row groups of k_sort_columns
+
+__host__ __device__ inline uint32_t sort_parts(uint32_t n)
+{
+    const uint32_t parts = (n + kSortStep - 1) / kSortStep;  // at most 256 blocks
+    return parts < 256 ? (parts ? parts : 1) : 256;
+}
+
+__host__ __device__ inline uint32_t sort_chunk(uint32_t n)
+{
+    const uint32_t parts = sort_parts(n);
+    return ((n + parts - 1) / parts + kSortThreads - 1) / kSortThreads * kSortThreads;
+}
+
+// ids and keys of the list positions k0 + q kSortThreads below hi (hi > 0)
+template <int Q>
+__device__ inline void sort_load(const GridDev &g, const double *x, const double *y,
+                                 const double *z, const uint8_t *status, const uint32_t *order,
+                                 uint32_t k0, uint32_t hi, bool cells, uint32_t *id, uint32_t *key)
+{
+    const AxisDev *ax[3] = {&g.ax, &g.ay, &g.az};
+    uint8_t st[Q];
+    double p[Q][3], lo[Q][3], up[Q][3];
+    int c[Q][3];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t k = k0 + (uint32_t)q * kSortThreads;
+        id[q] = order[k < hi ? k : hi - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        st[q] = status[id[q]];
+        p[q][0] = x[id[q]];
+        p[q][1] = y[id[q]];
+        p[q][2] = g.az.n ? z[id[q]] : 0.0;
+    }
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+        if (v < 2 || g.az.n)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                c[q][v] = cell_guess(*ax[v], p[q][v]);
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+        if (v < 2 || g.az.n)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                lo[q][v] = ax[v]->c[c[q][v]];
+                up[q][v] = ax[v]->c[c[q][v] + 1];
+            }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t k = k0 + (uint32_t)q * kSortThreads;
+        int m[3] = {0, 0, 0};
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+            if (v < 2 || g.az.n)
+                m[v] = cell_settle(*ax[v], p[q][v], c[q][v], lo[q][v], up[q][v]);
+        key[q] = k < hi && st[q] == 0 ? sort_key(g, m[0], m[1], m[2], cells) : 0xFFFFFFFFu;
+    }
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_sort_hist(
+    GridDev g, const double *x, const double *y, const double *z, const uint8_t *status,
+    const uint32_t *order, const uint32_t *n_in, uint32_t chunk, uint32_t nbins, uint32_t *keys,
+    uint32_t *rows, bool cells)
+{
+    extern __shared__ uint32_t bins[];
+    for (uint32_t b = threadIdx.x; b < nbins; b += kSortThreads)
+        bins[b] = 0u;
+    __syncthreads();
+    const uint32_t n = *n_in, lo = blockIdx.x * chunk;
+    const uint32_t hi = lo + chunk < n ? lo + chunk : n;
+    for (uint32_t k0 = lo; k0 < hi; k0 += kSortStep) {
+        uint32_t id[kSortItems], key[kSortItems];
+        sort_load<kSortItems>(g, x, y, z, status, order, k0 + threadIdx.x, hi, cells, id, key);
+#pragma unroll
+        for (int q = 0; q < kSortItems; ++q) {
+            const uint32_t k = k0 + threadIdx.x + (uint32_t)q * kSortThreads;
+            if (key[q] != 0xFFFFFFFFu)
+                atomicAdd(&bins[key[q]], 1u);
+            if (k < hi)
+                keys[k] = key[q];
+        }
+    }
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < nbins; b += kSortThreads)
+        rows[(size_t)blockIdx.x * nbins + b] = bins[b];
+}
+
+// each bin's counts over the blocks -> offsets within the bin; its total to totals
+// (64 bins x kSortGroups groups of rows a block, at most 16 rows a thread)
+__global__ __launch_bounds__(64 * kSortGroups) void k_sort_columns(uint32_t *rows, uint32_t nbins,
+                                                                   uint32_t parts,
+                                                                   uint32_t *totals)
+{
+    __shared__ uint32_t sum[kSortGroups][64];
+    const uint32_t lane = threadIdx.x & 63u, grp = threadIdx.x >> 6;
+    const uint32_t b = blockIdx.x * 64u + lane;
+    const uint32_t per = (parts + kSortGroups - 1) / kSortGroups, p0 = grp * per;
+    constexpr int kRows = 256 / kSortGroups;
+    uint32_t v[kRows], mine = 0;
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) {
+        const bool in = (uint32_t)q < per && p0 + q < parts && b < nbins;
+        v[q] = in ? rows[(size_t)(p0 + q) * nbins + b] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < kRows; ++q)
+        mine += v[q];
+    sum[grp][lane] = mine;
+    __syncthreads();
+    uint32_t run = 0, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kSortGroups; ++w) {
+        run += w < grp ? sum[w][lane] : 0u;
+        total += sum[w][lane];
+    }
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) {
+        if ((uint32_t)q < per && p0 + q < parts && b < nbins)
+            rows[(size_t)(p0 + q) * nbins + b] = run;
+        run += v[q];
+    }
+    if (grp == 0 && b < nbins)
+        totals[b] = total;
+}
+
+// exclusive scan of the nbins values at v (LDS) by one block; returns their sum
+__device__ inline uint32_t scan_bins(uint32_t *v, uint32_t nbins)
+{
+    __shared__ uint32_t wsum[kSortThreads / 64];
+    const uint32_t per = (nbins + kSortThreads - 1) / kSortThreads, lo = threadIdx.x * per;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint32_t s = 0;
+    for (uint32_t b = lo; b < lo + per && b < nbins; ++b)
+        s += v[b];
+    uint32_t incl = s;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t t = __shfl_up(incl, off, 64);
+        if (lane >= off)
+            incl += t;
+    }
+    if (lane == 63)
+        wsum[wid] = incl;
+    __syncthreads();
+    uint32_t run = incl - s, total = 0;
+    for (int w = 0; w < (int)(kSortThreads / 64); ++w) {
+        run += w < wid ? wsum[w] : 0u;
+        total += wsum[w];
+    }
+    for (uint32_t b = lo; b < lo + per && b < nbins; ++b) {
+        const uint32_t c = v[b];
+        v[b] = run;
+        run += c;
+    }
+    return total;
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_sort_apply(const uint32_t *order_in,
+                                                             const uint32_t *n_in, uint32_t chunk,
+                                                             uint32_t nbins, const uint32_t *keys,
+                                                             const uint32_t *rows,
+                                                             const uint32_t *totals,
+                                                             uint32_t *order_out, uint32_t *n_out)
+{
+    extern __shared__ uint32_t bins[];
+    for (uint32_t b = threadIdx.x; b < nbins; b += kSortThreads)
+        bins[b] = totals[b];
+    __syncthreads();
+    const uint32_t total = scan_bins(bins, nbins);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *n_out = total;
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < nbins; b += kSortThreads)
+        bins[b] += rows[(size_t)blockIdx.x * nbins + b];
+    __syncthreads();
+    const uint32_t n = *n_in, lo = blockIdx.x * chunk;
+    const uint32_t hi = lo + chunk < n ? lo + chunk : n;
+    for (uint32_t k0 = lo + threadIdx.x; k0 < hi; k0 += kSortStep) {
+        uint32_t id[kSortItems], key[kSortItems];
+#pragma unroll
+        for (int q = 0; q < kSortItems; ++q) {
+            const uint32_t k = k0 + (uint32_t)q * kSortThreads;
+            key[q] = k < hi ? keys[k] : 0xFFFFFFFFu;
+            id[q] = k < hi ? order_in[k] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < kSortItems; ++q)
+            if (key[q] != 0xFFFFFFFFu)
+                order_out[atomicAdd(&bins[key[q]], 1u)] = id[q];
+    }
 }
 
 // ---------------------------------------------------------------- snapshot conversion
@@ -411,7 +633,15 @@ uint32_t sort_bins(const GridDev &g, bool cells)
     return nb;
 }
 
-size_t sort_blocksums(uint32_t nbins) { return (nbins + kScanChunk - 1) / kScanChunk; }
+size_t sort_blocksums(uint32_t nbins)
+{
+    return nbins <= kSortBins ? nbins : (nbins + kScanChunk - 1) / kScanChunk;
+}
+
+size_t sort_hist(uint32_t nbins, size_t n)
+{
+    return nbins <= kSortBins ? (size_t)nbins * sort_parts((uint32_t)n) : nbins;
+}
 
 hipError_t launch_sort(const GridDev &g, const double *x, const double *y, const double *z,
                        const uint8_t *status, const uint32_t *order_in, const uint32_t *n_in,
@@ -419,13 +649,26 @@ hipError_t launch_sort(const GridDev &g, const double *x, const double *y, const
                        uint32_t *blocksums, uint32_t *order_out, uint32_t *n_out,
                        hipStream_t s, bool cells)
 {
+    cells = cells && !g.az.n;
+    if (nbins <= kSortBins) {
+        const size_t lds = (size_t)nbins * sizeof(uint32_t);
+        const dim3 blk(kSortThreads);
+        const uint32_t parts = sort_parts(n_launch), chunk = sort_chunk(n_launch);
+        hipLaunchKernelGGL(k_sort_hist, dim3(parts), blk, lds, s, g, x, y, z, status, order_in,
+                           n_in, chunk, nbins, keys, hist, cells);
+        hipLaunchKernelGGL(k_sort_columns, dim3((nbins + 63) / 64), dim3(64 * kSortGroups), 0, s,
+                           hist, nbins, parts, blocksums);
+        hipLaunchKernelGGL(k_sort_apply, dim3(parts), blk, lds, s, order_in, n_in, chunk, nbins,
+                           keys, hist, blocksums, order_out, n_out);
+        return hipGetLastError();
+    }
     hipError_t e = launch_fill_u32(hist, 0u, nbins, s);
     if (e != hipSuccess)
         return e;
     const uint32_t nb = (n_launch + 255) / 256;
     if (nb)
         hipLaunchKernelGGL(k_sort_keys, dim3(nb), dim3(256), 0, s, g, x, y, z, status, order_in,
-                           n_in, keys, hist, cells && !g.az.n);
+                           n_in, keys, hist, cells);
     const uint32_t nblk = (uint32_t)sort_blocksums(nbins);
     hipLaunchKernelGGL(k_scan_partial, dim3(nblk), dim3(kScanThreads), 0, s, hist, nbins,
                        blocksums);

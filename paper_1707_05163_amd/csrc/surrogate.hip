@@ -1296,7 +1296,7 @@ extern "C" int pset_execute_surrogate(lp_pset *ps, lp_model *m, double runtime, 
     // sized for tiles)
     const uint32_t cbins = lp::sort_bins(fs->g, true);
     uint32_t *chist, *cblk;
-    SCHECK(mem.get(&chist, (size_t)cbins));
+    SCHECK(mem.get(&chist, lp::sort_hist(cbins, (size_t)n)));
     SCHECK(mem.get(&cblk, lp::sort_blocksums(cbins)));
     int rc = model_work(m, rows);
     if (rc)
