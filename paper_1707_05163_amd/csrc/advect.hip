@@ -510,53 +510,56 @@ __device__ inline void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1)
     }
 }
 
+// 2^53 times the uniform (m + 1/2) 2^-53 of the words' upper 53 bits m, rounded once
 __device__ inline double unit53(uint32_t a, uint32_t b)
 {
     const uint64_t m = (((uint64_t)a << 32) | (uint64_t)b) >> 11;
-    return (double)m * 0x1p-53 + 0x1p-54;
+    return fma((double)(uint32_t)(m >> 32), 0x1p32, (double)(uint32_t)m + 0.5);
 }
 
-// sin and cos of 2 pi u for u in [0, 1].  The argument is a fraction of a turn, so the
-// reduction to a quarter turn is exact: 4u = q + f with q = rint(4u) and |f| <= 1/2,
-// 2 pi u = q pi/2 + f pi/2.  sin(f pi/2) and cos(f pi/2) come from their Taylor series
-// in f (coefficients (pi/2)^n / n!), cut after the f^17 and f^16 terms (the first
-// terms left out are below 1e-19 and 3e-18 at |f| = 1/2), and the quadrant q mod 4
-// rotates the pair.
-// The polynomial coefficients of sincos_turn and log_unit, in constant memory: the
+// The polynomial coefficients of sincos_quarters and log_unit, in constant memory: the
 // Brownian kernels read them with scalar loads inside their step loop (an index the
 // compiler cannot prove constant keeps the loads there), so that they do not sit in
-// vector registers across the loop.
+// vector registers across the loop.  The series' terms are stored with the opposite sign
+// and subtracted: the compiler then takes the three-operand form of the fused multiply-add,
+// which reads the coefficient from its scalar registers (the accumulating form wants it
+// copied into vector registers first, 50 moves a step).
 __constant__ double kBmCoef[28] = {
-    // sin(f pi/2) / f, highest power first (9)
-    0x1.aaec32af93359p-38, -0x1.6fadb9f155744p-31, 0x1.e8f434d018d63p-25,
-    -0x1.e3074fde8871fp-19, 0x1.50783487ee782p-13, -0x1.32d2cce62bd86p-8,
-    0x1.466bc6775aae2p-4, -0x1.4abbce625be53p-1, 0x1.921fb54442d18p+0,
-    // (cos(f pi/2) - 1) / f^2, highest power first (8)
-    0x1.20c62c2f2d7f5p-34, -0x1.b6e24f44b128fp-28, 0x1.f9d38a3763cc3p-22,
-    -0x1.a6d1f2a204a8cp-16, 0x1.e1f506891babbp-11, -0x1.55d3c7e3cbffap-6,
-    0x1.03c1f081b5ac4p-2, -0x1.3bd3cc9be45dep+0,
-    // atanh series 1/19 .. 1/3 (9)
-    1.0 / 19.0, 1.0 / 17.0, 1.0 / 15.0, 1.0 / 13.0, 1.0 / 11.0, 1.0 / 9.0, 1.0 / 7.0,
-    1.0 / 5.0, 1.0 / 3.0,
+    // -sin(f pi/2) / f, highest power first (9)
+    -0x1.aaec32af93359p-38, 0x1.6fadb9f155744p-31, -0x1.e8f434d018d63p-25,
+    0x1.e3074fde8871fp-19, -0x1.50783487ee782p-13, 0x1.32d2cce62bd86p-8,
+    -0x1.466bc6775aae2p-4, 0x1.4abbce625be53p-1, -0x1.921fb54442d18p+0,
+    // (1 - cos(f pi/2)) / f^2, highest power first (8)
+    -0x1.20c62c2f2d7f5p-34, 0x1.b6e24f44b128fp-28, -0x1.f9d38a3763cc3p-22,
+    0x1.a6d1f2a204a8cp-16, -0x1.e1f506891babbp-11, 0x1.55d3c7e3cbffap-6,
+    -0x1.03c1f081b5ac4p-2, 0x1.3bd3cc9be45dep+0,
+    // -1/19 .. -1/3 of the atanh series (9)
+    -1.0 / 19.0, -1.0 / 17.0, -1.0 / 15.0, -1.0 / 13.0, -1.0 / 11.0, -1.0 / 9.0, -1.0 / 7.0,
+    -1.0 / 5.0, -1.0 / 3.0,
     // log 2, head and tail (2)
     0x1.62e42fefa3800p-1, 0x1.ef35793c76730p-45};
 
-__device__ inline void sincos_turn(double u, double &sn, double &cs,
-                                   const double *k = kBmCoef)
+// sin and cos of t quarter turns for t in [0, 4].  The argument is a fraction of a turn, so
+// the reduction to a quarter turn is exact: t = q + f with q = rint(t) and |f| <= 1/2, an
+// angle of q pi/2 + f pi/2.  sin(f pi/2) and cos(f pi/2) come from their Taylor series
+// in f (coefficients (pi/2)^n / n!), cut after the f^17 and f^16 terms (the first
+// terms left out are below 1e-19 and 3e-18 at |f| = 1/2), and the quadrant q mod 4
+// rotates the pair.
+__device__ inline void sincos_quarters(double t, double &sn, double &cs,
+                                       const double *k = kBmCoef)
 {
-    const double t = 4.0 * u;
     const double q = rint(t);
     const double f = t - q;  // exact
     const double f2 = f * f;
-    double ps = k[0];
+    double ps = -k[0];
 #pragma unroll
     for (int i = 1; i < 9; ++i)
-        ps = fma(ps, f2, k[i]);
+        ps = fma(ps, f2, -k[i]);
     const double S = ps * f;
-    double pc = k[9];
+    double pc = -k[9];
 #pragma unroll
     for (int i = 10; i < 17; ++i)
-        pc = fma(pc, f2, k[i]);
+        pc = fma(pc, f2, -k[i]);
     const double C = fma(pc, f2, 1.0);
     const int qi = (int)q;
     double a = (qi & 1) ? C : S, b = (qi & 1) ? S : C;
@@ -564,15 +567,16 @@ __device__ inline void sincos_turn(double u, double &sn, double &cs,
     cs = ((qi + 1) & 2) ? -b : b;
 }
 
-// Natural logarithm of u in (0, 1] (the uniforms of unit53).  u = m 2^e with m in
+// Natural logarithm of u in (0, 1] given as 2^53 u (unit53).  u = m 2^e with m in
 // [sqrt(1/2), sqrt(2)); log m = 2 atanh(s) with s = (m - 1) / (m + 1), |s| < 0.1716,
 // from the series atanh(s) = s + s^3/3 + s^5/5 + ..., cut after s^19 (the first term
 // left out is below 2.4e-17 relative); e log 2 with log 2 split into a head whose
 // products with |e| < 2^11 are exact and a tail.  Within about two ulps.
-__device__ inline double log_unit(double u, const double *k = kBmCoef)
+__device__ inline double log_unit(double u53, const double *k = kBmCoef)
 {
     int e;
-    double m = frexp(u, &e);  // m in [1/2, 1)
+    double m = frexp(u53, &e);  // m in [1/2, 1)
+    e -= 53;
     if (m < 0.70710678118654752) {
         m = 2.0 * m;
         e -= 1;
@@ -584,27 +588,27 @@ __device__ inline double log_unit(double u, const double *k = kBmCoef)
     double sq = num * r;
     sq = fma(fma(-den, sq, num), r, sq);  // s to within an ulp
     const double z = sq * sq;
-    double p = k[17];
+    double p = -k[17];
 #pragma unroll
     for (int i = 18; i < 26; ++i)
-        p = fma(p, z, k[i]);
+        p = fma(p, z, -k[i]);
     const double s2 = 2.0 * sq;
     const double lm = fma(s2 * z, p, s2);  // log m
     const double de = (double)e;
     return fma(de, k[26], fma(de, k[27], lm));
 }
 
-// Square root of x in [2^-60, 2^60]: the hardware reciprocal square root refined by two
-// Newton steps for 1/sqrt(x), then y = x r with one correction (x - y^2) r / 2.  Within
-// about an ulp.
+// Square root of x in [2^-60, 2^60]: with g = x r and h = r / 2 from the hardware
+// reciprocal square root r, one step of Goldschmidt's iteration for both, then one
+// correction g + (x - g^2) h.  Within about an ulp.
 __device__ inline double sqrt_mid(double x)
 {
-    double r = __builtin_amdgcn_rsq(x);
-    const double hx = 0.5 * x;
-    r = r * fma(-hx * r, r, 1.5);
-    r = r * fma(-hx * r, r, 1.5);
-    const double y = x * r;
-    return fma(fma(-y, y, x), 0.5 * r, y);
+    const double r = __builtin_amdgcn_rsq(x);
+    double g = x * r, h = 0.5 * r;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    return fma(fma(-g, g, x), h, g);
 }
 
 // cos of a latitude in degrees, |lat| <= 90: a quarter turn at most, through the turn
@@ -612,23 +616,27 @@ __device__ inline double sqrt_mid(double x)
 __device__ inline double cos_deg(double lat)
 {
     double sn, cs;
-    sincos_turn(lat * (1.0 / 360.0), sn, cs);
+    sincos_quarters(4.0 * (lat * (1.0 / 360.0)), sn, cs);
     return cs;
 }
 
-// Two standard normals from two uniforms (Box-Muller); k: the coefficient table.
+// Two standard normals from two uniforms of unit53 (Box-Muller); k: the coefficient table.
 __device__ inline void box_muller(double u1, double u2, double &n1, double &n2,
                                   const double *k = kBmCoef)
 {
     const double r = sqrt_mid(-2.0 * log_unit(u1, k));
     double sn, cs;
-    sincos_turn(u2, sn, cs, k);
+    sincos_quarters(0x1p-51 * u2, sn, cs, k);
     n1 = r * cs;
     n2 = r * sn;
 }
 
 // The random term of Eq. (1) for one step, in metres: sqrt(2 Kh |dt|) times the two
-// normals drawn from the particle's Philox words for (id, step).
+// normals drawn from the particle's Philox words for (id, step).  Bound by the FP64 issue
+// rate, some 230 of the 2D kernels' 400 instructions a step; with the coefficients read in
+// place, the key's values added in scalar registers and shorter scalings and square root
+// 500k particles on the sphere take 9.3 ms for 1152 steps (9.85 before) and two flat sets
+// of 1M 7.9 ms for 288 (8.4).
 // LOOP_LOADS: read the Box-Muller coefficients inside the step loop (P.zero is 0 at
 // run time, but the compiler cannot know it, so the scalar loads stay in the loop
 // instead of the constants occupying vector registers across it).  That pays in the
@@ -636,13 +644,18 @@ __device__ inline void box_muller(double u1, double u2, double &n1, double &n2,
 // ones, with the metric's extra state, are faster with the constants in place.
 template <bool LOOP_LOADS>
 __device__ inline void brownian_metres(const AdvectParams &P, uint32_t id, int64_t step,
-                                       double dt, double &dx, double &dy)
+                                       double dt, double &dx, double &dy,
+                                       const double *kv = kBmCoef)
 {
     uint32_t w[4] = {id, (uint32_t)step, 0u, 0u};
-    philox4x32_10(w, P.run_id, P.seed);
+    // (the key's ten values are scalar additions inside the loop: with a key the compiler
+    // can tell is the same in every step it keeps all of them, 20 registers it has not got,
+    // and reads each back from a vector lane)
+    const uint32_t zs = P.zero & (uint32_t)step;
+    philox4x32_10(w, P.run_id + zs, P.seed + zs);
     double n1, n2;
     box_muller(unit53(w[0], w[1]), unit53(w[2], w[3]), n1, n2,
-               LOOP_LOADS ? kBmCoef + (P.zero & (uint32_t)step) : kBmCoef);
+               LOOP_LOADS ? kBmCoef + (P.zero & (uint32_t)step) : kv);
     const double sig = sqrt(2.0 * P.Kh * fabs(dt));
     dx = sig * n1;
     dy = sig * n2;
@@ -1611,6 +1624,21 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
             R tc[8] = {}, tm[8] = {}, te[8] = {};  // see stage2_rk4
             const double dt = P.dt, dt6 = P.dt6;
             double bx = 0.0, by = 0.0;
+            // The spherical Brownian kernel with the shortest metric keeps the polynomials'
+            // later coefficients in vector registers, as values the compiler cannot see
+            // through: known constants it copies before each use, 17 moves a step (9.7 ms
+            // for the case at brownian_metres, 9.3 so).  With all of them it spills, as do
+            // the kernels with more metric terms and the batch's with these.
+            double kv[28];
+            if constexpr (BROWN && MET != kFlat) {
+#pragma unroll
+                for (int q = 0; q < 28; ++q) {
+                    kv[q] = kBmCoef[q];
+                    const bool late = (q > 2 && q < 9) || (q > 11 && q < 17) || (q > 18 && q < 26);
+                    if (BS && MET == kSphTable2 && late)
+                        asm volatile("" : "+v"(kv[q]));
+                }
+            }
             for (int s = 0; s < P.nsteps; ++s) {
                 ++steps;
                 // (a steady field needs no times: every entry names the one snapshot)
@@ -1672,10 +1700,10 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                     double tx = fma(dx, g, bx), ty = fma(dy, g, by);
                     if (BROWN && P.Kh > 0.0) {
                         double wx, wy;
-                        brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, wx, wy);
+                        brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, wx, wy, kv);
                         if constexpr (MET != kFlat) {
                             wx = wx * inv_metres_lon<MET>(c, P, ty, ys);
-                            wy = wy / kMetresPerDegree;
+                            wy = wy * (1.0 / kMetresPerDegree);
                         }
                         xs = xs + wx;
                         ys = ys + wy;
@@ -2398,7 +2426,7 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                         brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, wx, wy);
                         if constexpr (MET != kFlat) {
                             wx = wx * inv_metres_lon<MET>(c, P, ty, ys);
-                            wy = wy / kMetresPerDegree;
+                            wy = wy * (1.0 / kMetresPerDegree);
                         }
                         xs = xs + wx;
                         ys = ys + wy;
