@@ -69,15 +69,15 @@ STATE_BYTES_RKF45_2D = STATE_BYTES_2D + 2  # plus the step exponent read and wri
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 COUNTER_SOURCE = "profiles/counters_k_advect2d_cfg1_k_advect3d_cfg2.md"
 COUNTERS = {
-    "advect_sha256": "07a8e58413fc66a254fc93aeedf8de7f10067d808f557bdb13fd324019b54e0c",
-    "cfg1": (185046.8, 64867.8),    # (FETCH_SIZE KiB, WRITE_SIZE KiB) per launch of k_advect2d
-    "cfg2": (7774787.2, 246243.9),  # the same for k_advect3d
+    "advect_sha256": "60982b024b62cf64be1718ebe5eab3fa66111116c8cdd685a37acf93317eb1c7",
+    "cfg1": (183865.5, 64909.8),    # (FETCH_SIZE KiB, WRITE_SIZE KiB) per launch of k_advect2d
+    "cfg2": (7777542.9, 246625.2),  # the same for k_advect3d
     # (TCC_HIT_sum, TCC_MISS_sum) per launch: L2 requests of the same kernels
-    "cfg1_l2": (3889879.5, 4499888.4),
-    "cfg2_l2": (71593672.8, 126480295.3),
+    "cfg1_l2": (3991949.0, 4484334.7),
+    "cfg2_l2": (71172126.0, 126524412.7),
     # (SQ_INSTS_VALU, SQ_INSTS_SALU) wave instructions per launch
-    "cfg1_sq": (8.45743e+08, 4.75763e+08),
-    "cfg2_sq": (8.06692e+09, 3.03271e+09),
+    "cfg1_sq": (6.97042e+08, 4.75934e+08),
+    "cfg2_sq": (7.37159e+09, 2.67902e+09),
 }
 
 
