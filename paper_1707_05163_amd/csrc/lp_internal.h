@@ -224,7 +224,5 @@ hipError_t launch_train_update(int mode, const UpdateArgs &u, hipStream_t s);
 hipError_t launch_mlp_fused(const MlpFusedArgs &a, hipStream_t s);
 // the first nvalid of n values rounded to bf16, the rest zero
 hipError_t launch_to_bf16(const float *x, int64_t nvalid, int64_t n, uint16_t *y, hipStream_t s);
-hipError_t launch_level_absmax(const float *F, size_t plane, int nzl, float *out,
-                               hipStream_t s);
 
 }  // namespace lp
