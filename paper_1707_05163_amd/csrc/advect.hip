@@ -1472,7 +1472,8 @@ __device__ inline bool stage2(const AdvectParams &P, Cell2<typename Real<ST>::T,
 // a step then forms coefficients once (16 products and 8 sums, against 32 products for
 // middle and end).  The end's weight is its own tau, or 1 where the table already names
 // the next bracket for a time on the snapshot; a step that straddles a snapshot forms the
-// middle's by themselves.
+// middle's by themselves.  (The table names no two stages of a step by one bracket where
+// tau does not run straight between them.)
 struct StepTimes {
     TimeEntry e0, e1, e2;
     bool mean;

@@ -644,6 +644,41 @@ int bracket(const lp_fieldset *fs, const std::vector<Resident> &r, double t, Tim
     return LP_OK;
 }
 
+// Whether two stages of a step of length adt that have the same bracket are always in the
+// same pass of it, so that tau runs straight between them.  Passes of a bracket are a
+// period less its own length apart; with a step as long as that (two snapshots and a wrap
+// shorter than the step, or a step near the period) they need not be.  The margin covers
+// the rounding of the stage times.
+bool one_pass(const lp_fieldset *fs, const std::vector<Resident> &r, double adt)
+{
+    if (!(fs->period > 0.0) || r.size() < 2)
+        return true;
+    double longest = r[0].t + fs->period - r.back().t;
+    for (size_t k = 0; k + 1 < r.size(); ++k)
+        longest = std::max(longest, r[k + 1].t - r[k].t);
+    return adt < 0.999 * (fs->period - longest);
+}
+
+// The cached 2D kernel takes the field at a step's middle as the mean of its ends where
+// the three entries name one bracket (an end on the later snapshot may name the next).
+// Where a step has left the bracket and come back to it a period on, tau does not run
+// straight from start to end: the middle's entry then names the same time by the bracket
+// turned round, which no other entry matches.
+void separate_middles(TimeEntry *tab, int64_t steps)
+{
+    for (int64_t q = 0; q < steps; ++q) {
+        const TimeEntry &a = tab[2 * q], &c = tab[2 * q + 2];
+        TimeEntry &b = tab[2 * q + 1];
+        const bool same = c.sa == b.sa && c.sb == b.sb, next = c.tau == 0.0 && c.sa == b.sb;
+        if (a.sa != b.sa || a.sb != b.sb || !(same || next))
+            continue;
+        if (std::fabs(2.0 * b.tau - (a.tau + (same ? c.tau : 1.0))) > 0x1p-36) {
+            std::swap(b.sa, b.sb);
+            b.tau = 1.0 - b.tau;
+        }
+    }
+}
+
 }  // namespace
 
 extern "C" int fieldset_get_snapshot(lp_fieldset *fs, double t, float *U, float *V, float *W)
@@ -1087,6 +1122,7 @@ int exec_prepare(lp_pset *ps, double runtime, double dt, double outputdt, const 
     if (!rkf) {
         size_t q = 0;
         int hint = 0;
+        const bool straight = one_pass(fs, res, adt);
         for (auto &sg : plan.segs) {
             for (int64_t h = 0; h <= 2 * sg.second; ++h) {
                 const int64_t nn = sg.first + h / 2;
@@ -1097,6 +1133,8 @@ int exec_prepare(lp_pset *ps, double runtime, double dt, double outputdt, const 
                 plan.used[ps->htab[q].sa] = plan.used[ps->htab[q].sb] = 1;
                 ++q;
             }
+            if (!straight)
+                separate_middles(ps->htab + q - (2 * sg.second + 1), sg.second);
         }
     }
     ps->t0 = t0;
