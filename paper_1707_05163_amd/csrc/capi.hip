@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "../../include/lp.h"
+#include "lp_fmod.h"
 #include "lp_internal.h"
 #include "lp_objects.h"
 
@@ -569,33 +570,6 @@ std::vector<Resident> resident(const lp_fieldset *fs)
     return r;
 }
 
-// Bracket of time t among the resident snapshots: linear weight tau between
-// slot sa (earlier) and sb (later).
-// fmod(a, P) for P > 0, bit for bit: where |a / P| < 2^51 the remainder a - n P with n =
-// trunc(a / P), corrected by at most one, is exact in one fused multiply-add.  (The
-// library's fmod divides bit by bit: 50 to 100 ns for each of a run's stage times.)
-double exact_fmod(double a, double P)
-{
-    double n = std::trunc(a / P);
-    if (!(std::fabs(n) < 0x1p51))
-        return std::fmod(a, P);
-    double r = std::fma(-n, P, a);
-    if (a >= 0.0) {
-        if (r < 0.0)
-            r = std::fma(-(n - 1.0), P, a);
-        else if (r >= P)
-            r = std::fma(-(n + 1.0), P, a);
-    } else {
-        if (r > 0.0)
-            r = std::fma(-(n + 1.0), P, a);
-        else if (r <= -P)
-            r = std::fma(-(n - 1.0), P, a);
-        if (r == 0.0)
-            r = -0.0;  // the sign of the dividend
-    }
-    return r;
-}
-
 // The largest k < m with r[k].t <= t (0 if none), looked for at `hint` and after it first:
 // a run's stage times follow each other.
 int last_at_or_before(const std::vector<Resident> &r, int m, double t, int &hint)
@@ -610,6 +584,8 @@ int last_at_or_before(const std::vector<Resident> &r, int m, double t, int &hint
     return hint = s;
 }
 
+// Bracket of time t among the resident snapshots: linear weight tau between
+// slot sa (earlier) and sb (later).
 int bracket(const lp_fieldset *fs, const std::vector<Resident> &r, double t, TimeEntry &e,
             int &hint)
 {

@@ -1,7 +1,8 @@
 """Periodic snapshots whose stage times leave a bracket and come back to it a period on
 within one step: each stage still takes the field at its own time.  Two snapshots with a
 wrap shorter than the step, and a bracket of three quarters of the period under a step
-of more than half of it, forward and backward, against the FP64 oracle."""
+of more than half of it, forward and backward, against the FP64 oracle.
+An infinite period, which holds the last snapshot for good."""
 
 import numpy as np
 import pytest
@@ -62,3 +63,28 @@ def test_stages_take_their_own_time(case, mesh, dtype, batch, sign):
     c, status = ps.status()
     assert np.array_equal(status, st.status)
     assert (status == 0).sum() > 100
+
+
+def test_infinite_period_is_no_period():
+    """Between the snapshots the run is the one without a period; after the last it goes
+    on in that snapshot."""
+    from paper_1707_05163_amd import FieldSet, ParticleSet
+    w, _, _ = _workload("wrap of 600 s", "spherical")
+    out = []
+    for period in (0.0, np.inf):
+        fs = FieldSet.from_workload(w, time_period=period)
+        ps = ParticleSet(fs, w.lon0, w.lat0)
+        ps.execute(DAY, 3600.0)
+        out.append(ps.get())
+    assert np.isfinite(out[0]["lon"]).all()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
+    ps.execute(DAY, 3600.0)
+    w.fields = SC.Fields(times=np.zeros(1), U=w.fields.U[1:], V=w.fields.V[1:])
+    last = ParticleSet(FieldSet.from_workload(w), out[1]["lon"], out[1]["lat"])
+    last.execute(DAY, 3600.0)
+    a, b = ps.get(), last.get()
+    ok = ps.status()[1] == 0
+    assert ok.sum() > 1000
+    assert np.abs(a["lon"] - b["lon"])[ok].max() < 1e-9 * 360
+    assert np.abs(a["lat"] - b["lat"])[ok].max() < 1e-9 * 360
