@@ -867,6 +867,16 @@ int grow_records(lp_pset *ps, int64_t need)
         (rc = palloc(&rst, tot)) || (rc = palloc(&ci, tot)) || (rc = palloc(&cj, tot)) ||
         (is3d && (rc = palloc(&ck, tot))))
         return rc;
+    double *rt = nullptr, *ra = nullptr;
+    if (ps->behave_records && ((rc = palloc(&rt, tot)) || (rc = palloc(&ra, tot)))) {
+        pfree(rt);
+        return rc;
+    }
+    // Queued records may still write the old arrays, and the copies run on the default
+    // stream, which a set's own need not wait for: the device is waited for on both sides
+    // of them (then no one uses the old blocks either).
+    if (ps->rx)
+        HIPCHECK(hipDeviceSynchronize());
     if (old) {
         HIPCHECK(hipMemcpy(rx, ps->rx, old * 8, hipMemcpyDeviceToDevice));
         HIPCHECK(hipMemcpy(ry, ps->ry, old * 8, hipMemcpyDeviceToDevice));
@@ -877,9 +887,15 @@ int grow_records(lp_pset *ps, int64_t need)
         HIPCHECK(hipMemcpy(cj, ps->rcj, old * 4, hipMemcpyDeviceToDevice));
         if (is3d)
             HIPCHECK(hipMemcpy(ck, ps->rck, old * 4, hipMemcpyDeviceToDevice));
-    }
-    if (ps->rx)  // queued records may still write the old arrays
+        if (rt && ps->rtemp) {
+            HIPCHECK(hipMemcpy(rt, ps->rtemp, old * 8, hipMemcpyDeviceToDevice));
+            HIPCHECK(hipMemcpy(ra, ps->rage, old * 8, hipMemcpyDeviceToDevice));
+        } else if (rt) {  // records taken before any worked-example kernel ran
+            HIPCHECK(hipMemset(rt, 0xFF, old * 8));
+            HIPCHECK(hipMemset(ra, 0, old * 8));
+        }
         HIPCHECK(hipDeviceSynchronize());
+    }
     pfree(ps->rx);
     pfree(ps->ry);
     pfree(ps->rz);
@@ -887,19 +903,7 @@ int grow_records(lp_pset *ps, int64_t need)
     pfree(ps->rci);
     pfree(ps->rcj);
     pfree(ps->rck);
-    if (ps->behave_records) {
-        double *rt = nullptr, *ra = nullptr;
-        if ((rc = palloc(&rt, tot)) || (rc = palloc(&ra, tot))) {
-            pfree(rt);
-            return rc;
-        }
-        if (old && ps->rtemp) {
-            HIPCHECK(hipMemcpy(rt, ps->rtemp, old * 8, hipMemcpyDeviceToDevice));
-            HIPCHECK(hipMemcpy(ra, ps->rage, old * 8, hipMemcpyDeviceToDevice));
-        } else if (old) {  // records taken before any worked-example kernel ran
-            HIPCHECK(hipMemset(rt, 0xFF, old * 8));
-            HIPCHECK(hipMemset(ra, 0, old * 8));
-        }
+    if (rt) {
         pfree(ps->rtemp);
         pfree(ps->rage);
         ps->rtemp = rt;
