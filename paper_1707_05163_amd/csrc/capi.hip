@@ -725,6 +725,34 @@ extern "C" int fieldset_resident(const lp_fieldset *fs, int32_t *count, double *
 }
 
 // ---------------------------------------------------------------- particle sets
+namespace {
+
+// The set's work so far is on `stream`.  hipStreamPerThread is another stream in every
+// thread: an event marks the place in this one.
+int note_stream(lp_pset *ps, hipStream_t stream)
+{
+    ps->last_stream = stream;
+    if (stream == hipStreamPerThread) {
+        if (!ps->thread_ev)
+            HIPCHECK(hipEventCreateWithFlags(&ps->thread_ev, hipEventDisableTiming));
+        HIPCHECK(hipEventRecord(ps->thread_ev, stream));
+    }
+    return LP_OK;
+}
+
+// A stream whose work comes after the set's, in any thread (the set's device is current).
+int query_stream(lp_pset *ps, hipStream_t *s)
+{
+    *s = ps->last_stream;
+    if (*s == hipStreamPerThread) {
+        *s = nullptr;
+        HIPCHECK(hipStreamWaitEvent(*s, ps->thread_ev, 0));
+    }
+    return LP_OK;
+}
+
+}  // namespace
+
 extern "C" void pset_destroy(lp_pset *ps)
 {
     if (!ps)
@@ -764,6 +792,8 @@ extern "C" void pset_destroy(lp_pset *ps)
         (void)hipEventDestroy(ps->tab_ev);
     if (ps->count_ev)
         (void)hipEventDestroy(ps->count_ev);
+    if (ps->thread_ev)
+        (void)hipEventDestroy(ps->thread_ev);
     for (auto &p : ps->prof) {
         (void)hipEventDestroy(p.first);
         (void)hipEventDestroy(p.second);
@@ -831,7 +861,8 @@ static int pset_create_common(lp_fieldset *fs, int64_t n, const double *lon, con
     if (!device_src && hipStreamSynchronize(stream) != hipSuccess)
         return bail(fail(LP_EDEVICE, "particle upload failed"));
     ps->n_launch = (uint32_t)n;
-    ps->last_stream = stream;
+    if ((rc = note_stream(ps, stream)))
+        return bail(rc);
     *out = ps;
     return LP_OK;
 }
@@ -1261,8 +1292,7 @@ int exec_finish(lp_pset *ps, ExecPlan &plan, hipStream_t stream)
     HIPCHECK(hipEventRecord(ps->count_ev, stream));
     ps->count_pending = true;
     ps->step += plan.nsteps;
-    ps->last_stream = stream;
-    return LP_OK;
+    return note_stream(ps, stream);
 }
 
 }  // namespace
@@ -1806,18 +1836,36 @@ extern "C" int pset_autotune_batch(lp_pset **ps, int32_t nruns, double dt, int32
     return LP_OK;
 }
 
+namespace {
+
+// The set's arrays to the host, after its work and with its stream done.
+int read_back(lp_pset *ps, const lp_readback *segs, int nsegs)
+{
+    const DeviceGuard dev(ps->device);
+    hipStream_t s;
+    if (int rc = query_stream(ps, &s))
+        return rc;
+    HIPCHECK(lp_read_back(ps->device, s, segs, nsegs));
+    HIPCHECK(hipStreamSynchronize(s));
+    return LP_OK;
+}
+
+}  // namespace
+
 extern "C" int pset_status(lp_pset *ps, lp_counts *c, uint8_t *status)
 {
     if (!ps || !c)
         return fail(LP_EINVAL, "null argument");
     const DeviceGuard dev(ps->device);
     const std::lock_guard<std::mutex> lock(ps->scratch_mu);
+    hipStream_t s;
+    if (int rc = query_stream(ps, &s))
+        return rc;
     unsigned long long v[6];
-    HIPCHECK(lp::launch_count_status(ps->dst, (size_t)ps->n, ps->dpsteps, ps->dstat,
-                                     ps->last_stream));
+    HIPCHECK(lp::launch_count_status(ps->dst, (size_t)ps->n, ps->dpsteps, ps->dstat, s));
     const lp_readback seg[2] = {{v, ps->dstat, sizeof v},
                                 {status, ps->dst, status ? (size_t)ps->n : 0}};
-    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 2));
+    HIPCHECK(lp_read_back(ps->device, s, seg, 2));
     lp_counts r{};
     r.n = ps->n;
     r.active = (int64_t)v[0];
@@ -1839,9 +1887,7 @@ extern "C" int pset_get_behaviour(lp_pset *ps, double *temp, double *age)
     const size_t N = (size_t)ps->n;
     const lp_readback seg[2] = {{temp, ps->dtemp, temp ? N * 8 : 0},
                                 {age, ps->dage, age ? N * 8 : 0}};
-    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 2));
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
-    return LP_OK;
+    return read_back(ps, seg, 2);
 }
 
 extern "C" int pset_records_behaviour(lp_pset *ps, double *temp, double *age)
@@ -1854,9 +1900,7 @@ extern "C" int pset_records_behaviour(lp_pset *ps, double *temp, double *age)
     const bool any = T > 0 && ps->rtemp;
     const lp_readback seg[2] = {{temp, ps->rtemp, any && temp ? T * 8 : 0},
                                 {age, ps->rage, any && age ? T * 8 : 0}};
-    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 2));
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
-    return LP_OK;
+    return read_back(ps, seg, 2);
 }
 
 extern "C" int pset_get_step_exponents(lp_pset *ps, int8_t *e)
@@ -1864,8 +1908,7 @@ extern "C" int pset_get_step_exponents(lp_pset *ps, int8_t *e)
     if (!ps || !e)
         return fail(LP_EINVAL, "null argument");
     const lp_readback seg = {e, ps->dexp, (size_t)ps->n};
-    HIPCHECK(lp_read_back(ps->device, ps->last_stream, &seg, 1));
-    return LP_OK;
+    return read_back(ps, &seg, 1);
 }
 
 extern "C" int pset_get(lp_pset *ps, double *lon, double *lat, double *depth, int32_t *ci,
@@ -1876,7 +1919,9 @@ extern "C" int pset_get(lp_pset *ps, double *lon, double *lat, double *depth, in
     const DeviceGuard dev(ps->device);
     const std::lock_guard<std::mutex> lock(ps->scratch_mu);
     const size_t N = (size_t)ps->n;
-    const hipStream_t s = ps->last_stream;
+    hipStream_t s;
+    if (int rc = query_stream(ps, &s))
+        return rc;
     const bool z = depth && ps->fs->is3d;
     if (!(lon || lat || z || ci || cj || ck)) {
         HIPCHECK(hipStreamSynchronize(s));
@@ -1964,7 +2009,9 @@ extern "C" int pset_get_noalloc(lp_pset *ps, double *lon, double *lat, double *d
         return fail(LP_EINVAL, "pset_get_noalloc takes sets of at most %d particles (this one "
                                "has %lld); use pset_get", LP_NOALLOC_MAX_PARTICLES,
                     (long long)ps->n);
-    const hipStream_t s = ps->last_stream;
+    hipStream_t s;
+    if (int qrc = query_stream(ps, &s))
+        return qrc;
     HIPCHECK(hipStreamSynchronize(s));
     const size_t N = (size_t)ps->n;
     if (lon) HIPCHECK(hipMemcpy(lon, ps->dx, N * 8, hipMemcpyDeviceToHost));
@@ -2015,9 +2062,7 @@ extern "C" int pset_records(lp_pset *ps, int64_t *nrec, int64_t *nper, double *l
                                 {ci, ps->rci, ci ? T * 4 : 0},
                                 {cj, ps->rcj, cj ? T * 4 : 0},
                                 {ck, ps->rck, ck && ps->rck ? T * 4 : 0}};
-    HIPCHECK(lp_read_back(ps->device, ps->last_stream, seg, 7));
-    HIPCHECK(hipStreamSynchronize(ps->last_stream));
-    return LP_OK;
+    return read_back(ps, seg, 7);
 }
 
 extern "C" int pset_timing(lp_pset *ps, double *kernel_ms, int64_t *launches)
@@ -2073,8 +2118,7 @@ int lp_pset_reset_device(lp_pset *ps, int64_t n, const double *x, const double *
     ps->dt = 0.0;
     ps->step = 0;
     ps->segs_since_sort = 1 << 30;
-    ps->last_stream = stream;
-    return LP_OK;
+    return note_stream(ps, stream);
 }
 
 void lp_set_error(const char *msg) { g_err = msg; }

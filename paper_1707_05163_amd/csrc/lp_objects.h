@@ -92,7 +92,8 @@ struct lp_pset {
     // profiling
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof;
     int segs_since_sort = 1 << 30;
-    hipStream_t last_stream = nullptr;
+    hipStream_t last_stream = nullptr;      // of the set's last work (see note_stream)
+    hipEvent_t thread_ev = nullptr;         // after it, if that is a thread's own stream
     // queries that use the set's scratch arrays (pset_get, pset_status) take turns
     std::mutex scratch_mu;
 };
@@ -109,7 +110,8 @@ void lp_pool_purge(void);
 // A field set comes (+1) or goes (-1): with the last one the kept blocks are given back.
 void lp_pool_user(int change);
 // Device arrays (16-byte aligned) into host arrays, in stream order after what is queued;
-// returns once they are there.
+// returns once they are there.  Several host threads launch on `stream`, so it is not
+// hipStreamPerThread.
 struct lp_readback {
     void *dst;
     const void *src;

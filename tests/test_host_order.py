@@ -1,5 +1,5 @@
 """The order of the library's runtime calls, on a stand-in for the HIP runtime (no GPU):
-what has to wait for what when record arrays grow."""
+what has to wait for what when record arrays grow, and when results come back."""
 
 import pytest
 
@@ -46,6 +46,57 @@ def grow(fake, behave):
             (c.op == "streamsync" and c.stream == 0)]
     launch = next(i for i, c in enumerate(log) if c.op == "launch" and i > copies[0])
     assert any(copies[-1] < i < launch for i in ends), log
+
+
+@pytest.mark.parametrize("stream", ["2", "0x770", "0"])
+@pytest.mark.parametrize("where", ["here", "elsewhere"])
+@pytest.mark.parametrize("n", ["1000", "700000"])
+def test_results_wait_for_the_run(so, stream, where, n):
+    host_only.run(so, __file__, "results", stream, where, n)
+
+
+def results(fake, stream, where, n):
+    """What a query launches comes after the run it reads, in the thread that ran it or in
+    another and in the query's own helper threads: on the run's stream, or on one that
+    waits for an event of it.  Stream 2 is the calling thread's own (hipStreamPerThread):
+    the same number is another stream in every thread."""
+    import threading
+
+    import numpy as np
+
+    from paper_1707_05163_amd import FieldSet, ParticleSet
+    stream, n = int(stream, 0), int(n)
+    x = np.arange(11) * 1000.0
+    fs = FieldSet(x, x, capacity=1)
+    z = np.zeros((11, 11), np.float32)
+    fs.push_snapshot(0.0, z, z, stream=0)
+    p = np.full(n, 5000.0)
+    ps = ParticleSet(fs, p, p)
+    for ask in (ps.get, ps.status, ps.behaviour, ps.records, ps.step_exponents):
+        fake.fake_clear()
+        ps.execute(600.0, 60.0, 600.0, output_stride=1, maxage=1e9, stream=stream)
+        run = host_only.calls(fake)
+        key = lambda c: (c.stream, c.tid if c.stream == 2 else 0)  # noqa: E731
+        done = [key(c) for c in run if c.op == "launch"][-1]
+        marks = {c.a for c in run[[c.op for c in run].index("launch"):]
+                 if c.op == "eventrecord" and key(c) == done}
+        if where == "here":
+            ask()
+        else:
+            t = threading.Thread(target=ask)
+            t.start()
+            t.join()
+        after = {done}  # streams whose work comes after the run
+        seen = 0
+        for c in host_only.calls(fake)[len(run):]:
+            if c.op == "waitevent" and c.a in marks:
+                after.add(key(c))
+            elif c.op in ("launch", "memcpyasync"):
+                assert key(c) in after, (ask.__name__, c, done)
+                seen += 1
+            elif c.op == "memcpy":
+                assert False, c
+        assert seen
 
 
 if __name__ == "__main__":
