@@ -1857,7 +1857,7 @@ extern "C" int pset_status(lp_pset *ps, lp_counts *c, uint8_t *status)
     if (!ps || !c)
         return fail(LP_EINVAL, "null argument");
     const DeviceGuard dev(ps->device);
-    const std::lock_guard<std::mutex> lock(ps->scratch_mu);
+    const std::lock_guard<std::mutex> lock(ps->stat_mu);
     hipStream_t s;
     if (int rc = query_stream(ps, &s))
         return rc;
@@ -1917,8 +1917,7 @@ extern "C" int pset_get(lp_pset *ps, double *lon, double *lat, double *depth, in
     if (!ps)
         return fail(LP_EINVAL, "null argument");
     const DeviceGuard dev(ps->device);
-    const std::lock_guard<std::mutex> lock(ps->scratch_mu);
-    const size_t N = (size_t)ps->n;
+    const size_t N = (size_t)ps->n, pad = (N + 3) & ~(size_t)3;
     hipStream_t s;
     if (int rc = query_stream(ps, &s))
         return rc;
@@ -1927,36 +1926,41 @@ extern "C" int pset_get(lp_pset *ps, double *lon, double *lat, double *depth, in
         HIPCHECK(hipStreamSynchronize(s));
         return LP_OK;
     }
-    // the cells into the sort's keys and the order list that is not in use, both scratch
-    // between executes; the depth index, the third, in a round of its own
-    lp::RecordParams R{};
-    R.g = ps->fs->g;
-    R.x = ps->dx;
-    R.y = ps->dy;
-    R.z = ps->dz;
-    R.status = ps->dst;
-    R.n = ps->n;
-    R.stride = 1;
-    R.nper = ps->n;
-    int32_t *ki = (int32_t *)ps->dkeys, *kj = (int32_t *)ps->dorder[1 - ps->cur];
-    if (ci || cj) {
-        R.ci = ci ? ki : nullptr;
-        R.cj = cj ? kj : nullptr;
-        HIPCHECK(lp::launch_record(R, s));
+    // the cells into a block of the query's own: the set's arrays are those of the sorts
+    // and launches that another thread may be queueing
+    int32_t *cells = nullptr, *kj = nullptr, *kk = nullptr;
+    hipError_t e = hipSuccess;
+    if (ci || cj || ck) {
+        if (int rc = palloc(&cells, 3 * pad))
+            return rc;
+        kj = cells + pad;
+        kk = kj + pad;
+        lp::RecordParams R{};
+        R.g = ps->fs->g;
+        R.x = ps->dx;
+        R.y = ps->dy;
+        R.z = ps->dz;
+        R.status = ps->dst;
+        R.n = ps->n;
+        R.stride = 1;
+        R.nper = ps->n;
+        R.ci = cells;
+        R.cj = kj;
+        R.ck = kk;
+        e = lp::launch_record(R, s);
     }
-    const lp_readback seg[5] = {{lon, ps->dx, lon ? N * 8 : 0},
+    const lp_readback seg[6] = {{lon, ps->dx, lon ? N * 8 : 0},
                                 {lat, ps->dy, lat ? N * 8 : 0},
                                 {depth, ps->dz, z ? N * 8 : 0},
-                                {ci, ki, ci ? N * 4 : 0},
-                                {cj, kj, cj ? N * 4 : 0}};
-    HIPCHECK(lp_read_back(ps->device, s, seg, 5));
-    if (ck) {
-        R.ci = R.cj = nullptr;
-        R.ck = ki;
-        HIPCHECK(lp::launch_record(R, s));
-        const lp_readback k = {ck, ki, N * 4};
-        HIPCHECK(lp_read_back(ps->device, s, &k, 1));
-    }
+                                {ci, cells, ci ? N * 4 : 0},
+                                {cj, kj, cj ? N * 4 : 0},
+                                {ck, kk, ck ? N * 4 : 0}};
+    if (e == hipSuccess)
+        e = lp_read_back(ps->device, s, seg, 6);
+    if (e != hipSuccess)
+        (void)hipStreamSynchronize(s);
+    pfree(cells);
+    HIPCHECK(e);
     return LP_OK;
 }
 

@@ -94,8 +94,7 @@ struct lp_pset {
     int segs_since_sort = 1 << 30;
     hipStream_t last_stream = nullptr;      // of the set's last work (see note_stream)
     hipEvent_t thread_ev = nullptr;         // after it, if that is a thread's own stream
-    // queries that use the set's scratch arrays (pset_get, pset_status) take turns
-    std::mutex scratch_mu;
+    std::mutex stat_mu;                     // one pset_status at a time (dstat)
 };
 
 

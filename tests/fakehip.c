@@ -1,5 +1,5 @@
 /* A host-only stand-in for the HIP runtime calls that the library makes: device memory is
- * host memory, kernels do nothing, and every call is written to a log.  Tests load it
+ * host memory, kernels do nothing (but results are copied), and every call is written to a log.  Tests load it
  * before the library to look at the order of the library's calls and at what it does when
  * memory runs out, without a GPU. */
 #define _GNU_SOURCE
@@ -146,6 +146,12 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int b, s
 }
 
 /* kernels */
+typedef struct { /* ToHost of results.hip */
+    const char *src[10];
+    uint32_t off[10], bytes[10];
+    int32_t n;
+    char *dst;
+} to_host;
 static __thread struct { dim3_t g, b; size_t l; void *s; } cfg_;
 int __hipPushCallConfiguration(dim3_t g, dim3_t b, size_t l, void *s)
 {
@@ -165,12 +171,19 @@ int __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *l, void **s)
 }
 int hipLaunchKernel(const void *f, dim3_t g, dim3_t b, void **args, size_t l, void *s)
 {
-    (void)g; (void)b; (void)args; (void)l;
+    (void)g; (void)b; (void)l;
     const char *name = "?";
     for (int i = 0; i < nfn_; ++i)
         if (fn_[i] == f)
             name = fname_[i];
     put("launch", name, s, f, NULL, 0);
+    if (strstr(name, "k_to_host")) {  /* the copies to pinned memory are done */
+        const to_host *h = args[0];
+        for (int i = 0; i < h->n; ++i) {
+            put("copyout", NULL, s, h->dst + h->off[i], h->src[i], h->bytes[i]);
+            memcpy(h->dst + h->off[i], h->src[i], h->bytes[i]);
+        }
+    }
     return 0;
 }
 static void *module_;

@@ -1,5 +1,6 @@
 """The order of the library's runtime calls, on a stand-in for the HIP runtime (no GPU):
-what has to wait for what when record arrays grow, and when results come back."""
+what has to wait for what when record arrays grow and when results come back, and what
+memory a query writes."""
 
 import pytest
 
@@ -97,6 +98,35 @@ def results(fake, stream, where, n):
             elif c.op == "memcpy":
                 assert False, c
         assert seen
+
+
+@pytest.mark.parametrize("n", ["1000", "700000"])
+def test_a_query_writes_no_array_of_the_set(so, n):
+    host_only.run(so, __file__, "scratch", n)
+
+
+def scratch(fake, n):
+    """The cell indices that a query computes are in memory of its own: another thread may
+    be queueing sorts and launches of the set meanwhile, which use every array it has."""
+    import numpy as np
+
+    from paper_1707_05163_amd import FieldSet, ParticleSet
+    n = int(n)
+    x = np.arange(11) * 1000.0
+    fs = FieldSet(x, x, np.arange(3.0), capacity=1)
+    z = np.zeros((3, 11, 11), np.float32)
+    fs.push_snapshot(0.0, z, z, z, stream=0)
+    fake.fake_clear()
+    lon = np.arange(n) * 1e-3
+    ps = ParticleSet(fs, lon, lon, lon)
+    ps.execute(600.0, 60.0, stream=0)
+    blocks = [(c.a, c.a + c.bytes) for c in host_only.calls(fake) if c.op == "malloc"]
+    fake.fake_clear()
+    got = ps.get()
+    assert np.array_equal(got["lon"], lon) and np.array_equal(got["depth"], lon)
+    out = [c for c in host_only.calls(fake) if c.op == "copyout"]
+    mine = sum(c.bytes for c in out if any(a <= c.b < b for a, b in blocks))
+    assert mine == 24 * n and sum(c.bytes for c in out) == 36 * n
 
 
 if __name__ == "__main__":
