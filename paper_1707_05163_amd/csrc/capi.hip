@@ -57,18 +57,10 @@ int dalloc(T **p, size_t count)
     *p = nullptr;
     if (count == 0)
         return LP_OK;
-    hipError_t e = hipMalloc((void **)p, count * sizeof(T));
-    if (e == hipErrorOutOfMemory) {  // without the blocks kept for later, it may fit
-        (void)hipGetLastError();
-        lp_pool_purge();
-        e = hipMalloc((void **)p, count * sizeof(T));
-    }
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
+    const hipError_t e = lp_malloc((void **)p, count * sizeof(T), false);
+    if (e != hipSuccess)
         return fail(LP_ENOMEM, "hipMalloc of %zu bytes failed: %s", count * sizeof(T),
                     hipGetErrorString(e));
-    }
     return LP_OK;
 }
 
@@ -377,11 +369,8 @@ int upload_from_host(lp_fieldset *fs, const void *const *src, int nvar, size_t b
 {
     if (!fs->hpin) {
         const size_t chunk = std::min(kPinChunk, (bytes + 4095) & ~(size_t)4095);
-        if (hipHostMalloc((void **)&fs->hpin, 2 * chunk, hipHostMallocDefault) != hipSuccess) {
-            fs->hpin = nullptr;
-            (void)hipGetLastError();
+        if (lp_malloc((void **)&fs->hpin, 2 * chunk, true) != hipSuccess)
             return fail(LP_ENOMEM, "pinned staging of %zu bytes failed", 2 * chunk);
-        }
         fs->pin_chunk = chunk;
         for (auto &e : fs->pin_ev)
             if (!e)
@@ -1404,10 +1393,8 @@ int batch_reserve(size_t nruns)
     int rc;
     if ((rc = dalloc(&b.druns, nruns)) || (rc = dalloc(&b.dcstart, nruns + 1)))
         return rc;
-    if (hipHostMalloc((void **)&b.hruns, nruns * sizeof(lp::AdvectParams), hipHostMallocDefault) !=
-            hipSuccess ||
-        hipHostMalloc((void **)&b.hcstart, (nruns + 1) * sizeof(uint32_t), hipHostMallocDefault) !=
-            hipSuccess)
+    if (lp_malloc((void **)&b.hruns, nruns * sizeof(lp::AdvectParams), true) != hipSuccess ||
+        lp_malloc((void **)&b.hcstart, (nruns + 1) * sizeof(uint32_t), true) != hipSuccess)
         return fail(LP_ENOMEM, "pinned allocation of batch descriptors failed");
     b.cap_runs = nruns;
     return LP_OK;

@@ -106,6 +106,8 @@ void lp_set_error(const char *msg);
 void *lp_pool_alloc(size_t bytes, bool host, hipError_t *err);
 void lp_pool_free(void *p);
 void lp_pool_purge(void);
+// A plain allocation, tried again without the kept blocks if there is no room.
+hipError_t lp_malloc(void **p, size_t bytes, bool host);
 // A field set comes (+1) or goes (-1): with the last one the kept blocks are given back.
 void lp_pool_user(int change);
 // Device arrays (16-byte aligned) into host arrays, in stream order after what is queued;

@@ -24,7 +24,7 @@ namespace {
 // the runs of an ensemble), and a hipMalloc and hipFree pair costs 13 us at 8 MB and 320 us
 // at 80 MB.  Freed blocks stay in lists by device and kind, at most kKeepDevice and
 // kKeepHost bytes of them, while any field set lives; they are given back when the last one
-// is destroyed, and when an allocation fails.  A block is freed only when no work on it is
+// is destroyed, and when an allocation of the library fails.  A block is freed only when no work on it is
 // pending, so the next owner may use it on any stream.  One lock guards it all.
 constexpr size_t kKeepDevice = (size_t)1 << 30, kKeepHost = (size_t)64 << 20;
 
@@ -135,6 +135,22 @@ void lp_pool_purge(void)
     Pool &P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
     purge_locked(P);
+}
+
+hipError_t lp_malloc(void **p, size_t bytes, bool host)
+{
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 2; ++k) {
+        *p = nullptr;
+        e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+        if (e == hipSuccess)
+            return e;
+        (void)hipGetLastError();
+        if (k == 0)
+            lp_pool_purge();
+    }
+    *p = nullptr;
+    return e;
 }
 
 void lp_pool_user(int change)

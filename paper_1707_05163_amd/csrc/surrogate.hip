@@ -48,7 +48,7 @@ template <class T>
 hipError_t dmalloc(T **p, size_t n)
 {
     *p = nullptr;
-    return n ? hipMalloc((void **)p, n * sizeof(T)) : hipSuccess;
+    return n ? lp_malloc((void **)p, n * sizeof(T), false) : hipSuccess;
 }
 
 template <class T>

@@ -1,6 +1,6 @@
 """The order of the library's runtime calls, on a stand-in for the HIP runtime (no GPU):
-what has to wait for what when record arrays grow and when results come back, and what
-memory a query writes."""
+what has to wait for what when record arrays grow and when results come back, what
+memory a query writes, and what gives way when memory runs out."""
 
 import pytest
 
@@ -127,6 +127,52 @@ def scratch(fake, n):
     out = [c for c in host_only.calls(fake) if c.op == "copyout"]
     mine = sum(c.bytes for c in out if any(a <= c.b < b for a, b in blocks))
     assert mine == 24 * n and sum(c.bytes for c in out) == 36 * n
+
+
+@pytest.mark.parametrize("what", ["push", "push_device", "batch", "forward", "train_step",
+                                  "gradients", "features", "surrogate", "set", "records"])
+def test_kept_blocks_give_way(so, what):
+    host_only.run(so, __file__, "full", what)
+
+
+def full(fake, what):
+    """With no memory left but the blocks kept from a closed set, every call that needs
+    some gets it; without those it says that there is none."""
+    import numpy as np
+
+    import paper_1707_05163_amd as lp
+    from paper_1707_05163_amd import _lib
+    from paper_1707_05163_amd.core import surrogate_features
+    x = np.arange(11) * 1000.0
+    u = np.zeros((11, 11), np.float32)
+    fs = lp.FieldSet(x, x, capacity=2)
+    if what != "push":
+        fs.push_snapshot(0.0, u, u, stream=0)
+    p = np.full(2000, 5000.0)
+    small = lp.ParticleSet(fs, p, p)
+    net = lp.Surrogate()
+    X, T = np.zeros((256, 64), np.float32), np.zeros((256, 2), np.float32)
+    tracer = np.zeros((11, 11), np.float32)
+    call = {"push": lambda: fs.push_snapshot(0.0, u, u, stream=0),
+            "push_device": lambda: fs.push_tracer(0.0, tracer, stream=0),
+            "batch": lambda: lp.execute_batch([small], 600.0, 60.0, stream=0),
+            "forward": lambda: net.forward(X), "train_step": lambda: net.train_step(X, T, 1e-3),
+            "gradients": lambda: net.gradients(X, T),
+            "features": lambda: surrogate_features(fs, p, p, 0.0),
+            "surrogate": lambda: lp.Surrogate(1), "set": lambda: lp.ParticleSet(fs, p, p),
+            "records": lambda: small.execute(600.0, 60.0, output_stride=1, stream=0)}[what]
+    big = np.full(300_000, 5000.0)
+    before = fake.fake_in_use()
+    lp.ParticleSet(fs, big, big).close()
+    kept = fake.fake_in_use() - before
+    assert kept > 300_000 * 40, "the closed set's blocks are not kept"
+    fake.fake_limit(fake.fake_in_use())
+    call()
+    fake.fake_limit(fake.fake_in_use())
+    with pytest.raises(_lib.LPError) as e:
+        lp.ParticleSet(fs, big, big)
+    assert e.value.code == _lib.LP_ENOMEM
+
 
 
 if __name__ == "__main__":
