@@ -334,12 +334,14 @@ __device__ inline LatRow lat_row(const GridDev &g, int j, double y0)
 }
 
 // A sample's velocity in coordinate units per second (degrees on the sphere), and the
-// metric M cos(lat) that it divided by (1 on a flat mesh).  With FP64 values the cosine
-// comes from the cell's latitude tables, as in the cached kernels: the library cosine and
-// the two divisions were more than half of a gather's instructions (adaptive RKF45 on
-// the 0.25 degree field, 1M particles: 1.63 ms a launch).  Grids without tables (cells
-// taller than 5 degrees) take the library cosine.
-template <int ST>
+// metric M cos(lat) that it divided by (1 on a flat mesh).  The adaptive lanes (ADAPT) take
+// the cosine of FP64 values from the cell's latitude tables, as the cached kernels do, and
+// its reciprocal from recip (RKF45 on 1M particles of the 0.25 degree field 1.14 ms a
+// launch in place of 1.24); grids without tables (cells taller than 5 degrees) the library's.
+// The RK4 gathers are bound by their reads, and the two of the tables cost them more than
+// the library's cosine and division: 288 steps of 1M particles 8.65 ms for FP32 fields and
+// 12.7 for FP64 (8.78 and 13.7 with tables), in 3D 4.23 and 7.53 for 48 steps (4.35, 7.70).
+template <int ST, bool ADAPT>
 __device__ inline bool sample_finish(const AdvectParams &P, double y, const LatRow &lr,
                                      const typename Real<ST>::T v[3], double k[3], double &m)
 {
@@ -347,12 +349,17 @@ __device__ inline bool sample_finish(const AdvectParams &P, double y, const LatR
     m = 1.0;
     if (P.g.spherical) {
         if constexpr (sizeof(R) == 8) {
-            if (P.g.coslat)
+            if (ADAPT && P.g.coslat)
                 m = kMetresPerDegree * cos_series(lr.cl, lr.sl, lr.y0, y, P.g.cos_terms);
             else
                 m = kMetresPerDegree * cos(y * kDegToRad);
-            k[0] = v[0] * recip(m);
-            k[1] = v[1] * (1.0 / kMetresPerDegree);
+            if constexpr (ADAPT) {
+                k[0] = v[0] * recip(m);
+                k[1] = v[1] * (1.0 / kMetresPerDegree);
+            } else {
+                k[0] = v[0] / m;
+                k[1] = v[1] / kMetresPerDegree;
+            }
         } else {
             const float cl = cosf((float)(y * kDegToRad));
             k[0] = (double)(v[0] / ((float)kMetresPerDegree * cl));
@@ -436,11 +443,12 @@ __device__ inline bool gather2(const AdvectParams &P, const TimeEntry &te, doubl
     return true;
 }
 
-// Velocity at a stage point in coordinate units per second; false if outside.  SPEC
+// Velocity at a stage point in coordinate units per second; false if outside.  ADAPT: for
+// an adaptive lane (see sample_finish).  SPEC
 // reads the corners of the guessed cell together with its faces (2D only): the RKF45
 // lane on FP32 fields gains 4% from it; in the RK4 gather kernels the registers it
 // holds cost as much as it saves, and the other storage forms of the RKF45 lane spill.
-template <int ST, bool IS3D, bool STEADY, bool SPEC = false>
+template <int ST, bool IS3D, bool STEADY, bool ADAPT = false, bool SPEC = false>
 __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double x, double y,
                               double z, double k[3], double &m)
 {
@@ -461,12 +469,13 @@ __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double
             for (int q = 0; q < 3; ++q)
                 v[q] = ((R)1 - tau) * a[q] + tau * b[q];
         }
-        return sample_finish<ST>(P, y, lr, v, k, m);
+        return sample_finish<ST, ADAPT>(P, y, lr, v, k, m);
     }
     Cell c;
     if (!locate_point<IS3D, true>(P.g, x, y, z, c))
         return false;
-    lr = lat_row(P.g, c.j, c.y0);
+    if constexpr (ADAPT)
+        lr = lat_row(P.g, c.j, c.y0);
     if (P.nearest) {
         c.xi = c.xi < 0.5 ? 0.0 : 1.0;
         c.eta = c.eta < 0.5 ? 0.0 : 1.0;
@@ -483,7 +492,7 @@ __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double
         for (int q = 0; q < 3; ++q)
             v[q] = ((R)1 - tau) * a[q] + tau * b[q];
     }
-    return sample_finish<ST>(P, y, lr, v, k, m);
+    return sample_finish<ST, ADAPT>(P, y, lr, v, k, m);
 }
 
 // Philox4x32-10 (Salmon et al., SC'11): ten Philox-4x32 rounds, key bumped by the
@@ -956,7 +965,7 @@ __device__ inline bool rkf45_attempt(const AdvectParams &P, double t, double h,
         }
         const TimeEntry te = bracket_lane(P, t + Fehlberg::c[i] * h, lt);
         double m = 1.0;
-        ok = sample<ST, IS3D, STEADY, ST == kF32>(P, te, q[0], q[1], q[2], k[i], m) & ok;
+        ok = sample<ST, IS3D, STEADY, true, ST == kF32>(P, te, q[0], q[1], q[2], k[i], m) & ok;
         if (i == 0)
             m0 = m;  // the metric at the step's start, for the error's length
     }
