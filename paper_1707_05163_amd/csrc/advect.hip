@@ -322,6 +322,16 @@ __device__ inline double recip(double d)
     return r;
 }
 
+// n / d to within an ulp: by a reciprocal refined by one Newton step, and one correction
+// by the remainder (as many operations as recip and a product).
+__device__ inline double quotient(double n, double d)
+{
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    const double q = n * r;
+    return fma(fma(-d, q, n), r, q);
+}
+
 // The latitude row that a gather's metric starts from: its lower face, and the tables'
 // cosine and sine there (read with the stencil; zero without tables).
 struct LatRow {
@@ -1370,21 +1380,35 @@ __device__ inline double recip_stage(double d)
     return fma(fma(-d, r, 1.0), r, r);
 }
 
-// 1 / (M cos(lat)) at a stage point inside the cached cell, at offset t from its lower
-// latitude face, for the slope of an RK4 stage: the polynomial in cells of at most 0.3
+// metric_at with the sine's fifth power too, for its full precision in any cell of at most
+// 0.3 degrees.
+__device__ inline double metric_at5(const double m[5], double t)
+{
+    constexpr double k2 = kDegToRad * kDegToRad;
+    const double m4 = fma(m[1], (k2 * k2 / 120.0) * t, m[4]);
+    return fma(fma(fma(fma(m4, t, m[3]), t, m[2]), t, m[1]), t, m[0]);
+}
+
+// u over M cos(lat) at a stage point inside the cached cell, at offset t from its lower
+// latitude face, the slope of an RK4 stage: the polynomial in cells of at most 0.3
 // degrees, else the cell's series (or the library cosine), then one Newton step on the
-// hardware reciprocal.
-template <int MET, class CellT>
-__device__ inline double stage_metric(const CellT &c, const AdvectParams &P, double t, double y)
+// hardware reciprocal.  FULL (the 2D runs with an age or a tracer sample, which took the
+// library's cosine and a division in the gather kernel): the polynomial in full and the
+// quotient to within an ulp, rms error of a slope below 80 degrees on 0.25 degree cells
+// 1.4e-16 (7.0e-15 without, 1.4e-16 in the gather), above 2.7e-15 (1.8e-13, 4.0e-15), for
+// 7% of a sampled run's time (400k particles, 288 steps: 1.20 ms, 1.13 without).
+template <int MET, bool FULL, class CellT>
+__device__ inline double east_slope(const CellT &c, const AdvectParams &P, double u, double t,
+                                    double y)
 {
     double m;
     if constexpr (MET == kSphLib)
         m = kMetresPerDegree * cos(y * kDegToRad);
     else if constexpr (MET == kSphTable2)
-        m = metric_at(c.m, t);
+        m = FULL ? metric_at5(c.m, t) : metric_at(c.m, t);
     else
         m = cos_series(c.m[0], c.m[1], 0.0, t, P.g.cos_terms);
-    return recip_stage(m);
+    return FULL ? quotient(u, m) : u * recip_stage(m);
 }
 
 // 1 / (M cos(lat)) at the end point of a step at offset t, for the metric of the Brownian
@@ -1397,8 +1421,7 @@ __device__ inline double inv_metres_lon(const CellT &c, const AdvectParams &P, d
         if (high_word(t) < c.wy) {
             if constexpr (MET == kSphTable)
                 return recip(cos_series(c.m[0], c.m[1], 0.0, t, P.g.cos_terms));
-            const double m3 = c.m[3] * fma(t * t, -kDegToRad * kDegToRad / 20.0, 1.0);
-            return recip(fma(fma(fma(fma(c.m[4], t, m3), t, c.m[2]), t, c.m[1]), t, c.m[0]));
+            return recip(metric_at5(c.m, t));
         }
     }
     return recip(kMetresPerDegree * cos_deg(y));
@@ -1442,12 +1465,12 @@ __device__ inline R poly_arg(double t, double r)
 }
 
 // U, V at offsets (tx, ty) as slopes in coordinate units per second.
-template <int MET, class R, int NL>
+template <int MET, bool FULL, class R, int NL>
 __device__ inline void slopes(const Cell2<R, NL> &c, const AdvectParams &P, R u, R v, double ty,
                               double y, double &kx, double &ky)
 {
     if constexpr (MET != kFlat) {
-        kx = (double)u * stage_metric<MET>(c, P, ty, y);
+        kx = east_slope<MET, FULL>(c, P, (double)u, ty, y);
         ky = v_in_degrees<R, MET>() ? (double)v : (double)v * (1.0 / kMetresPerDegree);
     } else {
         kx = (double)u;
@@ -1470,7 +1493,7 @@ __device__ inline bool stage2(const AdvectParams &P, Cell2<typename Real<ST>::T,
     }
     R u, v;
     values_at<STEADY>(c, e.tau, poly_arg<R>(tx, c.rx), poly_arg<R>(ty, c.ry), u, v);
-    slopes<MET>(c, P, u, v, ty, y, kx, ky);
+    slopes<MET, false>(c, P, u, v, ty, y, kx, ky);
     return true;
 }
 
@@ -1503,7 +1526,7 @@ struct StepTimes {
 // doubled (h is then half of theirs).  With coefficients in registers (NL = 0) or a steady
 // field nothing of that: tc serves every stage.  A point off the grid leaves the cell as
 // it was and returns false.
-template <int ST, bool STEADY, int MET, int NL, int Q>
+template <int ST, bool STEADY, int MET, int NL, int Q, bool FULL>
 __device__ inline bool stage2_rk4(const AdvectParams &P, Cell2<typename Real<ST>::T, NL> &c,
                                   const StepTimes &t, bool fresh, double x, double y, double h,
                                   double &bx, double &by, typename Real<ST>::T tc[8],
@@ -1561,7 +1584,7 @@ __device__ inline bool stage2_rk4(const AdvectParams &P, Cell2<typename Real<ST>
         u = poly<R>(te + 0, xi, eta);
         v = poly<R>(te + 4, xi, eta);
     }
-    slopes<MET>(c, P, u, v, ty, Q ? fma(ky, h, y) : y, kx, ky);
+    slopes<MET, FULL>(c, P, u, v, ty, Q ? fma(ky, h, y) : y, kx, ky);
     return ok;
 }
 
@@ -1672,8 +1695,8 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                 double kx = 0.0, ky = 0.0, sx, sy;
                 bx = x - c.x0;
                 by = y - c.y0;
-                bool ok = stage2_rk4<ST, STEADY, MET, NL, 0>(P, c, t, moves.at(0), x, y, 0.0, bx,
-                                                             by, tc, tm, te, kx, ky);
+                bool ok = stage2_rk4<ST, STEADY, MET, NL, 0, BEHAVE>(
+                    P, c, t, moves.at(0), x, y, 0.0, bx, by, tc, tm, te, kx, ky);
                 sx = kx;
                 sy = ky;
                 if constexpr (BEHAVE) {
@@ -1682,18 +1705,18 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                                                              by * c.ry, 0.0);
                 }
                 if (!P.scheme) {  // (Euler forward has one stage)
-                    ok = stage2_rk4<ST, STEADY, MET, NL, 1>(P, c, t, moves.at(1), x, y, P.hdt, bx,
-                                                            by, tc, tm, te, kx, ky) & ok;
+                    ok = stage2_rk4<ST, STEADY, MET, NL, 1, BEHAVE>(
+                             P, c, t, moves.at(1), x, y, P.hdt, bx, by, tc, tm, te, kx, ky) & ok;
                     sx = TWICE ? sx + kx : fma(2.0, kx, sx);
                     sy = TWICE ? sy + ky : fma(2.0, ky, sy);
-                    ok = stage2_rk4<ST, STEADY, MET, NL, 2>(P, c, t, moves.at(2), x, y,
-                                                            TWICE ? P.qdt : P.hdt, bx, by, tc, tm,
-                                                            te, kx, ky) & ok;
+                    ok = stage2_rk4<ST, STEADY, MET, NL, 2, BEHAVE>(
+                             P, c, t, moves.at(2), x, y, TWICE ? P.qdt : P.hdt, bx, by, tc, tm, te,
+                             kx, ky) & ok;
                     sx = TWICE ? sx + kx : fma(2.0, kx, sx);
                     sy = TWICE ? sy + ky : fma(2.0, ky, sy);
-                    ok = stage2_rk4<ST, STEADY, MET, NL, 3>(P, c, t, moves.at(3), x, y,
-                                                            TWICE ? P.hdt : dt, bx, by, tc, tm,
-                                                            te, kx, ky) & ok;
+                    ok = stage2_rk4<ST, STEADY, MET, NL, 3, BEHAVE>(
+                             P, c, t, moves.at(3), x, y, TWICE ? P.hdt : dt, bx, by, tc, tm, te,
+                             kx, ky) & ok;
                     if constexpr (TWICE) {
 #pragma unroll
                         for (int i = 0; i < 8; ++i)
@@ -2328,8 +2351,8 @@ __device__ inline bool stage3(const AdvectParams &P, Cell3<typename Real<ST>::T,
         }
     }
     if constexpr (MET != kFlat) {
-        k[0] = (double)v[0] *
-               stage_metric<MET>(c, P, ty, MET == kSphLib ? fma(k[1], h, y) : 0.0);
+        k[0] = east_slope<MET, false>(c, P, (double)v[0], ty,
+                                      MET == kSphLib ? fma(k[1], h, y) : 0.0);
         k[1] = (double)v[1] * (1.0 / kMetresPerDegree);
     } else {
         k[0] = (double)v[0];

@@ -1,7 +1,8 @@
 """The eastward metric of single Euler steps from the meridian 0 in a uniform eastward
 flow, where the step itself is the position: against dt U / (M cos(lat)) in extended
-precision, from the equator to a tenth of a degree from the poles, in the RK4
-gathers, which take the library's cosine and a division.
+precision, from the equator to a tenth of a degree from the poles, in the kernels that
+took the library's cosine and a division from the first (the gathers, and the 2D runs
+with an age, which run from the cached cell).
 
 The cosine's argument is rounded (and the constant pi / 180 with it) to 2^-52 of up to
 pi/2 radians, once for the point or for its row; the cosine, the row's sine and the series
@@ -15,7 +16,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("kind", ["gather"])
+@pytest.mark.parametrize("kind", ["gather", "age", "steady age"])
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("deg", [0.25, 1.0, 4.0, 10.0])
 def test_step_along_a_parallel(deg, dtype, kind):
