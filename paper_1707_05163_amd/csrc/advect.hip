@@ -1519,6 +1519,15 @@ struct StepTimes {
     }
 };
 
+// FP32 coefficients at the middle are always formed by themselves: the sum of two rounded
+// ones rounds once more, which put the rms error of a day's run on BF16 or scaled FP16
+// fields up by 4 to 8% (2.07e-8 km in place of 1.93).  Nor did it save time: 1M particles,
+// 288 steps, BF16 1.55 ms on the sphere and 1.39 flat (1.71 and 1.60 with the mean), scaled
+// FP16 1.68 and 1.55 (1.65 and 1.64).  With FP64 ones the positions' rounding is far above
+// either, and the mean is worth 8 of a stage's products.
+template <class R>
+constexpr bool mean_coefs() { return sizeof(R) == 8; }
+
 // One stage of the cached RK4 lane, Q = 0 .. 3, for the step that starts at (x, y), at
 // offsets (bx, by) from the cell's lower faces: slope (kx, ky) in, the previous stage's,
 // and out.  tc, tm, te: the coefficients (U in [0..3], V in [4..7]) at the step's start,
@@ -1565,10 +1574,11 @@ __device__ inline bool stage2_rk4(const AdvectParams &P, Cell2<typename Real<ST>
         v = poly<R>(tc + 4, xi, eta);
     } else if constexpr (Q < 3) {
         const R tau = (R)e.tau, te1 = (R)t.tau_end;
+        const bool mean = mean_coefs<R>() && t.mean;
         if (Q == 1 || moved) {
-            if (t.mean)
+            if (mean)
                 coefs_at<false>(c, (R)1 - te1, te1, te);
-            if (moved | !t.mean) {
+            if (moved | !mean) {
                 coefs_at<false>(c, (R)2 * ((R)1 - tau), (R)2 * tau, tm);
             } else {
 #pragma unroll
@@ -1579,7 +1589,7 @@ __device__ inline bool stage2_rk4(const AdvectParams &P, Cell2<typename Real<ST>
         u = poly<R>(tm + 0, xi, eta);
         v = poly<R>(tm + 4, xi, eta);
     } else {
-        if (moved | !t.mean)
+        if (moved | !(mean_coefs<R>() && t.mean))
             coefs_at<false>(c, (R)1 - (R)e.tau, (R)e.tau, te);
         u = poly<R>(te + 0, xi, eta);
         v = poly<R>(te + 4, xi, eta);
