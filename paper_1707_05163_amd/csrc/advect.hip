@@ -1524,7 +1524,7 @@ struct StepTimes {
 // fields up by 4 to 8% (2.07e-8 km in place of 1.93).  Nor did it save time: 1M particles,
 // 288 steps, BF16 1.55 ms on the sphere and 1.39 flat (1.71 and 1.60 with the mean), scaled
 // FP16 1.68 and 1.55 (1.65 and 1.64).  With FP64 ones the positions' rounding is far above
-// either, and the mean is worth 8 of a stage's products.
+// either, and the mean saves a step 8 products.
 template <class R>
 constexpr bool mean_coefs() { return sizeof(R) == 8; }
 

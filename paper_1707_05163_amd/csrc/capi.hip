@@ -809,7 +809,7 @@ static int pset_create_common(lp_fieldset *fs, int64_t n, const double *lon, con
         return code;
     };
     ps->fs = fs;
-    ps->device = fs->device;
+    (void)hipGetDevice(&ps->device);  // of its arrays and its launches
     ps->n = n;
     ps->t0 = t0;
     ps->step = step0;

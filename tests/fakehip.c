@@ -14,7 +14,7 @@ typedef struct { uint32_t x, y, z; } dim3_t;
 typedef struct {
     char op[24];
     char name[72];
-    int64_t tid, stream, a, b, bytes;
+    int64_t tid, stream, a, b, bytes, dev;
 } rec;
 
 enum { MAX = 1 << 16, KERNELS = 4096 };
@@ -25,6 +25,8 @@ static pthread_mutex_t mu_ = PTHREAD_MUTEX_INITIALIZER;
 static const void *fn_[KERNELS];
 static const char *fname_[KERNELS];
 static int nfn_;
+
+static __thread int dev_;  /* the thread's current device */
 
 static void put(const char *op, const char *name, const void *stream, const void *a,
                 const void *b, size_t bytes)
@@ -41,6 +43,7 @@ static void put(const char *op, const char *name, const void *stream, const void
         r->a = (int64_t)a;
         r->b = (int64_t)b;
         r->bytes = (int64_t)bytes;
+        r->dev = dev_;
     }
     pthread_mutex_unlock(&mu_);
 }
@@ -133,8 +136,8 @@ int hipEventSynchronize(void *e) { put("eventsync", NULL, NULL, e, NULL, 0); ret
 int hipEventQuery(void *e) { (void)e; return 0; }
 int hipEventElapsedTime(float *ms, void *a, void *b) { (void)a; (void)b; *ms = 1.f; return 0; }
 int hipDeviceSynchronize(void) { put("devicesync", NULL, NULL, NULL, NULL, 0); return 0; }
-int hipGetDevice(int *d) { *d = 0; return 0; }
-int hipSetDevice(int d) { (void)d; return 0; }
+int hipGetDevice(int *d) { *d = dev_; return 0; }
+int hipSetDevice(int d) { dev_ = d; return 0; }
 int hipGetLastError(void) { return 0; }
 const char *hipGetErrorString(int e) { return e == 2 ? "out of memory" : "error"; }
 int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }

@@ -26,13 +26,14 @@ def run(so, script, *args):
 class Rec(C.Structure):
     _fields_ = [("op", C.c_char * 24), ("name", C.c_char * 72), ("tid", C.c_int64),
                 ("stream", C.c_int64), ("a", C.c_int64), ("b", C.c_int64),
-                ("bytes", C.c_int64)]
+                ("bytes", C.c_int64), ("dev", C.c_int64)]
 
 
 class Call:
     def __init__(self, r):
         self.op, self.name = r.op.decode(), r.name.decode()
-        self.tid, self.stream, self.a, self.b, self.bytes = r.tid, r.stream, r.a, r.b, r.bytes
+        self.tid, self.stream, self.dev = r.tid, r.stream, r.dev
+        self.a, self.b, self.bytes = r.a, r.b, r.bytes
 
     def __repr__(self):
         return f"{self.op}({self.name} stream={self.stream:#x} tid={self.tid} {self.bytes})"

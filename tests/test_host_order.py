@@ -175,6 +175,36 @@ def full(fake, what):
 
 
 
+@pytest.mark.parametrize("n", ["1000", "700000"])
+def test_a_set_stays_on_its_device(so, n):
+    host_only.run(so, __file__, "device", n)
+
+
+def device(fake, n):
+    """A set made and run with device 1 current, on a field set of device 0 (as peers read
+    each other's memory): its memory is device 1's, and so is whatever a query or its end
+    does, with any device current."""
+    import numpy as np
+
+    from paper_1707_05163_amd import FieldSet, ParticleSet
+    x = np.arange(11) * 1000.0
+    fs = FieldSet(x, x, capacity=1)
+    z = np.zeros((11, 11), np.float32)
+    fs.push_snapshot(0.0, z, z, stream=0)
+    fake.fake_clear()
+    fake.hipSetDevice(1)
+    p = np.full(int(n), 5000.0)
+    ps = ParticleSet(fs, p, p)
+    ps.execute(600.0, 60.0, 600.0, output_stride=1, maxage=1e9, stream=0x770)
+    for now in (1, 0):
+        fake.hipSetDevice(now)
+        for ask in (ps.get, ps.status, ps.behaviour, ps.records, ps.step_exponents):
+            ask()
+    ps.close()
+    log = host_only.calls(fake)
+    assert {c.dev for c in log if c.op in ("malloc", "launch", "waitevent", "devicesync")} == {1}
+
+
 if __name__ == "__main__":
     import sys
     globals()[sys.argv[2]](host_only.load(sys.argv[1]), *sys.argv[3:])
