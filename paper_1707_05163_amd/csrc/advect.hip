@@ -1117,19 +1117,21 @@ struct GatherLane {
 // A stage works in offsets from the cell's lower faces: the step's start has the offsets
 // b = X - (x0, y0), a stage point's are b + h k (one product), and with FP64 coefficients
 // the inverse cell widths are folded into the coefficients at the reload, so the offsets
-// go straight into the polynomials.  A point is in the cell when the high words of its
-// offsets are below those of the widths, two 32-bit unsigned compares: a negative offset
-// or a NaN has a larger high word, and a point within 2^-20 of the upper face counts as
-// outside, which only sends it through the exact search of the reload.  Against positions
-// in degrees, faces compared in FP64 and fractions formed by a difference and a product
-// this saved 10 of 31 vector instructions a stage.
+// go straight into the polynomials.  A point is in the cell when the bits of its offsets
+// are below those of the widths, two 64-bit unsigned compares: a negative offset or a NaN
+// has larger bits.  The domain's closed upper end is in the last cell, whose width goes to
+// the next double above the last node.  Against positions in degrees, faces compared in
+// FP64 and fractions formed by a difference and a product this saved 10 of 31 vector
+// instructions a stage.  (Compares of the high words alone leave out the last 2^-20 of a
+// cell: a run that stays at a depth just below a level, or at the last one, then reloaded
+// at every stage, five times the time.)
 // NL of the 16 coefficients (the last NL) sit in the lane's LDS slot and the others
 // in registers: LDS frees registers, so more waves fit on a SIMD, at the cost of LDS
 // reads every stage; the split is chosen per kernel mode (cache_lds_coefs).
 template <class R, int NL>
 struct Cell2 {
     double x0, y0;          // lower faces
-    uint32_t wx, wy;        // high words of the cell widths
+    uint64_t wx, wy;        // bits of the cell widths (offset_bound)
     double rx, ry;          // inverse cell widths (FP32 coefficients and the tracer sample)
     double m[5];            // metric: see metric_poly; with the 3/4-term series m[0], m[1] are
                             // M cos and M sin of the lower latitude face
@@ -1225,9 +1227,14 @@ __device__ inline R poly(const R c[4], R xi, R eta)
 template <class R>
 constexpr bool folded() { return sizeof(R) == 8; }
 
-__device__ inline uint32_t high_word(double x)
+__device__ inline uint64_t bits(double x) { return __builtin_bit_cast(uint64_t, x); }
+
+// What the bits of an offset from the lower face of cell i (faces lo and hi) are below for
+// points of the cell.  A point beyond the domain's end has an offset of at least that of
+// the next double above it.
+__device__ inline uint64_t offset_bound(const AxisDev &a, int i, double lo, double hi)
 {
-    return (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32);
+    return bits((i == a.n - 2 ? nextafter(a.hi, __builtin_inf()) : hi) - lo);
 }
 
 // M cos(lat) inside a cell at most 0.3 degrees tall as a polynomial in the offset t from
@@ -1279,8 +1286,8 @@ __device__ inline bool reload2(const AdvectParams &P, Cell2<typename Real<ST>::T
     axis_faces(ay, j, c.y0, yh);
     axis_correct(ax, x, i, c.x0, xh);
     axis_correct(ay, y, j, c.y0, yh);
-    c.wx = high_word(xh - c.x0);
-    c.wy = high_word(yh - c.y0);
+    c.wx = offset_bound(ax, i, c.x0, xh);
+    c.wy = offset_bound(ay, j, c.y0, yh);
     const size_t nx = (size_t)ax.n;
     const size_t n00 = (size_t)j * nx + (size_t)i;
     c.node = (uint32_t)n00;
@@ -1340,7 +1347,7 @@ __device__ inline bool reload2(const AdvectParams &P, Cell2<typename Real<ST>::T
 template <class R, int NL>
 __device__ inline bool in_cell(const Cell2<R, NL> &c, double tx, double ty)
 {
-    return (high_word(tx) < c.wx) & (high_word(ty) < c.wy);
+    return (bits(tx) < c.wx) & (bits(ty) < c.wy);
 }
 
 // Whether two time-table entries interpolate between the same two snapshots.
@@ -1418,7 +1425,7 @@ template <int MET, class CellT>
 __device__ inline double inv_metres_lon(const CellT &c, const AdvectParams &P, double t, double y)
 {
     if constexpr (met_series<MET>()) {
-        if (high_word(t) < c.wy) {
+        if (bits(t) < c.wy) {
             if constexpr (MET == kSphTable)
                 return recip(cos_series(c.m[0], c.m[1], 0.0, t, P.g.cos_terms));
             return recip(metric_at5(c.m, t));
@@ -1666,7 +1673,7 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
             constexpr bool TWICE = NL > 0 && !STEADY;
             R tc[8] = {}, tm[8] = {}, te[8] = {};  // see stage2_rk4
             const double dt = P.dt, dt6 = P.dt6;
-            double bx = 0.0, by = 0.0;
+            double bx = 0.0, by = 0.0;  // the step's start in offsets from the cell
             // The spherical Brownian kernel with the shortest metric keeps the polynomials'
             // later coefficients in vector registers, as values the compiler cannot see
             // through: known constants it copies before each use, 17 moves a step (9.7 ms
@@ -1736,25 +1743,21 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
                 if (!ok)
                     goto fail;
                 {
-                    // the end point, and its offsets in the last stage's cell
                     const double g = P.scheme ? dt : dt6;
                     const double dx = P.scheme ? kx : sx + kx, dy = P.scheme ? ky : sy + ky;
                     double xs = fma(dx, g, x), ys = fma(dy, g, y);
-                    double tx = fma(dx, g, bx), ty = fma(dy, g, by);
                     if (BROWN && P.Kh > 0.0) {
                         double wx, wy;
                         brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, wx, wy, kv);
                         if constexpr (MET != kFlat) {
-                            wx = wx * inv_metres_lon<MET>(c, P, ty, ys);
+                            wx = wx * inv_metres_lon<MET>(c, P, ys - c.y0, ys);
                             wy = wy * (1.0 / kMetresPerDegree);
                         }
                         xs = xs + wx;
                         ys = ys + wy;
-                        tx = xs - c.x0;  // (of the rounded end point: both sides of a face agree)
-                        ty = ys - c.y0;
                     }
-                    bool land;
-                    if (in_cell(c, tx, ty)) {
+                    bool land;  // (by the rounded end point: both sides of a face agree)
+                    if (in_cell(c, xs - c.x0, ys - c.y0)) {
                         land = c.land;
                     } else {
                         const uint8_t e = point_status<false>(P.g, xs, ys, 0.0);
@@ -2091,7 +2094,7 @@ __attribute__((amdgpu_waves_per_eu(BROWN || MET == kSphLib ? 3 : 4))) void k_adv
 template <class R, bool DL>
 struct Cell3 {
     double x0, y0, z0;      // lower faces
-    uint32_t wx, wy, wz;    // high words of the cell widths (in_cell3)
+    uint64_t wx, wy, wz;    // bits of the cell widths (offset_bound)
     double rx, ry, rz;      // inverse cell widths
     double m[5];            // metric, as in Cell2
     R a[3][8];
@@ -2199,7 +2202,7 @@ __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T
     // changes are horizontal), which spares the depth axis's bin-table guess and face
     // reads, the longest chain of the search on a non-uniform axis.  The level sits in
     // the LDS slot, so only the LDS-cached forms keep it.
-    const bool keep_k = DL && high_word(z - c.z0) < c.wz;
+    const bool keep_k = DL && bits(z - c.z0) < c.wz;
     int i = axis_guess(ax, x), j = axis_guess(ay, y), k = 0;
     double xh, yh, zh = 0.0;
     if (keep_k)
@@ -2214,12 +2217,12 @@ __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T
     axis_correct(ay, y, j, c.y0, yh);
     if (!keep_k) {
         axis_correct(az, z, k, c.z0, zh);
-        c.wz = high_word(zh - c.z0);
+        c.wz = offset_bound(az, k, c.z0, zh);
     }
     if constexpr (DL)
         c.kidx() = k;
-    c.wx = high_word(xh - c.x0);
-    c.wy = high_word(yh - c.y0);
+    c.wx = offset_bound(ax, i, c.x0, xh);
+    c.wy = offset_bound(ay, j, c.y0, yh);
     const size_t nx = (size_t)ax.n, plane = nx * (size_t)ay.n;
     const size_t n000 = (size_t)k * plane + (size_t)j * nx + (size_t)i;
     const size_t off[8] = {0, 1, nx, nx + 1, plane, plane + 1, plane + nx, plane + nx + 1};
@@ -2291,13 +2294,12 @@ __device__ inline bool reload3(const AdvectParams &P, Cell3<typename Real<ST>::T
     return true;
 }
 
-// Whether a point at offsets t from the lower faces is in the cached cell (see Cell2: 12
-// FP64 instructions of a stage, three differences and six compares among them, for three
-// products and three 32-bit compares).
+// Whether a point at offsets t from the lower faces is in the cached cell (see Cell2: three
+// products and three compares in place of 12 FP64 instructions of a stage).
 template <class R, bool DL>
 __device__ inline bool in_cell3(const Cell3<R, DL> &c, double tx, double ty, double tz)
 {
-    return (high_word(tx) < c.wx) & (high_word(ty) < c.wy) & (high_word(tz) < c.wz);
+    return (bits(tx) < c.wx) & (bits(ty) < c.wy) & (bits(tz) < c.wz);
 }
 
 // With FP64 coefficients the cell carries the coefficients at the last stage's time,
@@ -2453,31 +2455,25 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                 if (!ok)
                     goto fail;
                 {
-                    // the end point, and its offsets in the last stage's cell
                     const double g = P.scheme ? dt : dt6;
                     const double dx = P.scheme ? k[0] : sm[0] + k[0];
                     const double dy = P.scheme ? k[1] : sm[1] + k[1];
                     const double dz = P.scheme ? k[2] : sm[2] + k[2];
                     double xs = fma(dx, g, x), ys = fma(dy, g, y), zs = fma(dz, g, z);
-                    double tx = fma(dx, g, b[0]), ty = fma(dy, g, b[1]), tz = fma(dz, g, b[2]);
-                    if (BEHAVE && horizontal) {  // a dwelling particle keeps its depth
+                    if (BEHAVE && horizontal)  // a dwelling particle keeps its depth
                         zs = z;
-                        tz = b[2];
-                    }
                     if (BROWN && P.Kh > 0.0) {
                         double wx, wy;
                         brownian_metres<MET == kFlat>(P, id, P.step0 + s, dt, wx, wy);
                         if constexpr (MET != kFlat) {
-                            wx = wx * inv_metres_lon<MET>(c, P, ty, ys);
+                            wx = wx * inv_metres_lon<MET>(c, P, ys - c.y0, ys);
                             wy = wy * (1.0 / kMetresPerDegree);
                         }
                         xs = xs + wx;
                         ys = ys + wy;
-                        tx = xs - c.x0;  // (of the rounded end point: both sides of a face agree)
-                        ty = ys - c.y0;
                     }
-                    bool land;
-                    if (in_cell3(c, tx, ty, tz)) {
+                    bool land;  // (by the rounded end point: both sides of a face agree)
+                    if (in_cell3(c, xs - c.x0, ys - c.y0, zs - c.z0)) {
                         land = c.land;
                     } else {
                         const uint8_t e = point_status<true>(P.g, xs, ys, zs);
