@@ -280,25 +280,26 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t *order_in,
 }
 
 // ---------------------------------------------------------------- sorts in LDS
-// With up to kSortBins bins (2D grids up to about 2000 x 2000 nodes) a block counts its
+// With up to kSortBins bins (2D grids up to about 1250 x 1250 nodes) a block counts its
 // part of the list in LDS and no global atomic is taken: k_sort_hist writes one row of
 // counts per block, k_sort_columns turns each bin's column into offsets, and k_sort_apply
 // scans the totals, each block for itself, and hands out places from LDS counters.  Bound
-// by the chain of reads order -> position -> cell faces, so a thread has kSortItems of them
-// in flight, and a block only 2048 particles until there are 256 blocks (with 4096 a block
-// k_sort_hist took 13.5 us for 10k particles, not 7.2; one block for the whole list 24).
-// 13 + 5 + 8 us for 500k particles in 4050 bins, 7 + 3 + 5 us for 10k (a call of 60 steps
-// on 10k: 155 -> 144 us; 24 sets of 1k to 2M in one batch: 68 -> 63 ms).  The six launches
-// above take one global atomic per particle, 54 + 52 us on average over those 24 sets and
-// up to 1.4 ms for the largest; they stay for grids with more bins.
-constexpr uint32_t kSortBins = 15360, kSortThreads = 1024;
-constexpr int kSortItems = 2;
-constexpr uint32_t kSortStep = kSortItems * kSortThreads;
+// by the chain of reads order -> position -> cell faces, once per thread until there are
+// 256 blocks (with two particles a thread k_sort_hist took 10.9 us for 20k particles, not
+// 6.6: half the blocks, and twice the code for each to fetch).  7 + 3 + 5 us for 20k
+// particles in 4050 bins, 13 + 5 + 8 for 500k.
+// The six launches above take one global atomic per particle, which on lists with many
+// particles a bin, or all in one, cost up to 1.4 ms; but they do not read and write a row
+// of bins per block.  The line is where evenly spread lists take as long either way (16
+// steps with a sort before each, LDS against atomics): 0.61 and 0.63 ms for 20k particles in
+// 4050 bins, 0.61 and 0.64 in 6072, 0.65 and 0.65 in 7497, 0.67 and 0.65 in 14875; 1.22 and
+// 1.24 for 400k in 6072, 1.28 and 1.22 in 7497.
+constexpr uint32_t kSortBins = 6144, kSortThreads = 1024;
 constexpr uint32_t kSortGroups = 16;  // row groups of k_sort_columns
 
 __host__ __device__ inline uint32_t sort_parts(uint32_t n)
 {
-    const uint32_t parts = (n + kSortStep - 1) / kSortStep;  // at most 256 blocks
+    const uint32_t parts = (n + kSortThreads - 1) / kSortThreads;  // at most 256 blocks
     return parts < 256 ? (parts ? parts : 1) : 256;
 }
 
@@ -308,52 +309,31 @@ __host__ __device__ inline uint32_t sort_chunk(uint32_t n)
     return ((n + parts - 1) / parts + kSortThreads - 1) / kSortThreads * kSortThreads;
 }
 
-// ids and keys of the list positions k0 + q kSortThreads below hi (hi > 0)
-template <int Q>
-__device__ inline void sort_load(const GridDev &g, const double *x, const double *y,
-                                 const double *z, const uint8_t *status, const uint32_t *order,
-                                 uint32_t k0, uint32_t hi, bool cells, uint32_t *id, uint32_t *key)
+// The key of list entry `id`, with its reads overlapped (0xFFFFFFFF: not active).
+__device__ inline uint32_t sort_load(const GridDev &g, const double *x, const double *y,
+                                     const double *z, const uint8_t *status, uint32_t id,
+                                     bool cells)
 {
     const AxisDev *ax[3] = {&g.ax, &g.ay, &g.az};
-    uint8_t st[Q];
-    double p[Q][3], lo[Q][3], up[Q][3];
-    int c[Q][3];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const uint32_t k = k0 + (uint32_t)q * kSortThreads;
-        id[q] = order[k < hi ? k : hi - 1];
-    }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        st[q] = status[id[q]];
-        p[q][0] = x[id[q]];
-        p[q][1] = y[id[q]];
-        p[q][2] = g.az.n ? z[id[q]] : 0.0;
-    }
+    const uint8_t st = status[id];
+    const double p[3] = {x[id], y[id], g.az.n ? z[id] : 0.0};
+    double lo[3], up[3];
+    int c[3] = {0, 0, 0};
 #pragma unroll
     for (int v = 0; v < 3; ++v)
         if (v < 2 || g.az.n)
+            c[v] = cell_guess(*ax[v], p[v]);
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-                c[q][v] = cell_guess(*ax[v], p[q][v]);
+    for (int v = 0; v < 3; ++v)
+        if (v < 2 || g.az.n) {
+            lo[v] = ax[v]->c[c[v]];
+            up[v] = ax[v]->c[c[v] + 1];
+        }
 #pragma unroll
     for (int v = 0; v < 3; ++v)
         if (v < 2 || g.az.n)
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                lo[q][v] = ax[v]->c[c[q][v]];
-                up[q][v] = ax[v]->c[c[q][v] + 1];
-            }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const uint32_t k = k0 + (uint32_t)q * kSortThreads;
-        int m[3] = {0, 0, 0};
-#pragma unroll
-        for (int v = 0; v < 3; ++v)
-            if (v < 2 || g.az.n)
-                m[v] = cell_settle(*ax[v], p[q][v], c[q][v], lo[q][v], up[q][v]);
-        key[q] = k < hi && st[q] == 0 ? sort_key(g, m[0], m[1], m[2], cells) : 0xFFFFFFFFu;
-    }
+            c[v] = cell_settle(*ax[v], p[v], c[v], lo[v], up[v]);
+    return st == 0 ? sort_key(g, c[0], c[1], c[2], cells) : 0xFFFFFFFFu;
 }
 
 __global__ __launch_bounds__(kSortThreads) void k_sort_hist(
@@ -367,17 +347,11 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(
     __syncthreads();
     const uint32_t n = *n_in, lo = blockIdx.x * chunk;
     const uint32_t hi = lo + chunk < n ? lo + chunk : n;
-    for (uint32_t k0 = lo; k0 < hi; k0 += kSortStep) {
-        uint32_t id[kSortItems], key[kSortItems];
-        sort_load<kSortItems>(g, x, y, z, status, order, k0 + threadIdx.x, hi, cells, id, key);
-#pragma unroll
-        for (int q = 0; q < kSortItems; ++q) {
-            const uint32_t k = k0 + threadIdx.x + (uint32_t)q * kSortThreads;
-            if (key[q] != 0xFFFFFFFFu)
-                atomicAdd(&bins[key[q]], 1u);
-            if (k < hi)
-                keys[k] = key[q];
-        }
+    for (uint32_t k = lo + threadIdx.x; k < hi; k += kSortThreads) {
+        const uint32_t key = sort_load(g, x, y, z, status, order[k], cells);
+        if (key != 0xFFFFFFFFu)
+            atomicAdd(&bins[key], 1u);
+        keys[k] = key;
     }
     __syncthreads();
     for (uint32_t b = threadIdx.x; b < nbins; b += kSortThreads)
@@ -461,30 +435,42 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_apply(const uint32_t *ord
                                                              uint32_t *order_out, uint32_t *n_out)
 {
     extern __shared__ uint32_t bins[];
-    for (uint32_t b = threadIdx.x; b < nbins; b += kSortThreads)
-        bins[b] = totals[b];
+    // (every read of the totals and of the block's row goes out before any is used: in a
+    // loop over the bins each waited for the one before, 12.9 us in place of 7.2 for 14875)
+    constexpr int kPer = kSortBins / kSortThreads;
+    uint32_t tot[kPer], row[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const uint32_t b = threadIdx.x + (uint32_t)q * kSortThreads;
+        if ((uint32_t)q * kSortThreads < nbins) {
+            tot[q] = b < nbins ? totals[b] : 0u;
+            row[q] = b < nbins ? rows[(size_t)blockIdx.x * nbins + b] : 0u;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const uint32_t b = threadIdx.x + (uint32_t)q * kSortThreads;
+        if (b < nbins)
+            bins[b] = tot[q];
+    }
     __syncthreads();
     const uint32_t total = scan_bins(bins, nbins);
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *n_out = total;
     __syncthreads();
-    for (uint32_t b = threadIdx.x; b < nbins; b += kSortThreads)
-        bins[b] += rows[(size_t)blockIdx.x * nbins + b];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const uint32_t b = threadIdx.x + (uint32_t)q * kSortThreads;
+        if (b < nbins)
+            bins[b] += row[q];
+    }
     __syncthreads();
     const uint32_t n = *n_in, lo = blockIdx.x * chunk;
     const uint32_t hi = lo + chunk < n ? lo + chunk : n;
-    for (uint32_t k0 = lo + threadIdx.x; k0 < hi; k0 += kSortStep) {
-        uint32_t id[kSortItems], key[kSortItems];
-#pragma unroll
-        for (int q = 0; q < kSortItems; ++q) {
-            const uint32_t k = k0 + (uint32_t)q * kSortThreads;
-            key[q] = k < hi ? keys[k] : 0xFFFFFFFFu;
-            id[q] = k < hi ? order_in[k] : 0u;
-        }
-#pragma unroll
-        for (int q = 0; q < kSortItems; ++q)
-            if (key[q] != 0xFFFFFFFFu)
-                order_out[atomicAdd(&bins[key[q]], 1u)] = id[q];
+    for (uint32_t k = lo + threadIdx.x; k < hi; k += kSortThreads) {
+        const uint32_t key = keys[k], id = order_in[k];
+        if (key != 0xFFFFFFFFu)
+            order_out[atomicAdd(&bins[key], 1u)] = id;
     }
 }
 
