@@ -313,6 +313,15 @@ __device__ inline double cos_series(double cl, double sl, double y0, double y, i
     return cl * cd - sl * sd;
 }
 
+// The same with two terms (cells of at most 0.3 degrees), at dl degrees from the face.
+__device__ inline double cos_series2(double cl, double sl, double dl)
+{
+    const double d = dl * kDegToRad, d2 = d * d;
+    const double cd = fma(d2, fma(d2, 1.0 / 24.0, -0.5), 1.0);
+    const double sd = d * fma(d2, fma(d2, 1.0 / 120.0, -1.0 / 6.0), 1.0);
+    return cl * cd - sl * sd;
+}
+
 // 1 / d to within an ulp or two: hardware reciprocal refined by two Newton steps
 __device__ inline double recip(double d)
 {
@@ -333,43 +342,40 @@ __device__ inline double quotient(double n, double d)
 }
 
 // The latitude row that a gather's metric starts from: its lower face, and the tables'
-// cosine and sine there (read with the stencil; zero without tables).
+// cosine and sine there (read with the stencil).
 struct LatRow {
     double y0, cl, sl;
 };
 
 __device__ inline LatRow lat_row(const GridDev &g, int j, double y0)
 {
-    return {y0, *(g.coslat ? g.coslat + j : &kAbsentTable), *(g.coslat ? g.sinlat + j : &kAbsentTable)};
+    return {y0, g.coslat[j], g.sinlat[j]};
 }
 
-// A sample's velocity in coordinate units per second (degrees on the sphere), and the
-// metric M cos(lat) that it divided by (1 on a flat mesh).  The adaptive lanes (ADAPT) take
-// the cosine of FP64 values from the cell's latitude tables, as the cached kernels do, and
-// its reciprocal from recip (RKF45 on 1M particles of the 0.25 degree field 1.14 ms a
-// launch in place of 1.24); grids without tables (cells taller than 5 degrees) the library's.
+// A sample's velocity in coordinate units per second (degrees on the sphere), and with TAB
+// the metric M cos(lat) that it divided by.  TAB, for the adaptive lanes on spherical grids
+// of FP64 values whose cells are at most 0.3 degrees tall: the cosine comes from the cell's
+// latitude tables, as in the cached kernels, and its reciprocal from recip (1M particles on
+// the 0.25 degree field 1.10 ms a launch in place of 1.25).  Taller cells would take the
+// longer series, whose constants cost these kernels the registers that they gain (300k
+// particles on 2 degrees 0.54 ms, 0.49 with the library).
 // The RK4 gathers are bound by their reads, and the two of the tables cost them more than
 // the library's cosine and division: 288 steps of 1M particles 8.65 ms for FP32 fields and
 // 12.7 for FP64 (8.78 and 13.7 with tables), in 3D 4.23 and 7.53 for 48 steps (4.35, 7.70).
-template <int ST, bool ADAPT>
+template <int ST, bool TAB>
 __device__ inline bool sample_finish(const AdvectParams &P, double y, const LatRow &lr,
                                      const typename Real<ST>::T v[3], double k[3], double &m)
 {
     using R = typename Real<ST>::T;
-    m = 1.0;
-    if (P.g.spherical) {
+    static_assert(!TAB || sizeof(R) == 8, "the tables are for FP64 values");
+    if constexpr (TAB) {
+        m = kMetresPerDegree * cos_series2(lr.cl, lr.sl, y - lr.y0);
+        k[0] = v[0] * recip(m);
+        k[1] = v[1] * (1.0 / kMetresPerDegree);
+    } else if (P.g.spherical) {
         if constexpr (sizeof(R) == 8) {
-            if (ADAPT && P.g.coslat)
-                m = kMetresPerDegree * cos_series(lr.cl, lr.sl, lr.y0, y, P.g.cos_terms);
-            else
-                m = kMetresPerDegree * cos(y * kDegToRad);
-            if constexpr (ADAPT) {
-                k[0] = v[0] * recip(m);
-                k[1] = v[1] * (1.0 / kMetresPerDegree);
-            } else {
-                k[0] = v[0] / m;
-                k[1] = v[1] / kMetresPerDegree;
-            }
+            k[0] = v[0] / (kMetresPerDegree * cos(y * kDegToRad));
+            k[1] = v[1] / kMetresPerDegree;
         } else {
             const float cl = cosf((float)(y * kDegToRad));
             k[0] = (double)(v[0] / ((float)kMetresPerDegree * cl));
@@ -418,7 +424,7 @@ __device__ inline void bilinear_from(const typename Real<ST>::T f[4][3], double 
 // guessed cell (inside the grid, whatever the guess) are read together with that
 // cell's faces and widths, and read again only where the correction moves the cell.
 // The arithmetic is the same as locate_point followed by spatial.
-template <int ST, bool STEADY>
+template <int ST, bool STEADY, bool TAB>
 __device__ inline bool gather2(const AdvectParams &P, const TimeEntry &te, double x, double y,
                                typename Real<ST>::T a[3], typename Real<ST>::T b[3], LatRow &lr)
 {
@@ -433,11 +439,13 @@ __device__ inline bool gather2(const AdvectParams &P, const TimeEntry &te, doubl
     corners2<ST>(P, te.sa, fx.g, fy.g, fa);
     if constexpr (!STEADY)
         corners2<ST>(P, te.sb, fx.g, fy.g, fb);
-    lr = lat_row(g, fy.g, fy.lo);
+    if constexpr (TAB)
+        lr = lat_row(g, fy.g, fy.lo);
     find_finish<true>(g.ax, x, fx);
     find_finish<true>(g.ay, y, fy);
     if (fx.g != fx.g0 || fy.g != fy.g0) {
-        lr = lat_row(g, fy.g, fy.lo);
+        if constexpr (TAB)
+            lr = lat_row(g, fy.g, fy.lo);
         corners2<ST>(P, te.sa, fx.g, fy.g, fa);
         if constexpr (!STEADY)
             corners2<ST>(P, te.sb, fx.g, fy.g, fb);
@@ -453,12 +461,12 @@ __device__ inline bool gather2(const AdvectParams &P, const TimeEntry &te, doubl
     return true;
 }
 
-// Velocity at a stage point in coordinate units per second; false if outside.  ADAPT: for
-// an adaptive lane (see sample_finish).  SPEC
+// Velocity at a stage point in coordinate units per second; false if outside.  TAB: see
+// sample_finish.  SPEC
 // reads the corners of the guessed cell together with its faces (2D only): the RKF45
 // lane on FP32 fields gains 4% from it; in the RK4 gather kernels the registers it
 // holds cost as much as it saves, and the other storage forms of the RKF45 lane spill.
-template <int ST, bool IS3D, bool STEADY, bool ADAPT = false, bool SPEC = false>
+template <int ST, bool IS3D, bool STEADY, bool TAB = false, bool SPEC = false>
 __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double x, double y,
                               double z, double k[3], double &m)
 {
@@ -467,7 +475,7 @@ __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double
     LatRow lr;
     if constexpr (SPEC && !IS3D) {
         R a[3], b[3];
-        if (!gather2<ST, STEADY>(P, te, x, y, a, b, lr))
+        if (!gather2<ST, STEADY, TAB>(P, te, x, y, a, b, lr))
             return false;
         if constexpr (STEADY) {
 #pragma unroll
@@ -479,12 +487,12 @@ __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double
             for (int q = 0; q < 3; ++q)
                 v[q] = ((R)1 - tau) * a[q] + tau * b[q];
         }
-        return sample_finish<ST, ADAPT>(P, y, lr, v, k, m);
+        return sample_finish<ST, TAB>(P, y, lr, v, k, m);
     }
     Cell c;
     if (!locate_point<IS3D, true>(P.g, x, y, z, c))
         return false;
-    if constexpr (ADAPT)
+    if constexpr (TAB)
         lr = lat_row(P.g, c.j, c.y0);
     if (P.nearest) {
         c.xi = c.xi < 0.5 ? 0.0 : 1.0;
@@ -502,7 +510,7 @@ __device__ inline bool sample(const AdvectParams &P, const TimeEntry &te, double
         for (int q = 0; q < 3; ++q)
             v[q] = ((R)1 - tau) * a[q] + tau * b[q];
     }
-    return sample_finish<ST, ADAPT>(P, y, lr, v, k, m);
+    return sample_finish<ST, TAB>(P, y, lr, v, k, m);
 }
 
 // Philox4x32-10 (Salmon et al., SC'11): ten Philox-4x32 rounds, key bumped by the
@@ -955,7 +963,7 @@ struct Fehlberg {
 
 // One attempt of signed size h from p at time t: fourth-order end point p4 and
 // error estimate ev (fifth minus fourth order); false if a stage leaves the grid.
-template <int ST, bool IS3D, bool STEADY>
+template <int ST, bool IS3D, bool STEADY, bool TAB>
 __device__ inline bool rkf45_attempt(const AdvectParams &P, double t, double h,
                                      const double p[3], double p4[3], double ev[3],
                                      LaneTime &lt, double &m0)
@@ -975,7 +983,7 @@ __device__ inline bool rkf45_attempt(const AdvectParams &P, double t, double h,
         }
         const TimeEntry te = bracket_lane(P, t + Fehlberg::c[i] * h, lt);
         double m = 1.0;
-        ok = sample<ST, IS3D, STEADY, true, ST == kF32>(P, te, q[0], q[1], q[2], k[i], m) & ok;
+        ok = sample<ST, IS3D, STEADY, TAB, ST == kF32>(P, te, q[0], q[1], q[2], k[i], m) & ok;
         if (i == 0)
             m0 = m;  // the metric at the step's start, for the error's length
     }
@@ -1030,7 +1038,7 @@ __device__ inline void rkf_commit(const AdvectParams &P, RkfState &s, double err
 
 // One particle's state for the gather form (2D or 3D): every stage gathers its
 // stencil from the snapshots.
-template <int ST, bool IS3D, bool STEADY>
+template <int ST, bool IS3D, bool STEADY, bool TAB>
 struct GatherLane {
     RkfState s;
     double p[3];
@@ -1065,17 +1073,14 @@ struct GatherLane {
         const bool cut = h >= rem;
         const double hs = sg * (cut ? rem : h);
         double p4[3], ev[3], m0 = 1.0;
-        if (!rkf45_attempt<ST, IS3D, STEADY>(P, s.t, hs, p, p4, ev, lt, m0)) {
+        if (!rkf45_attempt<ST, IS3D, STEADY, TAB>(P, s.t, hs, p, p4, ev, lt, m0)) {
             ++acc;
             s.st = (uint8_t)(ST_OOB | extra);
             return true;
         }
         double ex = ev[0], ey = ev[1];
-        if (P.g.spherical) {
-            if constexpr (sizeof(typename Real<ST>::T) == 8)
-                ex = ex * m0;
-            else  // (the FP32 gathers' metric is FP32)
-                ex = ex * (kMetresPerDegree * cos(p[1] * kDegToRad));
+        if (TAB || P.g.spherical) {
+            ex = ex * (TAB ? m0 : kMetresPerDegree * cos(p[1] * kDegToRad));
             ey = ey * kMetresPerDegree;
         }
         const double err = sqrt((ex * ex + ey * ey) + ev[2] * ev[2]);
@@ -2013,11 +2018,11 @@ __device__ inline void rkf45_refill(const AdvectParams &P)
 }
 
 // 4 waves per SIMD in 2D (the kernel needs one register more than that allows)
-template <int ST, bool IS3D, bool STEADY>
+template <int ST, bool IS3D, bool STEADY, bool TAB>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(IS3D ? 1 : 4))) void k_rkf45(AdvectParams P)
 {
-    rkf45_refill<GatherLane<ST, IS3D, STEADY>>(P);
+    rkf45_refill<GatherLane<ST, IS3D, STEADY, TAB>>(P);
 }
 
 template <int ST, bool STEADY, int MET>
@@ -2765,8 +2770,13 @@ hipError_t rkf3(const AdvectParams &p, bool steady, uint32_t n_launch, hipStream
             return e;
         }
     }
-    return steady ? launch_persistent(k_rkf45<ST, IS3D, true>, p, n_launch, s)
-                  : launch_persistent(k_rkf45<ST, IS3D, false>, p, n_launch, s);
+    if constexpr (sizeof(typename Real<ST>::T) == 8) {
+        if (p.g.spherical && p.g.coslat && p.g.cos_terms == 2)
+            return steady ? launch_persistent(k_rkf45<ST, IS3D, true, true>, p, n_launch, s)
+                          : launch_persistent(k_rkf45<ST, IS3D, false, true>, p, n_launch, s);
+    }
+    return steady ? launch_persistent(k_rkf45<ST, IS3D, true, false>, p, n_launch, s)
+                  : launch_persistent(k_rkf45<ST, IS3D, false, false>, p, n_launch, s);
 }
 
 }  // namespace
