@@ -290,35 +290,27 @@ __device__ inline void spatial(const AdvectParams &P, int sidx, const Cell &c,
     }
 }
 
-// cos of a latitude in a cell whose lower face has cosine cl and sine sl: cos(l0 + dl) =
-// cos l0 cos dl - sin l0 sin dl with dl = lat - l0 and cos dl, sin dl by their Taylor
-// series, cut after 2, 3 or 4 terms so that the truncation stays below a quarter ulp for
-// the grid's tallest cell (0.3, 1.5 or 5 degrees).
-__device__ inline double cos_series(double cl, double sl, double y0, double y, int terms)
-{
-    const double dl = (y - y0) * kDegToRad, d2 = dl * dl;
-    double cd, sd;
-    if (terms <= 2) {
-        cd = fma(d2, fma(d2, 1.0 / 24.0, -0.5), 1.0);
-        sd = dl * fma(d2, fma(d2, 1.0 / 120.0, -1.0 / 6.0), 1.0);
-    } else if (terms == 3) {
-        cd = fma(d2, fma(d2, fma(d2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);
-        sd = dl * fma(d2, fma(d2, fma(d2, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0), 1.0);
-    } else {
-        cd = fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 40320.0, -1.0 / 720.0), 1.0 / 24.0), -0.5),
-                 1.0);
-        sd = dl * fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 362880.0, -1.0 / 5040.0), 1.0 / 120.0),
-                              -1.0 / 6.0), 1.0);
-    }
-    return cl * cd - sl * sd;
-}
-
-// The same with two terms (cells of at most 0.3 degrees), at dl degrees from the face.
+// cos of a latitude in a cell whose lower face has cosine cl and sine sl, at dl degrees from
+// it: cos(l0 + d) = cos l0 cos d - sin l0 sin d with cos d, sin d by their Taylor series, cut
+// so that the truncation stays below a quarter ulp: after 2 terms for cells of at most 0.3
+// degrees, after 4 for any with tables (5 degrees; a series of 3 terms up to 1.5 degrees,
+// chosen in the stage, cost the cached kernels more than its term saves: 50k particles on 2
+// degrees 0.37 ms for 288 steps, 0.29 so, 1M 2.40 and 2.07).
 __device__ inline double cos_series2(double cl, double sl, double dl)
 {
     const double d = dl * kDegToRad, d2 = d * d;
     const double cd = fma(d2, fma(d2, 1.0 / 24.0, -0.5), 1.0);
     const double sd = d * fma(d2, fma(d2, 1.0 / 120.0, -1.0 / 6.0), 1.0);
+    return cl * cd - sl * sd;
+}
+
+__device__ inline double cos_series4(double cl, double sl, double dl)
+{
+    const double d = dl * kDegToRad, d2 = d * d;
+    const double cd =
+        fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 40320.0, -1.0 / 720.0), 1.0 / 24.0), -0.5), 1.0);
+    const double sd = d * fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 362880.0, -1.0 / 5040.0),
+                                              1.0 / 120.0), -1.0 / 6.0), 1.0);
     return cl * cd - sl * sd;
 }
 
@@ -1138,7 +1130,7 @@ struct Cell2 {
     double x0, y0;          // lower faces
     uint64_t wx, wy;        // bits of the cell widths (offset_bound)
     double rx, ry;          // inverse cell widths (FP32 coefficients and the tracer sample)
-    double m[5];            // metric: see metric_poly; with the 3/4-term series m[0], m[1] are
+    double m[5];            // metric: see metric_poly; with the 4-term series m[0], m[1] are
                             // M cos and M sin of the lower latitude face
     // U, V coefficients of the earlier snapshot [0..7] and of the later one [8..15]
     R *lc;                  // LDS: this lane's first 16-byte group of coefficients
@@ -1258,7 +1250,7 @@ __device__ inline void metric_poly(double mc, double ms, double m[5])
 }
 
 // What a cell keeps of its lower face's M cos and M sin: the polynomial, or with the
-// 3/4-term series the two themselves.
+// 4-term series the two themselves.
 template <int MET>
 __device__ inline void metric_of_face(double mc, double ms, double m[5])
 {
@@ -1419,7 +1411,7 @@ __device__ inline double east_slope(const CellT &c, const AdvectParams &P, doubl
     else if constexpr (MET == kSphTable2)
         m = FULL ? metric_at5(c.m, t) : metric_at(c.m, t);
     else
-        m = cos_series(c.m[0], c.m[1], 0.0, t, P.g.cos_terms);
+        m = cos_series4(c.m[0], c.m[1], t);
     return FULL ? quotient(u, m) : u * recip_stage(m);
 }
 
@@ -1432,7 +1424,7 @@ __device__ inline double inv_metres_lon(const CellT &c, const AdvectParams &P, d
     if constexpr (met_series<MET>()) {
         if (bits(t) < c.wy) {
             if constexpr (MET == kSphTable)
-                return recip(cos_series(c.m[0], c.m[1], 0.0, t, P.g.cos_terms));
+                return recip(cos_series4(c.m[0], c.m[1], t));
             return recip(metric_at5(c.m, t));
         }
     }
@@ -1802,10 +1794,19 @@ __device__ inline long long advect_lane_2d(const AdvectParams &P, uint32_t k, ui
 // Occupancy targets: 4 waves per SIMD with the LDS cache (the 8 coefficients at the
 // stage time that the lane keeps between stages take the registers of a fifth wave;
 // the LDS saved, a quarter to a half of the reads, is worth more), 3 with the Brownian
-// term.
+// term, and 3 with an age or a tracer sample on FP64 fields and the four-term series, which
+// spills 92 B at 4 (1M particles on 2 degrees, 288 steps: 2.92 and 2.55 ms).
+template <int ST, int MET, bool BROWN, bool BEHAVE>
+constexpr int waves2d()
+{
+    if (BROWN || (BEHAVE && MET == kSphTable && ST == kF64))
+        return 3;
+    return MET == kSphLib ? 1 : 4;
+}
+
 template <int ST, bool STEADY, int MET, bool BROWN, bool BEHAVE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    BROWN ? 3 : (MET == kSphLib ? 1 : 4)))) void k_advect2d(
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(waves2d<ST, MET, BROWN, BEHAVE>()))) void k_advect2d(
     AdvectParams P)
 {
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
@@ -2432,7 +2433,7 @@ __attribute__((amdgpu_waves_per_eu(cache3_lds<ST, STEADY, MET, BROWN>() ? (sizeo
                 // and FP16 forms), and with FP64 ones for FP32 fields in the 2-term and flat
                 // metric modes without the behaviour or Brownian terms (+8.7% on cfg2, no
                 // spill in the loop). The other FP64 forms spill more unrolled (the
-                // behaviour kernels lost 1.9%, the 3/4-term series spills 92 B), so they
+                // behaviour kernels lost 1.9%, the 4-term series spills 92 B), so they
                 // keep the rolled loop.
                 constexpr bool kUnrollF64 = ST == kF32 && !BEHAVE && !BROWN &&
                                             (MET == kSphTable2 || MET == kFlat);
@@ -2880,7 +2881,7 @@ hipError_t launch_advect_batch(int store, bool steady, int met, bool brown,
         q.g.coslat = (met == kSphTable || met == kSphTable2)
                          ? reinterpret_cast<const double *>(1)
                          : nullptr;
-        q.g.cos_terms = met == kSphTable2 ? 2 : 3;
+        q.g.cos_terms = met == kSphTable2 ? 2 : 4;
         q.Kh = brown ? 1.0 : 0.0;
         hipError_t r = hipSuccess;
         (void)dispatch_cached(q, steady, [&](auto stc, auto m, auto b) {

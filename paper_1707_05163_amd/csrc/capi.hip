@@ -249,7 +249,7 @@ extern "C" int fieldset_create(const lp_grid_desc *g, lp_fieldset **out)
             fs->g.coslat = fs->dcoslat;
             fs->g.sinlat = fs->dsinlat;
             // truncation of the series below a quarter ulp for the tallest cell
-            fs->g.cos_terms = tallest <= 0.3 ? 2 : (tallest <= 1.5 ? 3 : 4);
+            fs->g.cos_terms = tallest <= 0.3 ? 2 : 4;
         }
     }
     if (g->land) {
