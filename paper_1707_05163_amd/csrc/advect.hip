@@ -2038,12 +2038,24 @@ __global__ __launch_bounds__(kBlock) void k_rkf45_2d(AdvectParams P)
 // ranges, one per XCD, each with its own atomic counter.  A block takes items from
 // the range of the XCD it runs on and, when that is exhausted, from the others;
 // every block leaves once all 8 ranges are exhausted, so the grid always drains.
-// Occupancy target: 4 waves per SIMD (at most 128 VGPRs) for the plain modes, where
-// it costs one spill outside the step loop; 3 for the Brownian term and the library
-// cosine, whose extra state would spill inside it.
+// Occupancy target: 4 waves per SIMD (at most 128 VGPRs), and 3 where the state would
+// spill inside the step loop: with the Brownian term, the library cosine, the four-term
+// series on FP32 and FP64 fields, and two terms on FP64.  5 runs of 200k particles, 288
+// steps, at 4 and at 3 waves: four terms 5.48 and 2.84 ms (FP32), 4.79 and 2.83 (FP64);
+// two terms 2.51 and 2.56 (FP32), 3.06 and 2.61 (FP64); flat 2.50 and 2.87.
+template <int ST, bool STEADY, int MET, bool BROWN>
+constexpr int waves_batch()
+{
+    if (BROWN || MET == kSphLib)
+        return 3;
+    if (STEADY)
+        return 4;
+    return (ST == kF64 && MET != kFlat) || (ST == kF32 && MET == kSphTable) ? 3 : 4;
+}
+
 template <int ST, bool STEADY, int MET, bool BROWN>
 __global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(BROWN || MET == kSphLib ? 3 : 4))) void k_advect2d_batch(
+__attribute__((amdgpu_waves_per_eu(waves_batch<ST, STEADY, MET, BROWN>()))) void k_advect2d_batch(
     const AdvectParams *__restrict__ runs, const uint32_t *__restrict__ cstart, int nruns,
     uint32_t total, uint32_t *queues)
 {
