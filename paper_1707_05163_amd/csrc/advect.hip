@@ -1192,10 +1192,9 @@ template <int ST, bool BROWN>
 constexpr int cache_lds_coefs() { return BROWN ? 0 : 16; }
 
 // Metric modes of the cached kernels, fixed at compile time so that a launch carries
-// only the code it runs: flat mesh; spherical with the latitude tables and a series
-// whose length (3 or 4 terms) is read at run time; spherical with cells too tall for
-// the series (library cos); spherical with the 2-term series (cells up to 0.3 degree,
-// the common fine-grid case, with no branch on the length).
+// only the code it runs: flat mesh; spherical with the latitude tables and the 4-term
+// series; spherical with cells too tall for the series (library cos); spherical with the
+// 2-term series (cells up to 0.3 degree, the common fine-grid case).
 enum : int { kFlat = 0, kSphTable = 1, kSphLib = 2, kSphTable2 = 3 };
 
 // Whether the cached 2D kernels keep the V coefficients in degrees of latitude per

@@ -98,7 +98,8 @@ struct AdvectParams {
     int8_t *hexp;            // per-particle step exponents, id order
     uint32_t *queues;        // 8 work-queue counters of the persistent launch
     unsigned long long *prej;// attempts retried at half the step (kCountWords words)
-    // the worked example's kernels ahead of each step's advection (gather kernels)
+    // the worked example's kernels ahead of each step's advection (k_advect, and with FP32
+    // and FP64 fields and no Brownian term the cached kernels)
     int32_t behave;          // 1: any of them is on
     int32_t sample;          // sample the tracer into temp
     double sink_speed;       // m/s, 0 = off

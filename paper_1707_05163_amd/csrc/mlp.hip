@@ -287,14 +287,15 @@ __global__ __launch_bounds__(kFusedThreads) void k_mlp_fused(MlpFusedArgs a)
 // waves; wave w owns output features 32 w .. 32 w + 31 of every layer, computed
 // transposed as in k_mlp_fused: weights (16 fragments straight from L2, each used once
 // by the block) are the matrix core's A operand, the layer's inputs its B operand, read
-// from LDS where the waves leave them bf16 [row][feature].  A wave keeps the derivative
-// of its features' GELU in registers from the forward pass for the backward one.  The
-// products take k in increasing order into one accumulator per output from zero, the
-// bias is added after them, and values round to bf16 where they are handed on, as the
-// layers' definition says, so a step's gradients do not depend on the batch's split.
-// 32 rows a block because the matrix instruction is 32 wide and a batch of 4096 then
-// fills half the CUs; what bounds a block is reading the weights (1.1 MB at 64 B per
-// clock, about 8 us).
+// from LDS where the waves leave them bf16 [row][feature].  The derivatives of the four
+// layers' GELU wait in 128 KB of LDS from the forward pass for the backward one, each
+// thread reading back what it wrote.  The products take k in increasing order into one
+// accumulator per output from zero, the bias is added after them, and values round to
+// bf16 where they are handed on, as the layers' definition says, so the gradients of a
+// row's pre-activations do not depend on the rows that share its block; the sums over
+// rows are k_train_wgrad's, in parts whose number goes with the batch.  32 rows a block
+// because the matrix instruction is 32 wide and a batch of 4096 then fills half the CUs;
+// what bounds a block is reading the weights (1.1 MB at 64 B per clock, about 8 us).
 constexpr int kActStride = kNetHid + 8;  // bf16 per activation row in LDS (no conflicts)
 
 // Two rows' bf16 values of two adjacent features, exchanged between neighbouring lanes

@@ -24,8 +24,9 @@ namespace {
 // the runs of an ensemble), and a hipMalloc and hipFree pair costs 13 us at 8 MB and 320 us
 // at 80 MB.  Freed blocks stay in lists by device and kind, at most kKeepDevice and
 // kKeepHost bytes of them, while any field set lives; they are given back when the last one
-// is destroyed, and when an allocation of the library fails.  A block is freed only when no work on it is
-// pending, so the next owner may use it on any stream.  One lock guards it all.
+// is destroyed, and when any allocation of the library fails (lp_malloc).  A block is freed
+// only when no work on it is pending, so the next owner may use it on any stream.  One lock
+// guards it all.
 constexpr size_t kKeepDevice = (size_t)1 << 30, kKeepHost = (size_t)64 << 20;
 
 struct Pool {
@@ -63,7 +64,8 @@ void purge_locked(Pool &P)
     P.kept_bytes[0] = P.kept_bytes[1] = 0;
 }
 
-// Chunks of pinned memory for results: at most one set is kept, by the same rules.
+// Chunks of pinned memory for results: a set of 16 MB at most (2 MB for small results), so
+// kKeepHost keeps up to four of them.
 constexpr size_t kChunk = (size_t)1 << 20;
 constexpr int kThreads = 8;  // host threads, two chunks each
 
