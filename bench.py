@@ -69,15 +69,15 @@ STATE_BYTES_RKF45_2D = STATE_BYTES_2D + 2  # plus the step exponent read and wri
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 COUNTER_SOURCE = "profiles/counters_k_advect2d_cfg1_k_advect3d_cfg2.md"
 COUNTERS = {
-    "advect_sha256": "60982b024b62cf64be1718ebe5eab3fa66111116c8cdd685a37acf93317eb1c7",
-    "cfg1": (183865.5, 64909.8),    # (FETCH_SIZE KiB, WRITE_SIZE KiB) per launch of k_advect2d
-    "cfg2": (7777542.9, 246625.2),  # the same for k_advect3d
+    "advect_sha256": "89982ade187c494d4bb4e9ed87f538ee9419de02353bce351d1206db7e0fc35a",
+    "cfg1": (184079.1, 64910.3),    # (FETCH_SIZE KiB, WRITE_SIZE KiB) per launch of k_advect2d
+    "cfg2": (7777789.5, 246445.1),  # the same for k_advect3d
     # (TCC_HIT_sum, TCC_MISS_sum) per launch: L2 requests of the same kernels
-    "cfg1_l2": (3991949.0, 4484334.7),
-    "cfg2_l2": (71172126.0, 126524412.7),
+    "cfg1_l2": (3999393.9, 4483383.1),
+    "cfg2_l2": (71372789.1, 126526834.7),
     # (SQ_INSTS_VALU, SQ_INSTS_SALU) wave instructions per launch
-    "cfg1_sq": (6.97042e+08, 4.75934e+08),
-    "cfg2_sq": (7.37159e+09, 2.67902e+09),
+    "cfg1_sq": (7.06107e+08, 4.76743e+08),
+    "cfg2_sq": (7.46500e+09, 2.69053e+09),
 }
 
 

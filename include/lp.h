@@ -313,6 +313,8 @@ int pset_records(lp_pset *ps, int64_t *nrec, int64_t *nper, double *lon, double 
 /* Sum and count of the timed advection launches since the last call (needs
  * opts.profile = 1).  Synchronises. */
 int pset_timing(lp_pset *ps, double *kernel_ms, int64_t *launches);
+/* The set's device blocks are kept for the next sets (at most 1 GiB of them a process) until
+ * the last field set is destroyed or an allocation of the library fails. */
 void pset_destroy(lp_pset *ps);
 
 /* The random numbers of the Brownian term (Sect. 4.2.7), computed on the device by
